@@ -1,41 +1,131 @@
 // Gaussian pyramid of target frames for the spatial hierarchy (Sec. 3.3):
 // each level is the previous one blurred by the separable 5-tap binomial
 // filter [1 4 6 4 1] / 16 and decimated by 2 (even rows and columns kept),
-// borders mirrored without repeating the edge sample.  One thread per output
-// pixel; HBM-bound (the 5 x 5 window is re-read from cache).
+// borders mirrored without repeating the edge sample.
+//
+// HBM-bound.  A thread computes a column strip of PYR_ROWS output rows, two
+// outputs wide: every input row is filtered horizontally once (the five most
+// recent results stay in registers for the vertical filter) instead of once
+// per output row that reads it, and one 16-byte load brings the four samples
+// under the two outputs; the three samples beside them are reads of the
+// neighbouring lanes' cache lines.  Sums run in the order of the direct 5 x 5
+// form (rows inside, columns outside), so the values are the same bit for bit.
+// 50 960x540 frames, 4 levels: 340 us with one output per thread (25
+// four-byte loads each), 105 us now; reading and writing every level
+// once at the copy rate would take 82 us.
 #include "gv_internal.h"
 
 namespace gv {
 
+constexpr int PYR_ROWS = 8;
+
+// i mirrored into [0, n) without repeating the edges.
 __device__ __forceinline__ int mirror_index(int i, int n) {
-    if (n == 1) return 0;
-    while (i < 0 || i >= n) i = i < 0 ? -i : 2 * (n - 1) - i;
-    return i;
+    if (n < 3) return n == 1 ? 0 : i & 1;  // period 2 (n - 1)
+    if (i < 0) i = -i;
+    return i >= n ? 2 * (n - 1) - i : i;
 }
 
-__global__ __launch_bounds__(256) void k_pyr_reduce(const float* __restrict__ in, float* __restrict__ out,
-                                                    int64_t planes, int H, int W, int Ho, int Wo) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t per = static_cast<int64_t>(Ho) * Wo;
-    if (i >= planes * per) return;
-    const int64_t p = i / per;
-    const int r = static_cast<int>(i - p * per);
-    const int y = r / Wo, x = r - y * Wo;
-    const float k[5] = {0.0625f, 0.25f, 0.375f, 0.25f, 0.0625f};
-    const float* src = in + p * static_cast<int64_t>(H) * W;
-    int xs[5];
+// Horizontal filter at the outputs x and x + 1 of one input row: the samples
+// 2x - 2 .. 2x + 4.  VEC: W % 4 == 0 and 16-byte aligned rows (x even).
+template <bool VEC>
+__device__ __forceinline__ float2 filter_row(const float* __restrict__ row, int x, int W) {
+    float v[7];
+    if (VEC) {
+        const float4 m = *reinterpret_cast<const float4*>(row + 2 * x);
+        const bool right = 2 * x + 4 < W;
+        const float2 l = *reinterpret_cast<const float2*>(row + (x > 0 ? 2 * x - 2 : 0));
+        const float r = row[right ? 2 * x + 4 : 0];
+        v[0] = x > 0 ? l.x : m.z;
+        v[1] = x > 0 ? l.y : m.y;
+        v[2] = m.x;
+        v[3] = m.y;
+        v[4] = m.z;
+        v[5] = m.w;
+        v[6] = right ? r : m.z;
+    } else {
+        // the second output may lie past the row: its samples are clamped
+        // into the mirror's reach and its value is not stored
 #pragma unroll
-    for (int d = 0; d < 5; ++d) xs[d] = mirror_index(2 * x + d - 2, W);
-    float acc = 0.0f;
-#pragma unroll
-    for (int dy = 0; dy < 5; ++dy) {
-        const float* row = src + static_cast<int64_t>(mirror_index(2 * y + dy - 2, H)) * W;
-        float h = 0.0f;
-#pragma unroll
-        for (int dx = 0; dx < 5; ++dx) h += k[dx] * row[xs[dx]];
-        acc += k[dy] * h;
+        for (int d = 0; d < 7; ++d) v[d] = row[mirror_index(min(2 * x + d - 2, W + 1), W)];
     }
-    out[i] = acc;
+    const float k[5] = {0.0625f, 0.25f, 0.375f, 0.25f, 0.0625f};
+    float2 h = make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int d = 0; d < 5; ++d) {
+        h.x += k[d] * v[d];
+        h.y += k[d] * v[d + 2];
+    }
+    return h;
+}
+
+// I: index type (32 bits while the threads and planes fit).
+template <bool VEC, typename I>
+__global__ __launch_bounds__(256) void k_pyr_reduce(const float* __restrict__ in, float* __restrict__ out, I threads,
+                                                    int H, int W, int Ho, int Wo) {
+    const I i = static_cast<I>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= threads) return;
+    const I pairs = static_cast<I>((Wo + 1) >> 1), strips = static_cast<I>((Ho + PYR_ROWS - 1) / PYR_ROWS);
+    const I r = i / pairs;
+    const int x = 2 * static_cast<int>(i - r * pairs);
+    const I p = r / strips;
+    const int y0 = static_cast<int>(r - p * strips) * PYR_ROWS;
+    const float* src = in + static_cast<int64_t>(p) * H * W;
+    float* dst = out + static_cast<int64_t>(p) * Ho * Wo + static_cast<int64_t>(y0) * Wo + x;
+    auto at = [&](int y) { return filter_row<VEC>(src + static_cast<int64_t>(mirror_index(y, H)) * W, x, W); };
+    const float k[5] = {0.0625f, 0.25f, 0.375f, 0.25f, 0.0625f};
+    float2 h[5];
+    h[0] = at(2 * y0 - 2);
+    h[1] = at(2 * y0 - 1);
+    h[2] = at(2 * y0);
+#pragma unroll
+    for (int j = 0; j < PYR_ROWS; ++j) {
+        const int y = min(y0 + j, Ho - 1);  // rows past the end repeat the last one's reads and are not stored
+        h[3] = at(2 * y + 1);
+        h[4] = at(2 * y + 2);
+        float2 acc = make_float2(0.0f, 0.0f);
+#pragma unroll
+        for (int d = 0; d < 5; ++d) {
+            acc.x += k[d] * h[d].x;
+            acc.y += k[d] * h[d].y;
+        }
+        if (y0 + j < Ho) {
+            if (VEC) {
+                *reinterpret_cast<float2*>(dst) = acc;
+            } else {
+                dst[0] = acc.x;
+                if (x + 1 < Wo) dst[1] = acc.y;
+            }
+        }
+        dst += Wo;
+        h[0] = h[2];
+        h[1] = h[3];
+        h[2] = h[4];
+    }
+}
+
+static int64_t pyr_threads(int64_t planes, int ho, int wo) {
+    return planes * ((ho + PYR_ROWS - 1) / PYR_ROWS) * ((wo + 1) / 2);
+}
+
+static hipError_t launch_pyr_reduce(const float* src, float* dst, int64_t planes, int h, int w, int ho, int wo,
+                                    hipStream_t st) {
+    const int64_t threads = pyr_threads(planes, ho, wo);
+    const dim3 grid(static_cast<uint32_t>((threads + 255) / 256)), block(256);
+    // 16-byte loads and 8-byte stores need rows that start on those
+    // boundaries; other widths (one level in two of a ragged frame) take
+    // 4-byte accesses
+    const bool vec = w % 4 == 0 && (reinterpret_cast<uintptr_t>(src) & 15u) == 0u &&
+                     (reinterpret_cast<uintptr_t>(dst) & 7u) == 0u;
+    if (threads > 0x7fffff00LL) {
+        if (vec) hipLaunchKernelGGL((k_pyr_reduce<true, uint64_t>), grid, block, 0, st, src, dst, threads, h, w, ho, wo);
+        else hipLaunchKernelGGL((k_pyr_reduce<false, uint64_t>), grid, block, 0, st, src, dst, threads, h, w, ho, wo);
+    } else {
+        const uint32_t t = static_cast<uint32_t>(threads);
+        if (vec) hipLaunchKernelGGL((k_pyr_reduce<true, uint32_t>), grid, block, 0, st, src, dst, t, h, w, ho, wo);
+        else hipLaunchKernelGGL((k_pyr_reduce<false, uint32_t>), grid, block, 0, st, src, dst, t, h, w, ho, wo);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace gv
@@ -72,9 +162,7 @@ extern "C" gv_status gv_gaussian_pyramid(const float* images, int64_t planes, in
     for (int l = 1; l < levels; ++l) {
         const int ho = (h + 1) / 2, wo = (w + 1) / 2;
         const int64_t n = planes * static_cast<int64_t>(ho) * wo;
-        hipLaunchKernelGGL(k_pyr_reduce, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256), 0, st, src, dst,
-                           planes, h, w, ho, wo);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = launch_pyr_reduce(src, dst, planes, h, w, ho, wo, st);
         if (e != hipSuccess) return GV_ERR_HIP;
         src = dst;
         dst += n;
