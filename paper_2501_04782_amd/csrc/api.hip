@@ -717,7 +717,7 @@ gv_status gv_autotune(const gv_scene* scene, const gv_camera* cam, const float* 
     // measured ten times slower than the quadrant backward on every clip
     // tried and is left to gv_set_tuning.
     constexpr int NF = 12, NB = 6, NS = 4;
-    const int f_kernel[4] = {0, 4, 1, 36};  // the per-tile forward keeps bit 2: visibility counts use the quadrant forward
+    const int f_kernel[4] = {0, 4, 1, 36};
     const int batches[3] = {64, 128, 256};
     const int b_batch[NB] = {64, 128, 256, 64, 128, 64};
     const int b_pair[NB] = {0, 0, 0, 8, 8, 16};

@@ -344,10 +344,17 @@ __global__ __launch_bounds__(WG) void k_composite_fwd(Args a) {
 // exponent's terms in dx), so images, final transmittances and last indices
 // are identical; a lane reads each entry's staged data once for its four
 // pixels.
+//
+// VIS: also flag every (frame, Gaussian) that contributes to a pixel, for the
+// visibility counts.  A taking lane marks the staged entry in LDS (its
+// opacity word, which the loop does not read); after each batch the thread
+// that staged an entry writes the flag, so the loop holds no global store.
+// Visibility counts of 50 960x540 frames of 200k Gaussians: 3.77 ms with the
+// quadrant forward, 2.64 ms with this one.
 constexpr int WGF4 = 64;
 constexpr int FWD4_GROUP = 4;
 
-template <int B>
+template <int B, bool VIS>
 __global__ __launch_bounds__(WGF4) __attribute__((amdgpu_waves_per_eu(4))) void k_composite_fwd4(Args a) {
     constexpr int SPT = B / WGF4;  // entries staged per thread
     static_assert(SPT * WGF4 == B, "whole entries per thread");
@@ -404,6 +411,7 @@ __global__ __launch_bounds__(WGF4) __attribute__((amdgpu_waves_per_eu(4))) void 
                 Staged st;
                 float3 conic;
                 stage_entry(a, f, gn[i], ox, oy, st, conic);
+                if (VIS) st.p2.w = 0.0f;
                 sh[t] = st;
                 shm[t] = quadrant_mask(st, conic, xlim, ylim);
             }
@@ -459,6 +467,7 @@ __global__ __launch_bounds__(WGF4) __attribute__((amdgpu_waves_per_eu(4))) void 
                 const float4 p1 = P1[r];
                 const float dx = fx - p0.x;
                 const FootRow fr = footprint_row(dx, p0, p1);
+                bool any = false;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const float dy = fy[k] - p0.y;
@@ -475,13 +484,25 @@ __global__ __launch_bounds__(WGF4) __attribute__((amdgpu_waves_per_eu(4))) void 
                     c2[k] = __builtin_fmaf(P2[r].x, wgt, c2[k]);
                     T[k] = Tn;
                     loff[k] = take ? static_cast<int>(J[r]) : loff[k];
+                    any = any || take;
                 }
+                if (VIS && any) sh[J[r] / STAGED_BYTES].p2.w = 1.0f;
             }
             if (__ballot(!(done[0] && done[1] && done[2] && done[3])) == 0ull) break;
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (loff[k] >= 0) last[k] = b0 - s + static_cast<uint32_t>(loff[k]) / STAGED_BYTES + 1;
+        if (VIS) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < SPT; ++i) {
+                const uint32_t t = static_cast<uint32_t>(lane + WGF4 * i);
+                if (t >= nb || sh[t].p2.w == 0.0f) continue;
+                const uint32_t gid = __float_as_uint(sh[t].p2.z);
+                if (gid < static_cast<uint64_t>(a.n)) a.vis[static_cast<int64_t>(f) * a.n + gid] = 1;
+            }
+        }
         __syncthreads();  // the next batch overwrites the staged entries and lists
     }
 
@@ -1787,9 +1808,10 @@ __global__ __launch_bounds__(WG) void k_composite_fwd_sb(Args a) {
 }
 
 // Kernel choice: tune.compact bit 0 selects the compacted forward, else bit 2
-// the quadrant forward, else the sub-block forward runs; bit 1 selects the
-// compacted adjoint, else the quadrant adjoint runs.  The visibility flags use
-// the sub-block or quadrant forward.
+// the quadrant forward, else the sub-block forward runs, with bit 5 the
+// one-wave forward before either; bit 1 selects the compacted adjoint, else
+// the quadrant adjoint runs.  The compacted forward has no visibility flags:
+// they take the kernel that would run without bit 0.
 hipError_t launch_composite_fwd(const Args& a, hipStream_t stream) {
     const dim3 grid(static_cast<uint32_t>(a.tiles), static_cast<uint32_t>(a.frames)), block(WG);
     const int c = a.tune.compact;
@@ -1801,11 +1823,15 @@ hipError_t launch_composite_fwd(const Args& a, hipStream_t stream) {
         }
         return hipGetLastError();
     }
-    if ((c & 32) && !a.vis) {  // one wave per tile (batches of at most 128)
-        if (a.tune.batch == 64)
-            hipLaunchKernelGGL(k_composite_fwd4<64>, grid, dim3(WGF4), 0, stream, a);
-        else
-            hipLaunchKernelGGL(k_composite_fwd4<128>, grid, dim3(WGF4), 0, stream, a);
+    if (c & 32) {  // one wave per tile (batches of at most 128)
+        const dim3 wave(WGF4);
+        if (a.vis) {
+            if (a.tune.batch == 64) hipLaunchKernelGGL((k_composite_fwd4<64, true>), grid, wave, 0, stream, a);
+            else hipLaunchKernelGGL((k_composite_fwd4<128, true>), grid, wave, 0, stream, a);
+        } else {
+            if (a.tune.batch == 64) hipLaunchKernelGGL((k_composite_fwd4<64, false>), grid, wave, 0, stream, a);
+            else hipLaunchKernelGGL((k_composite_fwd4<128, false>), grid, wave, 0, stream, a);
+        }
         return hipGetLastError();
     }
 #define GV_FWD_SWITCH(KERNEL, VIS)                                                                       \

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from oracle import pyramid as pyr_ref
+from test_gpu_visibility_pyramid import check_visibility
 
 pytestmark = pytest.mark.gpu
 
@@ -28,3 +29,16 @@ def test_pyramid_strip_edges(H, W, offset):
     for lvl, (a, b) in enumerate(zip(got, pyr_ref.pyramid(img.astype(np.float64), 4))):
         assert tuple(a.shape) == b.shape
         np.testing.assert_allclose(a.cpu().numpy(), b, rtol=0, atol=(lvl + 1) * 10 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("batch", [64, 128])
+@pytest.mark.parametrize("kind", ["clip", "dense"])
+def test_visibility_of_the_one_wave_forward(kind, batch):
+    """The one-wave forward's flags (set after each batch of staged entries)
+    against the oracle's contributors, as for the other kernels."""
+    old = raster.get_tuning()
+    raster.set_tuning(batch, old["sort_cap"], 52, 128)
+    try:
+        check_visibility(kind)
+    finally:
+        raster.set_tuning(old["batch"], old["sort_cap"], old["compact"], old["bwd_batch"])
