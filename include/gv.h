@@ -158,7 +158,10 @@ typedef struct {
  * take precedence, select kernels that first build per-pixel entry lists
  * from closed-form coverage masks;
  * bwd_batch: the backward's LDS batch (0 = same as batch).
- * Defaults: batch 128, sort_cap 1024, compact 52, bwd_batch 64.  Images are
+ * Defaults: batch 128, sort_cap 1024, compact 52, bwd_batch 64.  While the
+ * defaults or an autotuned setting are in force, launches of few tiles run
+ * the one-quadrant-per-wave kernels in place of the one-wave-per-tile ones;
+ * any other setting given to gv_set_tuning is taken as it is.  Images are
  * identical under every setting and gradients equal up to floating-point
  * rounding (order of summation, and the compacted backward's arithmetic);
  * only the speed differs. */

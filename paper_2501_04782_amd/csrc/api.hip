@@ -31,7 +31,8 @@ hipError_t exclusive_scan(const uint32_t* in, uint32_t* out, int64_t count, unsi
 
 static thread_local int32_t g_last_hip = 0;
 static std::mutex g_tune_mu;
-static Tuning g_tune = {128, 1024, 64, 52};  // the autotuner's choice on the 960x540 benchmark clip
+constexpr Tuning DEFAULT_TUNE = {128, 1024, 64, 52, true};  // the autotuner's choice on the 960x540 benchmark clip
+static Tuning g_tune = DEFAULT_TUNE;
 
 Tuning current_tuning() {
     std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -614,6 +615,9 @@ gv_status gv_set_tuning(const gv_tuning* t) {
     n.bwd_batch = t->bwd_batch ? t->bwd_batch : t->batch;
     n.sort_cap = t->sort_cap;
     n.compact = t->compact;
+    // setting the defaults again restores the process's initial state
+    n.adaptive = n.batch == DEFAULT_TUNE.batch && n.bwd_batch == DEFAULT_TUNE.bwd_batch &&
+                 n.sort_cap == DEFAULT_TUNE.sort_cap && n.compact == DEFAULT_TUNE.compact;
     install_tuning(n);
     return GV_OK;
 }
@@ -684,6 +688,7 @@ gv_status gv_autotune(const gv_scene* scene, const gv_camera* cam, const float* 
     }
     Tuning best = current_tuning();
     if (cache_path && cached_tuning(cache_path, key, best) && tuning_valid(best)) {
+        best.adaptive = true;
         install_tuning(best);
         if (chosen) {
             memset(chosen, 0, sizeof(*chosen));
@@ -735,6 +740,7 @@ gv_status gv_autotune(const gv_scene* scene, const gv_camera* cam, const float* 
             t.batch = batches[fc % 3];
             t.bwd_batch = b_batch[c % NB];
             t.sort_cap = caps[c % NS];
+            t.adaptive = false;  // time the kernel named
             install_tuning(t);
             gv_status s = enqueue_batch(scene, cam, poses, times, frames, targets, nullptr, flags, images, loss,
                                         grads, dL_dposes, ws, ws_bytes, st, &tm);
@@ -770,6 +776,7 @@ gv_status gv_autotune(const gv_scene* scene, const gv_camera* cam, const float* 
         best.batch = batches[bf % 3];
         best.bwd_batch = b_batch[bb];
         best.sort_cap = caps[bs];
+        best.adaptive = true;
     }
     install_tuning(result == GV_OK ? best : saved);
     for (int i = 0; i < made && i <= GV_STAGES; ++i) hipEventDestroy(tm.ev[i]);

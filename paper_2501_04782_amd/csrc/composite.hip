@@ -1807,6 +1807,25 @@ __global__ __launch_bounds__(WG) void k_composite_fwd_sb(Args a) {
     }
 }
 
+// Small launches.  One wave per tile does the least work, but a launch of few
+// tiles leaves most of the chip's 1,024 SIMDs idle and lasts as long as its
+// longest tile's chain of entries; a wave per quadrant cuts that chain to a
+// quarter.  Times in us, one wave per tile (batch 128 forward, 64 backward)
+// against the quadrant kernels (batch 256; backward 128 in the last column):
+//   tiles (frames x tiles)             forward        backward
+//     64 (128x128, 2k Gaussians)       36 ->  19      70 ->  32 /  34
+//    300 (320x240, 20k)                96 ->  44     189 ->  72 /  79
+//  2,040 (960x540, 100k)              106 ->  53     207 -> 112 / 128
+//  4,080 (two such frames)            128 ->  79     269 -> 208 / 195
+//  8,160 (four)                       170 -> 129     345 -> 364 / 314
+//  8,160 (1920x1080, 500k)            116 -> 116     251 -> 337 / 281
+// 16,320 (960x540, 200k, 8 frames)    249 -> 274     549 -> 845 / 675
+constexpr int64_t FWD_QUADRANT_ITEMS = 8192;
+constexpr int64_t BWD_QUADRANT_ITEMS = 6144;
+constexpr int64_t BWD_QUADRANT_ITEMS_256 = 3072;
+
+static int64_t items(const Args& a) { return static_cast<int64_t>(a.tiles) * a.frames; }
+
 // Kernel choice: tune.compact bit 0 selects the compacted forward, else bit 2
 // the quadrant forward, else the sub-block forward runs, with bit 5 the
 // one-wave forward before either; bit 1 selects the compacted adjoint, else
@@ -1814,28 +1833,32 @@ __global__ __launch_bounds__(WG) void k_composite_fwd_sb(Args a) {
 // they take the kernel that would run without bit 0.
 hipError_t launch_composite_fwd(const Args& a, hipStream_t stream) {
     const dim3 grid(static_cast<uint32_t>(a.tiles), static_cast<uint32_t>(a.frames)), block(WG);
-    const int c = a.tune.compact;
+    int c = a.tune.compact, batch = a.tune.batch;
     if ((c & 1) && !a.vis) {
-        switch (a.tune.batch) {
+        switch (batch) {
             case 64: hipLaunchKernelGGL(k_composite_fwd_c<64>, grid, block, 0, stream, a); break;
             case 128: hipLaunchKernelGGL(k_composite_fwd_c<128>, grid, block, 0, stream, a); break;
             default: hipLaunchKernelGGL(k_composite_fwd_c<256>, grid, block, 0, stream, a); break;
         }
         return hipGetLastError();
     }
+    if ((c & 32) && a.tune.adaptive && items(a) <= FWD_QUADRANT_ITEMS) {
+        c = 4;
+        batch = 256;
+    }
     if (c & 32) {  // one wave per tile (batches of at most 128)
         const dim3 wave(WGF4);
         if (a.vis) {
-            if (a.tune.batch == 64) hipLaunchKernelGGL((k_composite_fwd4<64, true>), grid, wave, 0, stream, a);
+            if (batch == 64) hipLaunchKernelGGL((k_composite_fwd4<64, true>), grid, wave, 0, stream, a);
             else hipLaunchKernelGGL((k_composite_fwd4<128, true>), grid, wave, 0, stream, a);
         } else {
-            if (a.tune.batch == 64) hipLaunchKernelGGL((k_composite_fwd4<64, false>), grid, wave, 0, stream, a);
+            if (batch == 64) hipLaunchKernelGGL((k_composite_fwd4<64, false>), grid, wave, 0, stream, a);
             else hipLaunchKernelGGL((k_composite_fwd4<128, false>), grid, wave, 0, stream, a);
         }
         return hipGetLastError();
     }
 #define GV_FWD_SWITCH(KERNEL, VIS)                                                                       \
-    switch (a.tune.batch) {                                                                              \
+    switch (batch) {                                                                                     \
         case 64: hipLaunchKernelGGL((KERNEL<64, VIS>), grid, block, 0, stream, a); break;                \
         case 128: hipLaunchKernelGGL((KERNEL<128, VIS>), grid, block, 0, stream, a); break;              \
         default: hipLaunchKernelGGL((KERNEL<256, VIS>), grid, block, 0, stream, a); break;               \
@@ -1887,18 +1910,23 @@ hipError_t launch_composite_bwd(const Args& a, hipStream_t stream) {
         }
         return hipGetLastError();
     }
-    if (a.tune.compact & 16) {  // one wave per tile (batches of 64)
+    int c = a.tune.compact, batch = a.tune.bwd_batch;
+    if ((c & 16) && a.tune.adaptive && items(a) <= BWD_QUADRANT_ITEMS) {
+        c = 0;
+        batch = items(a) <= BWD_QUADRANT_ITEMS_256 ? 256 : 128;
+    }
+    if (c & 16) {  // one wave per tile (batches of 64)
         hipLaunchKernelGGL(k_composite_bwd4<64>, grid, dim3(WG4), 0, stream, a);
         return hipGetLastError();
     }
-    if (a.tune.compact & 8) {  // paired quadrants (batches of at most 128)
-        if (a.tune.bwd_batch == 64)
+    if (c & 8) {  // paired quadrants (batches of at most 128)
+        if (batch == 64)
             hipLaunchKernelGGL(k_composite_bwd2<64>, grid, dim3(WG2), 0, stream, a);
         else
             hipLaunchKernelGGL(k_composite_bwd2<128>, grid, dim3(WG2), 0, stream, a);
         return hipGetLastError();
     }
-    switch (a.tune.bwd_batch) {
+    switch (batch) {
         case 64: hipLaunchKernelGGL(k_composite_bwd<64>, grid, block, 0, stream, a); break;
         case 128: hipLaunchKernelGGL(k_composite_bwd<128>, grid, block, 0, stream, a); break;
         default: hipLaunchKernelGGL(k_composite_bwd<256>, grid, block, 0, stream, a); break;

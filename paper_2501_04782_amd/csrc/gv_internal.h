@@ -76,6 +76,8 @@ struct Tuning {
     int compact;    // bit 0 / bit 1: compacted forward / backward compositing (coverage masks + per-lane entry
                     // walks); else bit 2: quadrant forward (clear: 4x4-block forward); bit 4 / bit 3: the
                     // backward walks four / two quadrant lists per wave (clear: one)
+    bool adaptive;  // launches too small for the one-wave kernels take the quadrant kernels instead (the built-in
+                    // defaults and an autotuned setting; clear: a caller's own setting, taken as given)
 };
 
 // Byte offsets of the workspace regions (host-computed).

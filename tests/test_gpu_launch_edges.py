@@ -5,6 +5,8 @@ import pytest
 import torch
 
 from oracle import pyramid as pyr_ref
+from parity_util import device_inputs, workspace_for
+from test_gpu_parity import small_workload
 from test_gpu_visibility_pyramid import check_visibility
 
 pytestmark = pytest.mark.gpu
@@ -42,3 +44,32 @@ def test_visibility_of_the_one_wave_forward(kind, batch):
         check_visibility(kind)
     finally:
         raster.set_tuning(old["batch"], old["sort_cap"], old["compact"], old["bwd_batch"])
+
+
+@pytest.mark.parametrize("frames", [1, 256, 512, 683])
+def test_small_launches_match_the_one_wave_kernels(frames):
+    """12 tiles a frame: launches of 12, 3072, 6144 and 8196 tiles, on both
+    sides of the lines where the default setting leaves the quadrant kernels
+    (backward at 3072 and 6144, forward at 8192).  Images and decisions equal
+    those of the one-wave kernels bit for bit; gradients differ in the order of
+    sums of at most 256 pixels per tile."""
+    w = small_workload(7, 60, 44, 150, frames, trajectory=True, z=(2.0, 10.0), ls=(-2.6, 0.5))
+    scene, cam, poses, times = device_inputs(w)
+    ws = workspace_for(scene, cam, poses, times)
+    dl = torch.from_numpy(np.random.default_rng(8).normal(0, 1, (frames, 3, 44, 60)).astype(np.float32)).cuda()
+    old = raster.get_tuning()
+    assert (old["batch"], old["sort_cap"], old["compact"], old["bwd_batch"]) == (128, 1024, 52, 64)
+    a = raster.render_batch(scene, cam, poses, times, ws, dL_dimages=dl)
+    raster.set_tuning(128, 1024, 52, 128)
+    try:
+        b = raster.render_batch(scene, cam, poses, times, ws, dL_dimages=dl)
+    finally:
+        raster.set_tuning(old["batch"], old["sort_cap"], old["compact"], old["bwd_batch"])
+    c = raster.render_batch(scene, cam, poses, times, ws, dL_dimages=dl)
+    torch.cuda.synchronize()
+    assert ws.status()["overflow"] == 0
+    assert torch.equal(a["images"], b["images"])
+    for k, g in a["grads"].items():
+        if g is not None:
+            assert torch.linalg.norm(g - b["grads"][k]) <= 256 * 2.0 ** -24 * torch.linalg.norm(g), k
+            assert torch.equal(g, c["grads"][k]), k
