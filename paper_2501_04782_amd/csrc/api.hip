@@ -27,7 +27,7 @@ int64_t project_bwd_blocks(int64_t n);
 int64_t bin_blocks(int64_t n);
 int64_t scan_blocks(int64_t count);
 hipError_t exclusive_scan(const uint32_t* in, uint32_t* out, int64_t count, unsigned long long* tmp,
-                          uint32_t* status, int check, int64_t k_cap, hipStream_t stream);
+                          uint32_t* status, int64_t k_cap, hipStream_t stream);
 
 static thread_local int32_t g_last_hip = 0;
 static std::mutex g_tune_mu;
@@ -62,7 +62,7 @@ Layout make_layout(const gv_camera& cam, int64_t n, int frames, int64_t k_cap) {
     L.k_cap = k_cap;
     const int64_t FN = static_cast<int64_t>(frames) * n;
     const int64_t FT = static_cast<int64_t>(frames) * L.tiles;
-    L.scan_blocks = std::max(scan_blocks(FN), scan_blocks(FT));
+    L.scan_blocks = scan_blocks(FT);
     L.pose_blocks = project_bwd_blocks(n);
     L.bin_blocks = L.tiles <= LDS_TILE_LIMIT ? bin_blocks(n) : 0;
     size_t off = 0;
@@ -78,7 +78,7 @@ Layout make_layout(const gv_camera& cam, int64_t n, int frames, int64_t k_cap) {
     L.tmask = take(8 * static_cast<size_t>(FN));
     L.rect = take(sizeof(uint2) * static_cast<size_t>(FN));
     L.gcnt = take(4 * static_cast<size_t>(FN));
-    L.goff = take(4 * static_cast<size_t>(FN + 1));
+    L.goff = take(4 * static_cast<size_t>(FN));
     L.tcnt = take(4 * static_cast<size_t>(FT));
     L.toff = take(4 * static_cast<size_t>(FT + 1));
     L.tcur = take(4 * static_cast<size_t>(FT));
@@ -276,7 +276,6 @@ static inline void mark(StageTimer* tm, int i) {
 // Projection, binning and scans; optionally reads the intersection count back.
 static gv_status enqueue_binning(const Args& a, const Layout& L, hipStream_t st, bool readback,
                                  StageTimer* tm = nullptr) {
-    const int64_t FN = static_cast<int64_t>(a.frames) * a.n;
     const int64_t FT = static_cast<int64_t>(a.frames) * a.tiles;
     mark(tm, 0);
     GV_TRY(launch_fill_u32(a.status, 0u, ST_WORDS, st));
@@ -284,8 +283,7 @@ static gv_status enqueue_binning(const Args& a, const Layout& L, hipStream_t st,
     GV_TRY(launch_fill_u32(a.tcur, 0u, FT, st));
     GV_TRY(launch_project(a, st));
     mark(tm, 1);
-    GV_TRY(exclusive_scan(a.gcnt, a.goff, FN, scan_tmp(a, L), a.status, 0, a.k_cap, st));
-    GV_TRY(exclusive_scan(a.tcnt, a.toff, FT, scan_tmp(a, L), a.status, 1, a.k_cap, st));
+    GV_TRY(exclusive_scan(a.tcnt, a.toff, FT, scan_tmp(a, L), a.status, a.k_cap, st));
     mark(tm, 2);
     if (readback) {
         uint32_t k2[2] = {0, 0};

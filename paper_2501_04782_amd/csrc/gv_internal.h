@@ -67,7 +67,8 @@ struct __align__(16) ColorOp {
 };
 
 // Status word at the start of every workspace.
-enum : int { ST_OVERFLOW = 0, ST_NONFINITE = 1, ST_K_LO = 2, ST_K_HI = 3, ST_WORDS = 16 };
+// (ST_SLOTS: pre-sort slots handed out by the count pass).
+enum : int { ST_OVERFLOW = 0, ST_NONFINITE = 1, ST_K_LO = 2, ST_K_HI = 3, ST_SLOTS = 4, ST_WORDS = 16 };
 
 struct Tuning {
     int batch;      // 64 / 128 / 256 entries per LDS round of the forward compositing kernel
@@ -86,7 +87,7 @@ struct Layout {
     int frames, width, height, tiles_x, tiles_y, tiles;
     int64_t pixels;        // width * height
     int64_t k_cap;
-    int64_t scan_blocks;   // for the (frames*n) scan
+    int64_t scan_blocks;   // of the tile-count scan
     int64_t pose_blocks;   // workgroups of the projection adjoint (upper bound)
     int64_t bin_blocks;    // workgroups per frame of the LDS-histogram binning (0: global atomics)
     size_t status, col4, rec, dkey, rect, tmask, gcnt, goff, tcnt, toff, tcur, bhist, scan_tmp, tfin, nlast, loss_part, pose_part,
@@ -144,7 +145,7 @@ struct Args {
     uint64_t* tmask;      // [F][N]: tiles that passed the ellipse test, row-major bits over the rectangle
                           // (rectangles of at most 64 tiles; larger ones are tested again by the scatter)
     uint32_t* gcnt;       // [F*N]
-    uint32_t* goff;       // [F*N + 1]
+    uint32_t* goff;       // [F*N] first pre-sort slot of each (frame, Gaussian)
     uint32_t* tcnt;       // [F*T]
     uint32_t* toff;       // [F*T + 1]
     uint32_t* tcur;       // [F*T]

@@ -213,13 +213,23 @@ struct WaveCells {
 // projects BIN_GROUP Gaussians of one frame, counts their intersections per
 // tile with LDS atomics (16-bit counts, two tiles per word: a count never
 // exceeds BIN_GROUP), stores its histogram and adds it to the frame's tile
-// counts with one global atomic per non-empty tile.  A Gaussian's passing
-// tiles are also recorded as a row-major mask over its rectangle (rectangles
-// of at most 64 tiles), which the scatter walks.
+// counts with one global atomic per non-empty tile.  The workgroup's pre-sort
+// slots are one contiguous range taken with a single atomic and dealt out in
+// order of the Gaussians; where the range lies does not matter to any result,
+// and no prefix sum over the (frame, Gaussian) counts is needed (960x540 clip
+// of 50 frames and 200k Gaussians: prefix sums 73 -> 14 us, this pass 405 -> 425).
+// A Gaussian's passing tiles
+// are also recorded as a row-major mask over its rectangle (rectangles of at
+// most 64 tiles), which the scatter walks.
 template <bool EXT>
 __global__ __launch_bounds__(256) void k_project_lds(Args a) {
     extern __shared__ uint32_t hist[];
     __shared__ WaveCells wc[4];
+    constexpr int ROUNDS = BIN_GROUP / 256;
+    __shared__ uint16_t counts[ROUNDS][256];  // a Gaussian meets at most LDS_TILE_LIMIT tiles
+    __shared__ uint32_t wtotal[ROUNDS][4];
+    __shared__ uint32_t slot0;
+    static_assert(LDS_TILE_LIMIT <= 0xffff, "16-bit counts");
     const int f = blockIdx.y;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int words = (a.tiles + 1) >> 1;
@@ -230,7 +240,7 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
     const int64_t g0 = static_cast<int64_t>(blockIdx.x) * BIN_GROUP;
     WaveCells& W = wc[w];
 #pragma unroll 1
-    for (int k = 0; k < BIN_GROUP / 256; ++k) {
+    for (int k = 0; k < ROUNDS; ++k) {
         const int64_t g = g0 + k * 256 + threadIdx.x;
         BinShape S;
         const bool has = g < a.n && project_one<EXT>(a, f, g, cam, tt, S);
@@ -264,9 +274,27 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
             a.gcnt[i] = W.cnt[lane];
             if (has) a.tmask[i] = W.mask[lane];
         }
+        counts[k][threadIdx.x] = static_cast<uint16_t>(W.cnt[lane]);
         __builtin_amdgcn_wave_barrier();
     }
+    // the workgroup's slots, in order of the Gaussians
+    uint32_t before[ROUNDS];
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) {
+        uint32_t total;
+        before[k] = wave_exclusive_scan(counts[k][threadIdx.x], lane, total);
+        if (lane == 0) wtotal[k][w] = total;
+    }
     __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t run = 0;
+        for (int k = 0; k < ROUNDS * 4; ++k) {
+            const uint32_t v = wtotal[k >> 2][k & 3];
+            wtotal[k >> 2][k & 3] = run;
+            run += v;
+        }
+        slot0 = run ? atomicAdd(&a.status[ST_SLOTS], run) : 0u;
+    }
     uint32_t* bh = a.bhist + (static_cast<int64_t>(f) * a.bin_blocks + blockIdx.x) * a.tiles;
     uint32_t* tc = a.tcnt + static_cast<int64_t>(f) * a.tiles;
     for (int t = threadIdx.x; t < a.tiles; t += 256) {
@@ -274,12 +302,18 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
         bh[t] = v;
         if (v) atomicAdd(&tc[t], v);
     }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) {
+        const int64_t g = g0 + k * 256 + threadIdx.x;
+        if (g < a.n) a.goff[static_cast<int64_t>(f) * a.n + g] = slot0 + wtotal[k][w] + before[k];
+    }
 }
 
 // Write intersection (f, g) -> tile (tx, ty) with pre-sort slot goff + k at
 // position next(tile) of the tile's bucket, below end(tile) (the bucket's end
-// in the global-atomic scatter; the workspace's capacity in the LDS scatter,
-// whose reservations check the counts).  The counts bound every write; a
+// in the global-atomic scatter; the workspace's capacity in the LDS scatter).
+// The counts bound every write; a
 // mismatch is an internal error, reported instead of written out of bounds.
 template <typename Next, typename End>
 __device__ __forceinline__ void emit_key(const Args& a, uint64_t key, uint32_t slot, int tx, int ty, Next next,
@@ -418,8 +452,8 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
         const bool small =
             cnt && ((rc.x >> 16) - (rc.x & 0xffff) + 1) * ((rc.y >> 16) - (rc.y & 0xffff) + 1) <= 64u;
         uint32_t total;
-        const uint32_t start = wave_exclusive_scan(small ? cnt : 0u, lane, total);
-        W.start[lane] = start;
+        const uint32_t first = wave_exclusive_scan(small ? cnt : 0u, lane, total);
+        W.start[lane] = first;
         if (small) {
             W.mask[lane] = tm;
             W.key[lane] = sort_key(cur.depth, g);
@@ -431,7 +465,7 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
         __builtin_amdgcn_wave_barrier();
         for (uint32_t b0 = 0; b0 < total; b0 += 64) {
             const uint32_t item = b0 + static_cast<uint32_t>(lane);
-            const int o = chunk_owner(W.own, start, small ? cnt : 0u, b0, lane);
+            const int o = chunk_owner(W.own, first, small ? cnt : 0u, b0, lane);
             if (item < total) {
                 const uint32_t kk = item - W.start[o];
                 const uint64_t m = W.mask[o];
@@ -464,14 +498,15 @@ template <bool EXT>
 __global__ __launch_bounds__(256) void k_project(Args a) {
     const int f = blockIdx.y;
     const int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g >= a.n) return;
+    const int lane = threadIdx.x & 63;
+    const bool live = g < a.n;
     const CamD cam = load_camera(a.poses + 7 * f);
     const double t = a.times ? static_cast<double>(a.times[f]) : static_cast<double>(a.t0);
     uint32_t* tc = a.tcnt + static_cast<int64_t>(f) * a.tiles;
     const int64_t i = static_cast<int64_t>(f) * a.n + g;
     BinShape S;
     uint32_t cnt = 0;
-    if (project_one<EXT>(a, f, g, cam, t, S)) {
+    if (live && project_one<EXT>(a, f, g, cam, t, S)) {
         uint64_t mask = 0;
         const bool small = S.rw * S.rh <= 64;
         for (int ry = 0; ry < S.rh; ++ry)
@@ -483,7 +518,15 @@ __global__ __launch_bounds__(256) void k_project(Args a) {
                 }
         a.tmask[i] = mask;
     }
-    a.gcnt[i] = cnt;
+    // the wave's slots: one contiguous range
+    uint32_t total, slot0 = 0;
+    const uint32_t before = wave_exclusive_scan(cnt, lane, total);
+    if (lane == 0 && total) slot0 = atomicAdd(&a.status[ST_SLOTS], total);
+    slot0 = static_cast<uint32_t>(__shfl(static_cast<int>(slot0), 0, 64));
+    if (live) {
+        a.gcnt[i] = cnt;
+        a.goff[i] = slot0 + before;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_scatter(Args a) {

@@ -1,4 +1,4 @@
-// Device-wide exclusive prefix sums of u32 counts (three passes: per-block
+// Exclusive prefix sum of the u32 tile counts (three passes: per-block
 // scan with 64-bit block totals, scan of the block totals in one workgroup,
 // add-back).  The grand total is kept in 64 bits so that an intersection count
 // beyond 2^32 is detected as an overflow instead of wrapping.
@@ -57,12 +57,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_local(const uint32_t* __r
 }
 
 // One workgroup: exclusive scan of the block totals in place; writes the
-// grand total to out[count] (u32) and, if status_total_slot >= 0, to the
-// status word, raising the overflow flag when it exceeds k_cap.
+// grand total to out[count] (u32) and to the status word, raising the
+// overflow flag when it exceeds k_cap.
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_block_sums(unsigned long long* __restrict__ block_sums, int64_t n_blocks,
                                                                   uint32_t* __restrict__ out, int64_t count,
-                                                                  uint32_t* __restrict__ status, int check,
-                                                                  int64_t k_cap) {
+                                                                  uint32_t* __restrict__ status, int64_t k_cap) {
     const int64_t per = (n_blocks + SCAN_THREADS - 1) / SCAN_THREADS;
     const int64_t b0 = threadIdx.x * per;
     unsigned long long s = 0;
@@ -76,11 +75,9 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_block_sums(unsigned long 
     }
     if (threadIdx.x == 0) {
         out[count] = static_cast<uint32_t>(total);
-        if (check) {
-            status[ST_K_LO] = static_cast<uint32_t>(total);
-            status[ST_K_HI] = static_cast<uint32_t>(total >> 32);
-            if (total > static_cast<uint64_t>(k_cap)) status[ST_OVERFLOW] = 1u;
-        }
+        status[ST_K_LO] = static_cast<uint32_t>(total);
+        status[ST_K_HI] = static_cast<uint32_t>(total >> 32);
+        if (total > static_cast<uint64_t>(k_cap)) status[ST_OVERFLOW] = 1u;
     }
 }
 
@@ -99,13 +96,13 @@ int64_t scan_blocks(int64_t count) { return (count + SCAN_TILE - 1) / SCAN_TILE;
 // Exclusive scan in[count] -> out[count + 1] on `stream`; tmp holds
 // scan_blocks(count) 64-bit values.
 hipError_t exclusive_scan(const uint32_t* in, uint32_t* out, int64_t count, unsigned long long* tmp, uint32_t* status,
-                          int check, int64_t k_cap, hipStream_t stream) {
+                          int64_t k_cap, hipStream_t stream) {
     const int64_t nb = scan_blocks(count);
     if (nb > 0) {
         hipLaunchKernelGGL(k_scan_local, dim3(static_cast<uint32_t>(nb)), dim3(SCAN_THREADS), 0, stream, in, out, count,
                            tmp);
     }
-    hipLaunchKernelGGL(k_scan_block_sums, dim3(1), dim3(SCAN_THREADS), 0, stream, tmp, nb, out, count, status, check,
+    hipLaunchKernelGGL(k_scan_block_sums, dim3(1), dim3(SCAN_THREADS), 0, stream, tmp, nb, out, count, status,
                        k_cap);
     if (nb > 0) {
         hipLaunchKernelGGL(k_scan_add, dim3(static_cast<uint32_t>(nb)), dim3(SCAN_THREADS), 0, stream, out, count, tmp);
