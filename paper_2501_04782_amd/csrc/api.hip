@@ -26,8 +26,7 @@ hipError_t launch_project_bwd(const Args& a, hipStream_t stream);
 int64_t project_bwd_blocks(int64_t n);
 int64_t bin_blocks(int64_t n);
 int64_t scan_blocks(int64_t count);
-hipError_t exclusive_scan(const uint32_t* in, uint32_t* out, int64_t count, unsigned long long* tmp,
-                          uint32_t* status, int64_t k_cap, hipStream_t stream);
+hipError_t launch_tile_scan(const Args& a, unsigned long long* tmp, hipStream_t stream);
 
 static thread_local int32_t g_last_hip = 0;
 static std::mutex g_tune_mu;
@@ -62,7 +61,6 @@ Layout make_layout(const gv_camera& cam, int64_t n, int frames, int64_t k_cap) {
     L.k_cap = k_cap;
     const int64_t FN = static_cast<int64_t>(frames) * n;
     const int64_t FT = static_cast<int64_t>(frames) * L.tiles;
-    L.scan_blocks = scan_blocks(FT);
     L.pose_blocks = project_bwd_blocks(n);
     L.bin_blocks = L.tiles <= LDS_TILE_LIMIT ? bin_blocks(n) : 0;
     size_t off = 0;
@@ -83,7 +81,7 @@ Layout make_layout(const gv_camera& cam, int64_t n, int frames, int64_t k_cap) {
     L.toff = take(4 * static_cast<size_t>(FT + 1));
     L.tcur = take(4 * static_cast<size_t>(FT));
     L.bhist = take(4 * static_cast<size_t>(FT) * static_cast<size_t>(L.bin_blocks));
-    L.scan_tmp = take(8 * static_cast<size_t>(L.scan_blocks + 1));
+    L.scan_tmp = take(8 * static_cast<size_t>(scan_blocks(FT) + 1));
     L.tfin = take(4 * static_cast<size_t>(frames) * L.pixels);
     L.nlast = take(4 * static_cast<size_t>(frames) * L.pixels);
     L.loss_part = take(4 * static_cast<size_t>(FT));
@@ -278,12 +276,9 @@ static gv_status enqueue_binning(const Args& a, const Layout& L, hipStream_t st,
                                  StageTimer* tm = nullptr) {
     const int64_t FT = static_cast<int64_t>(a.frames) * a.tiles;
     mark(tm, 0);
-    GV_TRY(launch_fill_u32(a.status, 0u, ST_WORDS, st));
-    GV_TRY(launch_fill_u32(a.tcnt, 0u, FT, st));
-    GV_TRY(launch_fill_u32(a.tcur, 0u, FT, st));
     GV_TRY(launch_project(a, st));
     mark(tm, 1);
-    GV_TRY(exclusive_scan(a.tcnt, a.toff, FT, scan_tmp(a, L), a.status, a.k_cap, st));
+    GV_TRY(launch_tile_scan(a, scan_tmp(a, L), st));
     mark(tm, 2);
     if (readback) {
         uint32_t k2[2] = {0, 0};
@@ -336,7 +331,6 @@ static gv_status enqueue_batch(const gv_scene* scene, const gv_camera* cam, cons
         for (int i = 0; i <= 6; ++i) mark(tm, i);
     }
     if (flags & GV_BWD) {
-        GV_TRY(launch_fill_u32(a.pused, 0u, a.k_cap / 32 + 2, st));
         GV_TRY(launch_composite_bwd(a, st));
         mark(tm, 7);
         GV_TRY(launch_project_bwd(a, st));
@@ -382,8 +376,6 @@ gv_status gv_project_fwd(const gv_scene* scene, const gv_camera* cam, const floa
     if (s != GV_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     a.t0 = t;
-    GV_TRY(launch_fill_u32(a.status, 0u, ST_WORDS, st));
-    GV_TRY(launch_fill_u32(a.tcnt, 0u, a.tiles, st));
     GV_TRY(launch_project(a, st));
     GV_TRY(launch_export_records(a, records, tile_counts, st));
     return GV_OK;
@@ -439,7 +431,6 @@ gv_status gv_render_bwd(const gv_scene* scene, const gv_camera* cam, const float
     set_grads(a, grads);
     a.g_poses = dL_dpose7;
     a.accumulate = (flags & GV_ACCUMULATE) ? 1 : 0;
-    GV_TRY(launch_fill_u32(a.pused, 0u, a.k_cap / 32 + 2, st));
     GV_TRY(launch_composite_bwd(a, st));
     GV_TRY(launch_project_bwd(a, st));
     return GV_OK;

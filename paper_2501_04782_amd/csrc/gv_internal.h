@@ -87,7 +87,6 @@ struct Layout {
     int frames, width, height, tiles_x, tiles_y, tiles;
     int64_t pixels;        // width * height
     int64_t k_cap;
-    int64_t scan_blocks;   // of the tile-count scan
     int64_t pose_blocks;   // workgroups of the projection adjoint (upper bound)
     int64_t bin_blocks;    // workgroups per frame of the LDS-histogram binning (0: global atomics)
     size_t status, col4, rec, dkey, rect, tmask, gcnt, goff, tcnt, toff, tcur, bhist, scan_tmp, tfin, nlast, loss_part, pose_part,
@@ -100,7 +99,7 @@ Layout make_layout(const gv_camera& cam, int64_t n, int frames, int64_t k_cap);
 
 // Everything a kernel needs, passed by value.
 // Frame-independent part of a static Gaussian's projection, computed once
-// per call (k_static_shapes) with the very operations project_gaussian would
+// per call (k_begin) with the very operations project_gaussian would
 // repeat in every frame: 3D covariance and opacity, whether the shape's
 // parameters (log-scales, quaternion, opacity logit, colour) are finite, and
 // whether the quaternion has a nonzero norm.
@@ -161,7 +160,7 @@ struct Args {
     uint32_t* sgid;       // [K]
     uint32_t* sslot;      // [K]
     float* part;          // [K][PART] (du, dv, dA00, dA01, dA11, do, dr, dg, db) per pre-sort slot
-    uint32_t* pused;      // [K/32 + 2] bit per pre-sort slot: its partial record was written this pass
+    uint32_t* pused;      // [K/32 + 2] bit per pre-sort slot: its partial record was written (cleared by the forward)
     ShapeD* shapes;       // [N] static shapes of this call (scenes without dynamics or SH), or nullptr
     KeySlot* tkv;         // [K] merge scratch of the sort
     int64_t k_cap;
@@ -691,7 +690,8 @@ __device__ __forceinline__ int reduce_scatter16_index(int lane) {
 // adjoint writes records only for the entries up to each tile's last
 // contributor; the projection adjoint adds only the marked slots, so the
 // entries behind (about half of them on dense scenes) need no zero records.
-// The bits are cleared before the adjoint; OR is order-independent.
+// The bits are cleared by the forward, and every adjoint of one forward marks
+// the same slots; OR is order-independent.
 __device__ __forceinline__ void store_partials_marked(const Args& a, uint32_t slot, const float (&v)[PART]) {
     store_partials(a.part, slot, v);
     atomicOr(&a.pused[slot >> 5], 1u << (slot & 31u));

@@ -6,15 +6,25 @@
 // FP64 keeps the rounded records (centre, conic, depth key) as close to the
 // exact values as their storage format allows.  Only the per-pixel loop of the
 // compositing kernels runs in FP32.
+#include <algorithm>
+
 #include "gv_internal.h"
 
 namespace gv {
 
-// The frame-independent shape of every Gaussian of a static scene (no
-// dynamics, no SH), once per call instead of once per frame.
-__global__ __launch_bounds__(256) void k_static_shapes(Args a) {
+// First kernel of a forward: the frame-independent shape of every Gaussian of
+// a static scene (no dynamics, no SH; once per call instead of once per frame),
+// and in the same launch the words the later kernels count in or mark: the
+// status, the tiles' counts and next positions, and the adjoint's marks (the
+// entries a tile's adjoint writes are fixed by its forward, so one clear here
+// serves every adjoint of this forward).  A single 128x128 frame spent a tenth
+// of its step in the separate clears.
+__global__ __launch_bounds__(256) void k_begin(Args a, bool shapes, int64_t ft, int64_t marks) {
     const int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g >= a.n) return;
+    if (g < ST_WORDS) a.status[g] = 0u;
+    if (g < ft) a.tcnt[g] = a.tcur[g] = 0u;
+    if (g < marks) a.pused[g] = 0u;
+    if (!shapes || g >= a.n) return;
     const int64_t n = a.n;
     double raw[14];
     for (int k = 0; k < 3; ++k) raw[k] = 0.0;
@@ -76,7 +86,7 @@ __device__ __forceinline__ bool project_one(const Args& a, int f, int64_t g, con
         a.col4[g] = co;
     }
     ProjD P;
-    // the static instantiation takes the shapes launch_project computed first
+    // the static instantiation takes the shapes k_begin computed
     bool vis;
     if constexpr (EXT) vis = project_gaussian<true>(a, g, cam, t, P);
     else vis = project_gaussian_shaped(a, g, cam, t, P);
@@ -584,12 +594,16 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, hipStream
 
 int64_t bin_blocks(int64_t n) { return (n + BIN_GROUP - 1) / BIN_GROUP; }
 
+// Clears the counters (and the adjoint's marks) and projects; the static
+// instantiation reads the shapes the first kernel leaves.
 hipError_t launch_project(const Args& a, hipStream_t stream) {
-    if (a.n <= 0) return hipSuccess;
     const bool ext = a.n_ctrl > 0 || a.scale_coeffs || a.quat_coeffs || a.sh_degree > 0;
     const dim3 block(256);
-    if (!ext)
-        hipLaunchKernelGGL(k_static_shapes, dim3(static_cast<uint32_t>((a.n + 255) / 256)), block, 0, stream, a);
+    const int64_t ft = static_cast<int64_t>(a.frames) * a.tiles, marks = a.k_cap / 32 + 2;
+    const int64_t threads = std::max({static_cast<int64_t>(ST_WORDS), ft, marks, ext ? int64_t(0) : a.n});
+    hipLaunchKernelGGL(k_begin, dim3(static_cast<uint32_t>((threads + 255) / 256)), block, 0, stream, a, !ext, ft,
+                       marks);
+    if (a.n <= 0) return hipGetLastError();
     if (a.bhist) {
         const dim3 grid(static_cast<uint32_t>(a.bin_blocks), a.frames);
         const size_t lds = sizeof(uint32_t) * ((a.tiles + 1) / 2);

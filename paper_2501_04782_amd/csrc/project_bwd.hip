@@ -580,53 +580,56 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
         for (int k = 0; k < 3 * sh_count(a.sh_degree); ++k) put(a.g_sh, static_cast<int64_t>(k) * n + g, acc_sh[k][tid]);
 }
 
-// Per frame: sum the workgroups' pose partials (each of the 256 threads takes
-// a strided subset of workgroups, then a fixed-order tree over threads), then
-// map dL/dRc and dL/dtc to the unnormalised pose quaternion and translation.
-__global__ __launch_bounds__(256) void k_pose_finalize(Args a, int64_t n_blocks) {
-    const int f = blockIdx.x;
-    __shared__ double red[256][13];
-    double v[12];
-    for (int k = 0; k < 12; ++k) v[k] = 0.0;
-    for (int64_t b = threadIdx.x; b < n_blocks; b += 256) {
-        const double* p = a.pose_part + (b * a.frames + f) * 12;
-        for (int k = 0; k < 12; ++k) v[k] += p[k];
+// Sums of V values over the projection adjoint's workgroups, part[b * stride + k]
+// for k < V, in a fixed order: groups of V threads (whose loads are contiguous)
+// take every GROUPS-th workgroup, then the groups are added in order.  The sums
+// are in out[0, V) for every thread afterwards.
+constexpr int FIN_THREADS = 1024;
+
+template <int V>
+__device__ __forceinline__ void sum_parts(const double* part, int64_t stride, int64_t n_blocks, double* red,
+                                          double* out) {
+    constexpr int GROUPS = FIN_THREADS / V;
+    const int q = threadIdx.x / V, k = threadIdx.x % V;
+    if (q < GROUPS) {
+        double v = 0.0;
+#pragma unroll 4
+        for (int64_t b = q; b < n_blocks; b += GROUPS) v += part[b * stride + k];
+        red[q * V + k] = v;
     }
-    for (int k = 0; k < 12; ++k) red[threadIdx.x][k] = v[k];
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s)
-            for (int k = 0; k < 12; ++k) red[threadIdx.x][k] += red[threadIdx.x + s][k];
-        __syncthreads();
+    const int used = n_blocks < GROUPS ? static_cast<int>(n_blocks) : GROUPS;
+    if (threadIdx.x < V) {
+        double v = 0.0;
+        for (int g = 0; g < used; ++g) v += red[g * V + threadIdx.x];
+        out[threadIdx.x] = v;
     }
-    if (threadIdx.x == 0) {
-        double acc[12];
-        for (int k = 0; k < 12; ++k) acc[k] = red[0][k];
+    __syncthreads();
+}
+
+// Workgroup f < pose_frames: the frame's pose gradient, its sums of dL/dRc and
+// dL/dtc mapped to the unnormalised pose quaternion and translation.  The
+// workgroup after them: the intrinsics gradient.
+__global__ __launch_bounds__(FIN_THREADS) void k_adjoint_finalize(Args a, int64_t n_blocks, int pose_frames) {
+    __shared__ double red[FIN_THREADS], acc[12];
+    const int f = blockIdx.x;
+    if (f < pose_frames) {
+        sum_parts<12>(a.pose_part + static_cast<int64_t>(f) * 12, static_cast<int64_t>(a.frames) * 12, n_blocks, red,
+                      acc);
+        if (threadIdx.x != 0) return;
+        double G[9];
+        for (int k = 0; k < 9; ++k) G[k] = acc[k];
         const CamD cam = load_camera(a.poses + 7 * f);
         double dq[4] = {0, 0, 0, 0};
-        if (cam.ok) quat_grad(cam.qh, cam.qn, acc, dq);
+        if (cam.ok) quat_grad(cam.qh, cam.qn, G, dq);
         float* out = a.g_poses + 7 * f;
         const bool bad = overflowed(a.status);
         for (int k = 0; k < 4; ++k) out[k] = bad ? 0.0f : static_cast<float>(dq[k]);
         for (int k = 0; k < 3; ++k) out[4 + k] = bad ? 0.0f : static_cast<float>(acc[9 + k]);
-    }
-}
-
-// Intrinsics gradient: fixed-order sum of the workgroups' partials.
-__global__ __launch_bounds__(256) void k_intr_finalize(Args a, int64_t n_blocks) {
-    __shared__ double red[256][4];
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t b = threadIdx.x; b < n_blocks; b += 256)
-        for (int k = 0; k < 4; ++k) v[k] += a.intr_part[b * 4 + k];
-    for (int k = 0; k < 4; ++k) red[threadIdx.x][k] = v[k];
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s)
-            for (int k = 0; k < 4; ++k) red[threadIdx.x][k] += red[threadIdx.x + s][k];
-        __syncthreads();
-    }
-    if (threadIdx.x < 4) {
-        const float g = overflowed(a.status) ? 0.0f : static_cast<float>(red[0][threadIdx.x]);
+    } else {
+        sum_parts<4>(a.intr_part, 4, n_blocks, red, acc);
+        if (threadIdx.x >= 4) return;
+        const float g = overflowed(a.status) ? 0.0f : static_cast<float>(acc[threadIdx.x]);
         if (a.accumulate) a.g_intr[threadIdx.x] += g;
         else a.g_intr[threadIdx.x] = g;
     }
@@ -666,12 +669,10 @@ hipError_t launch_project_bwd(const Args& a, hipStream_t stream) {
         else
             hipLaunchKernelGGL((k_project_bwd<false, false>), grid, dim3(pb_threads<false, false>()), 0, stream, a);
     }
-    if (a.g_poses)
-        hipLaunchKernelGGL(k_pose_finalize, dim3(static_cast<uint32_t>(a.frames)), dim3(256), 0, stream, a, nb);
-    if (a.g_intr) {
-        if (nb > 0) hipLaunchKernelGGL(k_intr_finalize, dim3(1), dim3(256), 0, stream, a, nb);
-        else hipLaunchKernelGGL(k_intr_finalize, dim3(1), dim3(256), 0, stream, a, int64_t(0));
-    }
+    const int pose_frames = a.g_poses ? a.frames : 0, intr = a.g_intr ? 1 : 0;
+    if (pose_frames + intr > 0)
+        hipLaunchKernelGGL(k_adjoint_finalize, dim3(static_cast<uint32_t>(pose_frames + intr)), dim3(FIN_THREADS), 0,
+                           stream, a, nb, pose_frames);
     return hipGetLastError();
 }
 
