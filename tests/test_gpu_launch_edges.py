@@ -18,7 +18,7 @@ if torch.cuda.is_available():
 @pytest.mark.parametrize("H,W,offset", [(1, 1, 0), (2, 2, 0), (3, 3, 0), (2, 4, 0), (5, 8, 0), (16, 12, 0),
                                         (17, 20, 1), (18, 6, 0), (33, 9, 3), (15, 16, 2)])
 def test_pyramid_strip_edges(H, W, offset):
-    """Strips of eight output rows and pairs of outputs: whole, cut and
+    """Strips of output rows and pairs of outputs: whole, cut and
     smaller than a strip; widths and base addresses that take the 16-byte loads
     and ones that do not.  Each output is a mean of values below 1 with 10
     roundings of 2^-24 per level."""
@@ -31,6 +31,28 @@ def test_pyramid_strip_edges(H, W, offset):
     for lvl, (a, b) in enumerate(zip(got, pyr_ref.pyramid(img.astype(np.float64), 4))):
         assert tuple(a.shape) == b.shape
         np.testing.assert_allclose(a.cpu().numpy(), b, rtol=0, atol=(lvl + 1) * 10 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("W", [36, 38])
+def test_pyramid_long_strips(W):
+    """Enough planes for the strips of eight rows (H_out 17: whole and cut
+    strips), with and without the 16-byte loads, against the short strips on
+    one plane at a time (the same sums in the same order: equal bits)."""
+    img = torch.rand(6000, 33, W, device="cuda")
+    got = raster.gaussian_pyramid(img, 2)[1]
+    for p in (0, 1, 2999, 5999):
+        assert torch.equal(got[p], raster.gaussian_pyramid(img[p].clone(), 2)[1])
+
+
+@pytest.mark.parametrize("H,W", [(1, 8192), (8192, 1), (90, 91), (91, 91), (64, 128)])
+def test_pyramid_levels_in_one_launch(H, W):
+    """Planes at and above the size whose remaining levels share a launch:
+    equal bits to the levels computed one call at a time."""
+    img = torch.rand(3, H, W, device="cuda")
+    got = raster.gaussian_pyramid(img, 6)
+    for lvl in range(1, 6):
+        one = raster.gaussian_pyramid(got[lvl - 1].clone(), 2)[1]
+        assert torch.equal(got[lvl], one), lvl
 
 
 @pytest.mark.parametrize("batch", [64, 128])
