@@ -14,18 +14,19 @@ namespace gv {
 
 // dR_e * dR_e/dq for the e-th entry (row-major) of the rotation matrix of the
 // unit quaternion (w, x, y, z); e is a compile-time constant after unrolling.
-__device__ __forceinline__ void add_rot_partial(int e, float v, const float q[4], float g[4]) {
-    const float w = q[0], x = q[1], y = q[2], z = q[3];
+template <typename F>
+__device__ __forceinline__ void add_rot_partial(int e, F v, const F q[4], F g[4]) {
+    const F w = q[0], x = q[1], y = q[2], z = q[3];
     switch (e) {
-        case 0: g[2] += -4.0f * y * v; g[3] += -4.0f * z * v; break;
-        case 1: g[0] += -2.0f * z * v; g[1] += 2.0f * y * v; g[2] += 2.0f * x * v; g[3] += -2.0f * w * v; break;
-        case 2: g[0] += 2.0f * y * v; g[1] += 2.0f * z * v; g[2] += 2.0f * w * v; g[3] += 2.0f * x * v; break;
-        case 3: g[0] += 2.0f * z * v; g[1] += 2.0f * y * v; g[2] += 2.0f * x * v; g[3] += 2.0f * w * v; break;
-        case 4: g[1] += -4.0f * x * v; g[3] += -4.0f * z * v; break;
-        case 5: g[0] += -2.0f * x * v; g[1] += -2.0f * w * v; g[2] += 2.0f * z * v; g[3] += 2.0f * y * v; break;
-        case 6: g[0] += -2.0f * y * v; g[1] += 2.0f * z * v; g[2] += -2.0f * w * v; g[3] += 2.0f * x * v; break;
-        case 7: g[0] += 2.0f * x * v; g[1] += 2.0f * w * v; g[2] += 2.0f * z * v; g[3] += 2.0f * y * v; break;
-        default: g[1] += -4.0f * x * v; g[2] += -4.0f * y * v; break;
+        case 0: g[2] += -F(4) * y * v; g[3] += -F(4) * z * v; break;
+        case 1: g[0] += -F(2) * z * v; g[1] += F(2) * y * v; g[2] += F(2) * x * v; g[3] += -F(2) * w * v; break;
+        case 2: g[0] += F(2) * y * v; g[1] += F(2) * z * v; g[2] += F(2) * w * v; g[3] += F(2) * x * v; break;
+        case 3: g[0] += F(2) * z * v; g[1] += F(2) * y * v; g[2] += F(2) * x * v; g[3] += F(2) * w * v; break;
+        case 4: g[1] += -F(4) * x * v; g[3] += -F(4) * z * v; break;
+        case 5: g[0] += -F(2) * x * v; g[1] += -F(2) * w * v; g[2] += F(2) * z * v; g[3] += F(2) * y * v; break;
+        case 6: g[0] += -F(2) * y * v; g[1] += F(2) * z * v; g[2] += -F(2) * w * v; g[3] += F(2) * x * v; break;
+        case 7: g[0] += F(2) * x * v; g[1] += F(2) * w * v; g[2] += F(2) * z * v; g[3] += F(2) * y * v; break;
+        default: g[1] += -F(4) * x * v; g[2] += -F(4) * y * v; break;
     }
 }
 
@@ -131,24 +132,43 @@ __device__ __forceinline__ void frame_inputs(const Args& a, int64_t g, const Rec
 // dL/dSig (symmetric, stored xx xy xz yy yz zz) -> gradients of the stored
 // log-scales (out 0-2) and the unnormalised quaternion (out 3-6), through
 // Sig = M M^T, M = R diag(s): dM = 2 G M, dR = dM diag(s), ds_j = sum_i dM_ij R_ij.
-__device__ __forceinline__ void sigma_adjoint(const float G[6], const AdjIn& P, float out[7]) {
-    const float Gm[9] = {G[0], G[1], G[2], G[1], G[3], G[4], G[2], G[4], G[5]};
-    float ds[3] = {0.f, 0.f, 0.f};
-    float gq[4] = {0.f, 0.f, 0.f, 0.f};
+// The quaternion's sums cancel (for equal scales they vanish), which amplifies
+// rounding: Gaussians without dynamics, which take this once after the sum
+// over frames, take it in FP64.
+template <typename F, typename Shape>
+__device__ __forceinline__ void sigma_adjoint(const F G[6], const Shape& P, F out[7]) {
+    const F Gm[9] = {G[0], G[1], G[2], G[1], G[3], G[4], G[2], G[4], G[5]};
+    F ds[3] = {F(0), F(0), F(0)};
+    F gq[4] = {F(0), F(0), F(0), F(0)};
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const float V = Gm[i * 3 + 0] * P.R[0 * 3 + j] + Gm[i * 3 + 1] * P.R[1 * 3 + j] +
-                            Gm[i * 3 + 2] * P.R[2 * 3 + j];
-            const float dM = 2.0f * P.s[j] * V;
+            const F V = Gm[i * 3 + 0] * P.R[0 * 3 + j] + Gm[i * 3 + 1] * P.R[1 * 3 + j] +
+                        Gm[i * 3 + 2] * P.R[2 * 3 + j];
+            const F dM = F(2) * P.s[j] * V;
             ds[j] += dM * P.R[i * 3 + j];
-            add_rot_partial(i * 3 + j, dM * P.s[j], P.qh, gq);
+            add_rot_partial<F>(i * 3 + j, dM * P.s[j], P.qh, gq);
         }
     for (int k = 0; k < 3; ++k) out[k] = ds[k] * P.s[k];
     // q_hat = q / |q|
-    const float dot = P.qh[0] * gq[0] + P.qh[1] * gq[1] + P.qh[2] * gq[2] + P.qh[3] * gq[3];
+    const F dot = P.qh[0] * gq[0] + P.qh[1] * gq[1] + P.qh[2] * gq[2] + P.qh[3] * gq[3];
     for (int k = 0; k < 4; ++k) out[3 + k] = (gq[k] - P.qh[k] * dot) * P.iqn;
+}
+
+// The FP64 shape sigma_adjoint takes for Gaussians without dynamics.
+struct ShapeAdj {
+    double s[3], qh[4], iqn, R[9];
+};
+
+__device__ __forceinline__ void shape_f64(const Args& a, int64_t g, ShapeAdj& P) {
+    const int64_t n = a.n;
+    double q[4];
+    for (int k = 0; k < 3; ++k) P.s[k] = exp(load_param(a.log_scales, a.dtype, k * n + g));
+    for (int k = 0; k < 4; ++k) q[k] = load_param(a.quats, a.dtype, k * n + g);
+    P.iqn = 1.0 / sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
+    for (int k = 0; k < 4; ++k) P.qh[k] = q[k] * P.iqn;
+    rot_from_quat(P.qh[0], P.qh[1], P.qh[2], P.qh[3], P.R);
 }
 
 // Chain rule for one (frame, Gaussian).  d: dL/d(u, v, A00, A01, A11, o, r, g,
@@ -233,7 +253,7 @@ __device__ __forceinline__ void projection_adjoint(const Args& a, const float* R
         for (int k = 0; k < 6; ++k) gout[3 + k] = G[k];
         gout[9] = 0.0f;
     } else {
-        sigma_adjoint(G, P, gout + 3);
+        sigma_adjoint<float>(G, P, gout + 3);
     }
     gout[10] = d[5] * P.o * (1.0f - P.o);
     gout[11] = d[6];
@@ -551,14 +571,18 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
         // a Gaussian culled in every frame (e.g. for non-finite parameters)
         // has dL/dSig = 0 exactly; its shape may hold NaN, so it is not taken
         // through the chain (0 * NaN would poison its gradient)
-        float Gs[6], o7[7];
+        double Gs[6];
         bool touched = false;
         for (int k = 0; k < 6; ++k) {
-            Gs[k] = static_cast<float>(acc[3 + k][tid]);
-            touched = touched || Gs[k] != 0.0f;
+            Gs[k] = acc[3 + k][tid];
+            touched = touched || Gs[k] != 0.0;
         }
-        if (touched) sigma_adjoint(Gs, Pstatic, o7);
-        for (int k = 0; k < 7; ++k) gsq[k] = touched ? o7[k] : 0.0;
+        for (int k = 0; k < 7; ++k) gsq[k] = 0.0;
+        if (touched) {
+            ShapeAdj S;
+            shape_f64(a, g, S);
+            sigma_adjoint<double>(Gs, S, gsq);
+        }
     }
     for (int k = 0; k < 3; ++k) {
         if (a.n_ctrl == 0) put(a.g_means, k * n + g, acc[k][tid]);
