@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gv.h"
 
 namespace gv {
@@ -30,6 +32,7 @@ constexpr float SUB_Q_SLACK = 9.0f * (1.0f + 1e-4f) + 1e-4f;
 
 // Gaussians per workgroup of the LDS-histogram binning kernels, and the
 // largest tile grid whose histogram fits in LDS (64 KiB).
+constexpr int XCDS = 8;  // dies with an L2 each; workgroups are dealt to them in turn
 constexpr int BIN_GROUP = 1024;
 constexpr int LDS_TILE_LIMIT = 16384;
 
@@ -101,7 +104,7 @@ Layout make_layout(const gv_camera& cam, int64_t n, int frames, int64_t k_cap);
 // Frame-independent part of a static Gaussian's projection, computed once
 // per call (k_begin) with the very operations project_gaussian would
 // repeat in every frame: 3D covariance and opacity, whether the shape's
-// parameters (log-scales, quaternion, opacity logit, colour) are finite, and
+// parameters (log-scales, quaternion, opacity logit, colour, SH) are finite, and
 // whether the quaternion has a nonzero norm.
 struct ShapeD {
     double Sig[6];
@@ -161,7 +164,7 @@ struct Args {
     uint32_t* sslot;      // [K]
     float* part;          // [K][PART] (du, dv, dA00, dA01, dA11, do, dr, dg, db) per pre-sort slot
     uint32_t* pused;      // [K/32 + 2] bit per pre-sort slot: its partial record was written (cleared by the forward)
-    ShapeD* shapes;       // [N] static shapes of this call (scenes without dynamics or SH), or nullptr
+    ShapeD* shapes;       // [N] static shapes of this call (scenes without dynamics)
     KeySlot* tkv;         // [K] merge scratch of the sort
     int64_t k_cap;
     // image-space inputs/outputs
@@ -197,9 +200,14 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
     return __uint_as_float(static_cast<uint32_t>(h) << 16);
 }
 
-__device__ __forceinline__ double load_param(const void* base, int dtype, int64_t i) {
-    if (dtype == GV_BF16) return static_cast<double>(bf16_to_f32(static_cast<const uint16_t*>(base)[i]));
-    return static_cast<double>(static_cast<const float*>(base)[i]);
+// A stored parameter of type T: float, or uint16_t for bfloat16 bits.  The type
+// is a template argument of every kernel that reads parameters: as a run-time
+// branch around each load it put every load in a block of its own, waited for
+// before the next was issued.
+template <typename T>
+__device__ __forceinline__ double load_param(const void* base, int64_t i) {
+    if constexpr (sizeof(T) == 2) return static_cast<double>(bf16_to_f32(static_cast<const uint16_t*>(base)[i]));
+    else return static_cast<double>(static_cast<const float*>(base)[i]);
 }
 
 // Rotation matrix (row-major) of the unit quaternion (w, x, y, z).
@@ -400,34 +408,90 @@ __device__ __forceinline__ bool shape_from_params(const double* raw, ProjD& P) {
 
 __device__ __forceinline__ bool project_shaped(const Args& a, const CamD& cam, ProjD& P);
 
-// Returns true if the Gaussian is in front of the near plane with a valid
-// footprint.  P.nonfinite marks non-finite inputs.  EXT compiles in the
-// optional B-spline / polynomial dynamics and the SH colour; the projection
-// kernel takes project_gaussian_shaped instead for scenes without them, whose
-// frame-independent shape is precomputed once per call.
-template <bool EXT>
-__device__ __forceinline__ bool project_gaussian(const Args& a, int64_t g, const CamD& cam, double t, ProjD& P) {
+// Are the Gaussian's SH coefficients finite?
+template <typename T>
+__device__ __forceinline__ bool sh_finite(const Args& a, int64_t g) {
+    bool fin = true;
+    for (int k = 0; k < 3 * sh_count(a.sh_degree); ++k)
+        fin = fin && isfinite(load_param<T>(a.sh, static_cast<int64_t>(k) * a.n + g));
+    return fin;
+}
+
+// View-dependent colour P.col: RGB plus the SH terms at the unit direction
+// from the camera centre to the mean (P.mu).
+template <typename T>
+__device__ __forceinline__ void sh_colour(const Args& a, int64_t g, const CamD& cam, ProjD& P) {
+    const int64_t n = a.n;
+    for (int c = 0; c < 3; ++c) P.col[c] = load_param<T>(a.colors, c * n + g);
+    double v[3];
+    for (int i = 0; i < 3; ++i)
+        v[i] = P.mu[i] + (cam.R[0 * 3 + i] * cam.t[0] + cam.R[1 * 3 + i] * cam.t[1] + cam.R[2 * 3 + i] * cam.t[2]);
+    const double vn = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+    const double iv = vn > 0.0 ? 1.0 / vn : 0.0;
+    double Y[15];
+    sh_eval<double>(a.sh_degree, v[0] * iv, v[1] * iv, v[2] * iv, Y, nullptr);
+    // constant indices (a degree at a time) keep Y in registers; indexed by a
+    // loop of a.sh_degree's length it lived in scratch memory (projection of
+    // the 50-frame clip with degree 3: 1,712 us, 937 us with constant indices)
+    auto add = [&](auto from, auto to) {
+#pragma unroll
+        for (int k = decltype(from)::value; k < decltype(to)::value; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const double kc = load_param<T>(a.sh, (static_cast<int64_t>(k) * 3 + c) * n + g);
+                P.col[c] = P.col[c] + Y[k] * kc;
+            }
+    };
+    add(std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
+    if (a.sh_degree >= 2) add(std::integral_constant<int, 3>{}, std::integral_constant<int, 8>{});
+    if (a.sh_degree >= 3) add(std::integral_constant<int, 8>{}, std::integral_constant<int, 15>{});
+}
+
+// A Gaussian with dynamics (B-spline mean, polynomial log-scales or quaternion).
+// Returns true if it is in front of the near plane with a valid footprint.
+// P.nonfinite marks non-finite inputs.  Scenes without dynamics take
+// project_gaussian_shaped instead, whose frame-independent shape is computed
+// once per call.  SH compiles in the check of the SH coefficients.
+//
+// basis: the spline weights at t, the same for every Gaussian of a frame
+// (SplineD); unused without control points.
+struct SplineD {
+    double N[4];
+    int first;       // first control point they weight
+    bool in_domain;  // t in [0, 1]
+};
+
+__device__ __forceinline__ SplineD spline_at(int n_ctrl, double t) {
+    SplineD s;
+    s.in_domain = t >= 0.0 && t <= 1.0;
+    s.first = spline_basis<double>(n_ctrl, s.in_domain ? t : 0.0, s.N);
+    return s;
+}
+
+template <bool SH, typename T>
+__device__ __forceinline__ bool project_gaussian(const Args& a, int64_t g, const CamD& cam, double t,
+                                                 const SplineD& basis, ProjD& P) {
     const int64_t n = a.n;
     double raw[14];
-    for (int k = 0; k < 3; ++k) raw[k] = EXT && a.n_ctrl > 0 ? 0.0 : load_param(a.means, a.dtype, k * n + g);
-    for (int k = 0; k < 3; ++k) raw[3 + k] = load_param(a.log_scales, a.dtype, k * n + g);
-    for (int k = 0; k < 4; ++k) raw[6 + k] = load_param(a.quats, a.dtype, k * n + g);
-    raw[10] = load_param(a.opacity_logits, a.dtype, g);
-    for (int k = 0; k < 3; ++k) raw[11 + k] = load_param(a.colors, a.dtype, k * n + g);
+    for (int k = 0; k < 3; ++k) raw[k] = a.n_ctrl > 0 ? 0.0 : load_param<T>(a.means, k * n + g);
+    for (int k = 0; k < 3; ++k) raw[3 + k] = load_param<T>(a.log_scales, k * n + g);
+    for (int k = 0; k < 4; ++k) raw[6 + k] = load_param<T>(a.quats, k * n + g);
+    raw[10] = load_param<T>(a.opacity_logits, g);
+    for (int k = 0; k < 3; ++k) raw[11 + k] = load_param<T>(a.colors, k * n + g);
     bool fin = true;
     for (int k = 0; k < 14; ++k) fin = fin && isfinite(raw[k]);
     bool in_domain = true;
-    if (EXT && a.n_ctrl > 0) {
+    if (a.n_ctrl > 0) {
         // B-spline mean (Eq. 2): sum over the span's four control points in
         // index order (the other basis functions are exact zeros)
-        in_domain = t >= 0.0 && t <= 1.0;
-        double N[4];
-        const int b = spline_basis<double>(a.n_ctrl, in_domain ? t : 0.0, N);
+        in_domain = basis.in_domain;
+        const double* N = basis.N;
+        const int b = basis.first;
         for (int k = 0; k < 3; ++k) {
             double mu = 0.0;
             for (int r = 0; r < 4; ++r) {
                 if (N[r] == 0.0) continue;  // local support: zero weight, no part in mu
-                const double c = load_param(a.ctrl, a.dtype, (static_cast<int64_t>(b + r) * 3 + k) * n + g);
+                const double c = load_param<T>(a.ctrl, (static_cast<int64_t>(b + r) * 3 + k) * n + g);
                 fin = fin && isfinite(c);
                 mu = mu + N[r] * c;
             }
@@ -437,9 +501,9 @@ __device__ __forceinline__ bool project_gaussian(const Args& a, int64_t g, const
         for (int k = 0; k < 3; ++k) {
             double mu = raw[k];
             if (a.mean_coeffs) {
-                const double c1 = load_param(a.mean_coeffs, a.dtype, (0 * 3 + k) * n + g);
-                const double c2 = load_param(a.mean_coeffs, a.dtype, (1 * 3 + k) * n + g);
-                const double c3 = load_param(a.mean_coeffs, a.dtype, (2 * 3 + k) * n + g);
+                const double c1 = load_param<T>(a.mean_coeffs, (0 * 3 + k) * n + g);
+                const double c2 = load_param<T>(a.mean_coeffs, (1 * 3 + k) * n + g);
+                const double c3 = load_param<T>(a.mean_coeffs, (2 * 3 + k) * n + g);
                 fin = fin && isfinite(c1) && isfinite(c2) && isfinite(c3);
                 // same left-to-right order as mu0 + a1 t + a2 t t + a3 t t t
                 mu = mu + c1 * t + c2 * t * t + c3 * t * t * t;
@@ -447,63 +511,44 @@ __device__ __forceinline__ bool project_gaussian(const Args& a, int64_t g, const
             P.mu[k] = mu;
         }
     }
-    if (EXT && a.scale_coeffs)
+    if (a.scale_coeffs)
         for (int k = 0; k < 3; ++k) {
-            const double b1 = load_param(a.scale_coeffs, a.dtype, (0 * 3 + k) * n + g);
-            const double b2 = load_param(a.scale_coeffs, a.dtype, (1 * 3 + k) * n + g);
-            const double b3 = load_param(a.scale_coeffs, a.dtype, (2 * 3 + k) * n + g);
+            const double b1 = load_param<T>(a.scale_coeffs, (0 * 3 + k) * n + g);
+            const double b2 = load_param<T>(a.scale_coeffs, (1 * 3 + k) * n + g);
+            const double b3 = load_param<T>(a.scale_coeffs, (2 * 3 + k) * n + g);
             fin = fin && isfinite(b1) && isfinite(b2) && isfinite(b3);
             raw[3 + k] = raw[3 + k] + b1 * t + b2 * t * t + b3 * t * t * t;
         }
-    if (EXT && a.quat_coeffs)
+    if (a.quat_coeffs)
         for (int k = 0; k < 4; ++k) {
-            const double r1 = load_param(a.quat_coeffs, a.dtype, (0 * 4 + k) * n + g);
-            const double r2 = load_param(a.quat_coeffs, a.dtype, (1 * 4 + k) * n + g);
-            const double r3 = load_param(a.quat_coeffs, a.dtype, (2 * 4 + k) * n + g);
+            const double r1 = load_param<T>(a.quat_coeffs, (0 * 4 + k) * n + g);
+            const double r2 = load_param<T>(a.quat_coeffs, (1 * 4 + k) * n + g);
+            const double r3 = load_param<T>(a.quat_coeffs, (2 * 4 + k) * n + g);
             fin = fin && isfinite(r1) && isfinite(r2) && isfinite(r3);
             raw[6 + k] = raw[6 + k] + r1 * t + r2 * t * t + r3 * t * t * t;
         }
-    for (int c = 0; c < 3; ++c) P.col[c] = raw[11 + c];
-    if (EXT && a.sh_degree > 0) {
-        // view-dependent colour: SH at the unit direction camera centre -> mean
-        double v[3];
-        for (int i = 0; i < 3; ++i)
-            v[i] = P.mu[i] + (cam.R[0 * 3 + i] * cam.t[0] + cam.R[1 * 3 + i] * cam.t[1] + cam.R[2 * 3 + i] * cam.t[2]);
-        const double vn = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-        const double iv = vn > 0.0 ? 1.0 / vn : 0.0;
-        double Y[15];
-        sh_eval<double>(a.sh_degree, v[0] * iv, v[1] * iv, v[2] * iv, Y, nullptr);
-        const int nb = sh_count(a.sh_degree);
-        for (int c = 0; c < 3; ++c) {
-            double acc = P.col[c];
-            for (int k = 0; k < nb; ++k) {
-                const double kc = load_param(a.sh, a.dtype, (static_cast<int64_t>(k) * 3 + c) * n + g);
-                fin = fin && isfinite(kc);
-                acc = acc + Y[k] * kc;
-            }
-            P.col[c] = acc;
-        }
-    }
+    if (SH) fin = sh_finite<T>(a, g) && fin;
     P.nonfinite = !fin;
     if (!fin || !cam.ok || !in_domain) return false;
     if (!shape_from_params(raw, P)) return false;
     return project_shaped(a, cam, P);
 }
 
-// The static path with the frame-independent shape precomputed (a.shapes):
-// only the mean (and its cubic in t) is read per frame.
+// The path without dynamics, with the frame-independent shape precomputed
+// (a.shapes): only the mean (and its cubic in t) is read per frame.
+template <typename T>
 __device__ __forceinline__ bool project_gaussian_shaped(const Args& a, int64_t g, const CamD& cam, double t,
                                                         ProjD& P) {
     const int64_t n = a.n;
     const ShapeD& S = a.shapes[g];
     bool fin = S.fin != 0u;
     for (int k = 0; k < 3; ++k) {
-        double mu = load_param(a.means, a.dtype, k * n + g);
+        double mu = load_param<T>(a.means, k * n + g);
         fin = fin && isfinite(mu);
         if (a.mean_coeffs) {
-            const double c1 = load_param(a.mean_coeffs, a.dtype, (0 * 3 + k) * n + g);
-            const double c2 = load_param(a.mean_coeffs, a.dtype, (1 * 3 + k) * n + g);
-            const double c3 = load_param(a.mean_coeffs, a.dtype, (2 * 3 + k) * n + g);
+            const double c1 = load_param<T>(a.mean_coeffs, (0 * 3 + k) * n + g);
+            const double c2 = load_param<T>(a.mean_coeffs, (1 * 3 + k) * n + g);
+            const double c3 = load_param<T>(a.mean_coeffs, (2 * 3 + k) * n + g);
             fin = fin && isfinite(c1) && isfinite(c2) && isfinite(c3);
             // same left-to-right order as mu0 + a1 t + a2 t t + a3 t t t
             mu = mu + c1 * t + c2 * t * t + c3 * t * t * t;

@@ -40,33 +40,34 @@ struct AdjIn {
 };
 
 // Cubic polynomial in t without a constant term: c1 t + c2 t^2 + c3 t^3.
+template <typename T>
 __device__ __forceinline__ float cubic_in_t(const Args& a, const void* coeffs, int rows, int k, int64_t g, float t) {
     const int64_t n = a.n;
-    const float c1 = static_cast<float>(load_param(coeffs, a.dtype, (0 * rows + k) * n + g));
-    const float c2 = static_cast<float>(load_param(coeffs, a.dtype, (1 * rows + k) * n + g));
-    const float c3 = static_cast<float>(load_param(coeffs, a.dtype, (2 * rows + k) * n + g));
+    const float c1 = static_cast<float>(load_param<T>(coeffs, (0 * rows + k) * n + g));
+    const float c2 = static_cast<float>(load_param<T>(coeffs, (1 * rows + k) * n + g));
+    const float c3 = static_cast<float>(load_param<T>(coeffs, (2 * rows + k) * n + g));
     return t * (c1 + t * (c2 + t * c3));
 }
 
 // Shape part of the adjoint inputs at time t: scales, normalised quaternion
 // (and 1/|q|), rotation, 3D covariance and opacity.  Static Gaussians (DYN
 // false) compute it once; t enters only through Eq. 3's polynomials.
-template <bool DYN>
+template <bool DYN, typename T>
 __device__ __forceinline__ void shape_inputs(const Args& a, int64_t g, float t, AdjIn& P) {
     const int64_t n = a.n;
     float q[4];
     for (int k = 0; k < 3; ++k) {
-        float ls = static_cast<float>(load_param(a.log_scales, a.dtype, k * n + g));
-        if (DYN && a.scale_coeffs) ls = ls + cubic_in_t(a, a.scale_coeffs, 3, k, g, t);
+        float ls = static_cast<float>(load_param<T>(a.log_scales, k * n + g));
+        if (DYN && a.scale_coeffs) ls = ls + cubic_in_t<T>(a, a.scale_coeffs, 3, k, g, t);
         P.s[k] = expf(ls);
     }
     for (int k = 0; k < 4; ++k) {
-        q[k] = static_cast<float>(load_param(a.quats, a.dtype, k * n + g));
-        if (DYN && a.quat_coeffs) q[k] = q[k] + cubic_in_t(a, a.quat_coeffs, 4, k, g, t);
+        q[k] = static_cast<float>(load_param<T>(a.quats, k * n + g));
+        if (DYN && a.quat_coeffs) q[k] = q[k] + cubic_in_t<T>(a, a.quat_coeffs, 4, k, g, t);
     }
     P.iqn = 1.0f / sqrtf(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
     for (int k = 0; k < 4; ++k) P.qh[k] = q[k] * P.iqn;
-    const float eta = static_cast<float>(load_param(a.opacity_logits, a.dtype, g));
+    const float eta = static_cast<float>(load_param<T>(a.opacity_logits, g));
     P.o = 1.0f / (1.0f + expf(-eta));
     {
         const float w = P.qh[0], x = P.qh[1], y = P.qh[2], z = P.qh[3];
@@ -92,7 +93,7 @@ __device__ __forceinline__ void shape_inputs(const Args& a, int64_t g, float t, 
 // position, the projection Jacobian times the camera rotation, and the conic
 // of the forward record (the FP64 value rounded once: exactly the one the
 // compositing kernels used).
-template <bool DYN>
+template <bool DYN, typename T>
 __device__ __forceinline__ void frame_inputs(const Args& a, int64_t g, const Record& rec, const float* Rc,
                                              const float* tc, float t, AdjIn& P) {
     const int64_t n = a.n;
@@ -104,13 +105,13 @@ __device__ __forceinline__ void frame_inputs(const Args& a, int64_t g, const Rec
             for (int r = 0; r < 4; ++r)
                 if (P.N[r] != 0.0f)
                     mu += P.N[r] * static_cast<float>(
-                                       load_param(a.ctrl, a.dtype, (static_cast<int64_t>(P.span + r) * 3 + k) * n + g));
+                                       load_param<T>(a.ctrl, (static_cast<int64_t>(P.span + r) * 3 + k) * n + g));
             P.mu[k] = mu;
         }
     } else {
         for (int k = 0; k < 3; ++k) {
-            float mu = static_cast<float>(load_param(a.means, a.dtype, k * n + g));
-            if (a.mean_coeffs) mu = mu + cubic_in_t(a, a.mean_coeffs, 3, k, g, t);
+            float mu = static_cast<float>(load_param<T>(a.means, k * n + g));
+            if (a.mean_coeffs) mu = mu + cubic_in_t<T>(a, a.mean_coeffs, 3, k, g, t);
             P.mu[k] = mu;
         }
     }
@@ -161,11 +162,12 @@ struct ShapeAdj {
     double s[3], qh[4], iqn, R[9];
 };
 
+template <typename T>
 __device__ __forceinline__ void shape_f64(const Args& a, int64_t g, ShapeAdj& P) {
     const int64_t n = a.n;
     double q[4];
-    for (int k = 0; k < 3; ++k) P.s[k] = exp(load_param(a.log_scales, a.dtype, k * n + g));
-    for (int k = 0; k < 4; ++k) q[k] = load_param(a.quats, a.dtype, k * n + g);
+    for (int k = 0; k < 3; ++k) P.s[k] = exp(load_param<T>(a.log_scales, k * n + g));
+    for (int k = 0; k < 4; ++k) q[k] = load_param<T>(a.quats, k * n + g);
     P.iqn = 1.0 / sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
     for (int k = 0; k < 4; ++k) P.qh[k] = q[k] * P.iqn;
     rot_from_quat(P.qh[0], P.qh[1], P.qh[2], P.qh[3], P.R);
@@ -278,7 +280,7 @@ struct AccLayout {
 // add Y_k(d) dL/dc to the coefficient accumulators and return, through the
 // unit direction d = v / |v|, v = mu - C, dL/dv (it adds to dL/dmu, and
 // -dL/dv is the gradient of the camera centre C = -Rc^T tc).
-template <int NT>
+template <int NT, typename T>
 __device__ __forceinline__ void sh_adjoint(const Args& a, int64_t g, const AdjIn& P, const float* camC,
                                            const float dc[3], float (*acc_sh)[NT], int tid, float dv[3]) {
     const int64_t n = a.n;
@@ -298,7 +300,7 @@ __device__ __forceinline__ void sh_adjoint(const Args& a, int64_t g, const AdjIn
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 acc_sh[k * 3 + c][tid] += Y[k] * dc[c];
-                w += dc[c] * static_cast<float>(load_param(a.sh, a.dtype, (static_cast<int64_t>(k) * 3 + c) * n + g));
+                w += dc[c] * static_cast<float>(load_param<T>(a.sh, (static_cast<int64_t>(k) * 3 + c) * n + g));
             }
 #pragma unroll
             for (int j = 0; j < 3; ++j) dd[j] += w * G[k][j];
@@ -320,7 +322,7 @@ constexpr int pb_split() { return DYN ? 1 : SH ? 2 : 4; }
 template <bool DYN, bool SH>
 constexpr int pb_threads() { return DYN ? 128 : 64 * pb_split<DYN, SH>(); }
 
-template <bool DYN, bool SH>
+template <bool DYN, bool SH, typename T>
 __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a) {
     if (overflowed(a.status)) return;
     using LA = AccLayout<DYN>;
@@ -369,7 +371,7 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
     // a static Gaussian's shape (scales, rotation, 3D covariance, opacity) is
     // the same in every frame
     AdjIn Pstatic = {};
-    if (!DYN && live) shape_inputs<false>(a, g, 0.0f, Pstatic);
+    if (!DYN && live) shape_inputs<false, T>(a, g, 0.0f, Pstatic);
     // the next frame's count, slot offset and record are loaded one frame ahead
     uint32_t cnt_n = 0u, base_n = 0u;
     Record rec_n = {};
@@ -440,8 +442,8 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
                 load_round(0);
                 const float t = a.times ? a.times[f] : a.t0;
                 AdjIn P = Pstatic;
-                if (DYN) shape_inputs<DYN>(a, g, t, P);
-                frame_inputs<DYN>(a, g, rec, camR, camT, t, P);
+                if (DYN) shape_inputs<DYN, T>(a, g, t, P);
+                frame_inputs<DYN, T>(a, g, rec, camR, camT, t, P);
                 double dd[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
                 for (uint32_t k0 = 0;;) {
                     const uint32_t bits = static_cast<uint32_t>(
@@ -464,7 +466,7 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
                 if (SH) {
                     float dv[3];
                     const float dc[3] = {go[11], go[12], go[13]};
-                    sh_adjoint<PB_THREADS>(a, g, P, camC, dc, acc_sh, tid, dv);
+                    sh_adjoint<PB_THREADS, T>(a, g, P, camC, dc, acc_sh, tid, dv);
                     for (int j = 0; j < 3; ++j) {
                         go[j] += dv[j];
                         // C = -Rc^T tc, dL/dC = -dv: dL/dtc = Rc dv, dL/dRc[j][i] = tc[j] dv[i]
@@ -580,7 +582,7 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
         for (int k = 0; k < 7; ++k) gsq[k] = 0.0;
         if (touched) {
             ShapeAdj S;
-            shape_f64(a, g, S);
+            shape_f64<T>(a, g, S);
             sigma_adjoint<double>(Gs, S, gsq);
         }
     }
@@ -678,20 +680,22 @@ static int64_t blocks_for(int64_t n, bool dyn, bool sh) {
     return (n + gpb - 1) / gpb;
 }
 
+template <bool DYN, bool SH, typename T>
+static void launch_adjoint(const Args& a, dim3 grid, hipStream_t stream) {
+    hipLaunchKernelGGL((k_project_bwd<DYN, SH, T>), grid, dim3(pb_threads<DYN, SH>()), 0, stream, a);
+}
+
 hipError_t launch_project_bwd(const Args& a, hipStream_t stream) {
     const bool dyn = a.n_ctrl > 0 || a.scale_coeffs || a.quat_coeffs;
     const bool sh = a.sh_degree > 0;
     const int64_t nb = blocks_for(a.n, dyn, sh);
     const dim3 grid(static_cast<uint32_t>(nb > 0 ? nb : 1));
     if (nb > 0) {
-        if (dyn && sh)
-            hipLaunchKernelGGL((k_project_bwd<true, true>), grid, dim3(pb_threads<true, true>()), 0, stream, a);
-        else if (dyn)
-            hipLaunchKernelGGL((k_project_bwd<true, false>), grid, dim3(pb_threads<true, false>()), 0, stream, a);
-        else if (sh)
-            hipLaunchKernelGGL((k_project_bwd<false, true>), grid, dim3(pb_threads<false, true>()), 0, stream, a);
-        else
-            hipLaunchKernelGGL((k_project_bwd<false, false>), grid, dim3(pb_threads<false, false>()), 0, stream, a);
+        const bool bf16 = a.dtype == GV_BF16;
+        if (dyn && sh) bf16 ? launch_adjoint<true, true, uint16_t>(a, grid, stream) : launch_adjoint<true, true, float>(a, grid, stream);
+        else if (dyn) bf16 ? launch_adjoint<true, false, uint16_t>(a, grid, stream) : launch_adjoint<true, false, float>(a, grid, stream);
+        else if (sh) bf16 ? launch_adjoint<false, true, uint16_t>(a, grid, stream) : launch_adjoint<false, true, float>(a, grid, stream);
+        else bf16 ? launch_adjoint<false, false, uint16_t>(a, grid, stream) : launch_adjoint<false, false, float>(a, grid, stream);
     }
     const int pose_frames = a.g_poses ? a.frames : 0, intr = a.g_intr ? 1 : 0;
     if (pose_frames + intr > 0)
