@@ -1,10 +1,9 @@
-// Adjoint of the EWA projection.  One thread per Gaussian loops over the
-// frames: it sums the per-(Gaussian, tile) partials left by the compositing
-// adjoint (contiguous slots of this Gaussian, in FP64), takes the conic of the
-// forward record, re-derives the rest of the frame's projection and applies
-// the chain rule down to the stored parameters in FP32, accumulating the
-// shared parameters over frames in FP64 (in LDS, which keeps the chain rule's
-// registers free for occupancy).
+// Adjoint of the EWA projection.  Per (frame, Gaussian) it sums the
+// per-(Gaussian, tile) partials left by the compositing adjoint (contiguous
+// slots of this Gaussian, in FP64), takes the conic of the forward record,
+// re-derives the rest of the frame's projection and applies the chain rule down
+// to the stored parameters in FP32; the shared parameters are summed over the
+// frames in FP64.
 // Each frame's pose gradient (dL/dRc, dL/dtc) is reduced per workgroup in a
 // fixed order; a second kernel sums the workgroups and maps it to the 7-vector
 // pose.  Everything is deterministic (no floating-point atomics).
@@ -89,6 +88,21 @@ __device__ __forceinline__ void shape_inputs(const Args& a, int64_t g, float t, 
     }
 }
 
+// Camera-space position of the mean P.mu and the projection Jacobian times the
+// camera rotation.
+__device__ __forceinline__ void frame_geometry(const Args& a, const float* Rc, const float* tc, AdjIn& P) {
+    for (int i = 0; i < 3; ++i)
+        P.m[i] = tc[i] + Rc[i * 3 + 0] * P.mu[0] + Rc[i * 3 + 1] * P.mu[1] + Rc[i * 3 + 2] * P.mu[2];
+    P.iz = 1.0f / P.m[2];
+    const float iz = P.iz;
+    const float j00 = a.fx * iz, j02 = -a.fx * P.m[0] * iz * iz;
+    const float j11 = a.fy * iz, j12 = -a.fy * P.m[1] * iz * iz;
+    for (int j = 0; j < 3; ++j) {
+        P.T[j] = j00 * Rc[0 * 3 + j] + j02 * Rc[2 * 3 + j];
+        P.T[3 + j] = j11 * Rc[1 * 3 + j] + j12 * Rc[2 * 3 + j];
+    }
+}
+
 // Frame part: the mean at time t (B-spline, cubic or static), its camera-space
 // position, the projection Jacobian times the camera rotation, and the conic
 // of the forward record (the FP64 value rounded once: exactly the one the
@@ -115,16 +129,7 @@ __device__ __forceinline__ void frame_inputs(const Args& a, int64_t g, const Rec
             P.mu[k] = mu;
         }
     }
-    for (int i = 0; i < 3; ++i)
-        P.m[i] = tc[i] + Rc[i * 3 + 0] * P.mu[0] + Rc[i * 3 + 1] * P.mu[1] + Rc[i * 3 + 2] * P.mu[2];
-    P.iz = 1.0f / P.m[2];
-    const float iz = P.iz;
-    const float j00 = a.fx * iz, j02 = -a.fx * P.m[0] * iz * iz;
-    const float j11 = a.fy * iz, j12 = -a.fy * P.m[1] * iz * iz;
-    for (int j = 0; j < 3; ++j) {
-        P.T[j] = j00 * Rc[0 * 3 + j] + j02 * Rc[2 * 3 + j];
-        P.T[3 + j] = j11 * Rc[1 * 3 + j] + j12 * Rc[2 * 3 + j];
-    }
+    frame_geometry(a, Rc, tc, P);
     P.A[0] = rec.a;
     P.A[1] = rec.b;
     P.A[2] = rec.c;
@@ -171,6 +176,21 @@ __device__ __forceinline__ void shape_f64(const Args& a, int64_t g, ShapeAdj& P)
     P.iqn = 1.0 / sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
     for (int k = 0; k < 4; ++k) P.qh[k] = q[k] * P.iqn;
     rot_from_quat(P.qh[0], P.qh[1], P.qh[2], P.qh[3], P.R);
+}
+
+// dL/dSig summed over the frames to log-scales and quaternion.  A Gaussian
+// culled in every frame (e.g. for non-finite parameters) has dL/dSig = 0
+// exactly; its shape may hold NaN, so it is not taken through the chain (0 * NaN
+// would poison its gradient).
+template <typename T>
+__device__ __forceinline__ void static_shape_adjoint(const Args& a, int64_t g, const double* Gs, double out[7]) {
+    bool touched = false;
+    for (int k = 0; k < 6; ++k) touched = touched || Gs[k] != 0.0;
+    for (int k = 0; k < 7; ++k) out[k] = 0.0;
+    if (!touched) return;
+    ShapeAdj S;
+    shape_f64<T>(a, g, S);
+    sigma_adjoint<double>(Gs, S, out);
 }
 
 // Chain rule for one (frame, Gaussian).  d: dL/d(u, v, A00, A01, A11, o, r, g,
@@ -310,7 +330,223 @@ __device__ __forceinline__ void sh_adjoint(const Args& a, int64_t g, const AdjIn
     for (int j = 0; j < 3; ++j) dv[j] = (dd[j] - d[j] * dot) * iv;
 }
 
-// SPLIT waves share each Gaussian: wave h of a workgroup takes the h-th
+// Sum of a Gaussian's marked partial records in one frame (cnt slots from base
+// on), in slot order in FP64, rounded once.  PU records per round, their loads
+// issued together with the marks (past the end they repeat a valid record and
+// are not added; records the adjoint did not write this pass hold stale values
+// and are not added either).
+template <uint32_t PU>
+struct PartialRound {
+    float r[PU][PART];
+    uint32_t w0, w1;  // words holding the round's marks
+    __device__ __forceinline__ void load(const Args& a, uint32_t base, uint32_t cnt, uint32_t k0) {
+        const uint32_t wi = (base + k0) >> 5;
+        w0 = a.pused[wi];
+        w1 = a.pused[wi + 1];
+#pragma unroll
+        for (uint32_t u = 0; u < PU; ++u) {
+            const uint32_t k = k0 + u < cnt ? k0 + u : k0;
+            const float* pp = a.part + static_cast<int64_t>(base + k) * PART;
+#pragma unroll
+            for (int m = 0; m < PART; ++m) r[u][m] = pp[m];
+        }
+    }
+    __device__ __forceinline__ void add(uint32_t base, uint32_t cnt, uint32_t k0, double (&s)[PART]) const {
+        const uint32_t bits = static_cast<uint32_t>(((static_cast<uint64_t>(w1) << 32) | w0) >> ((base + k0) & 31u));
+#pragma unroll
+        for (uint32_t u = 0; u < PU; ++u)
+            if (k0 + u < cnt && ((bits >> u) & 1u))
+#pragma unroll
+                for (int m = 0; m < PART; ++m) s[m] += r[u][m];
+    }
+};
+constexpr uint32_t PU = 4;
+
+// The adjoint of Gaussians without dynamics or SH: one lane per Gaussian and
+// SPLIT waves per 64 Gaussians, each taking a contiguous part of the frames
+// (quarters rather than halves shorten the last round of workgroups, which runs
+// almost alone); the parts' FP64 sums are added in order at the end.  Fewer than
+// four frames take SPLIT = 1, which leaves no wave of a workgroup idle: the
+// adjoint of one 960x540 frame of 100k Gaussians 48 -> 26 us.
+//
+// Bound by the latency and the rate of the record reads (36 bytes each, in runs
+// of a few).  Rounds of four records and sums in registers hold it at three
+// waves per SIMD where rounds of eight with the sums in LDS held two; the next
+// frame's count, offset and conic are requested after this frame's first
+// records, not before, so that waiting for the records does not wait for them:
+// 544 -> 526 us on the 50-frame 960x540 clip, 1,869 -> 1,648 us on the 32-frame
+// 1080p clip with cubic means.  (Staging a wave's records through LDS in
+// coalesced reads cut the loads to a quarter but took twice the VALU: 613 us.)
+template <int SPLIT, bool CUBIC, typename T>
+__global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
+    if (overflowed(a.status)) return;
+    constexpr int FC = 16;  // frames whose cameras and pose sums are in LDS
+    constexpr int NA = CUBIC ? 23 : 14;
+    __shared__ float cam[SPLIT][FC][12], wpose[SPLIT][FC][12];
+    __shared__ double red[SPLIT][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int h = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t n = a.n, g0 = static_cast<int64_t>(blockIdx.x) * 64;
+    const int64_t g = g0 + lane;
+    const bool live = g < n;
+    const int64_t gs = live ? g : n - 1;
+    const int fpart = (a.frames + SPLIT - 1) / SPLIT;
+    const int fb = min(h * fpart, a.frames), fe = min(fb + fpart, a.frames);
+
+    AdjIn P = {};
+    float mu0[3], mc[9];
+    for (int k = 0; k < 3; ++k) mu0[k] = static_cast<float>(load_param<T>(a.means, k * n + gs));
+    if (CUBIC)
+        for (int k = 0; k < 9; ++k) mc[k] = static_cast<float>(load_param<T>(a.mean_coeffs, k * n + gs));
+    for (int k = 0; k < 6; ++k) P.Sig[k] = static_cast<float>(a.shapes[gs].Sig[k]);
+    P.o = static_cast<float>(a.shapes[gs].o);
+
+    double acc[NA], iacc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < NA; ++k) acc[k] = 0.0;
+
+    uint32_t cnt1 = 0u, base1 = 0u;  // of the frame about to be taken
+    float4 rec1 = {};
+    auto slots = [&](int f, uint32_t& c, uint32_t& b) {
+        const int64_t i = static_cast<int64_t>(f) * n + gs;
+        c = live ? a.gcnt[i] : 0u;
+        b = a.goff[i];
+    };
+    auto conic = [&](int f) {
+        return *reinterpret_cast<const float4*>(&a.rec[static_cast<int64_t>(f) * n + gs].a);
+    };
+    auto prefetch = [&](int f) {
+        if (f >= fe) return;
+        slots(f, cnt1, base1);
+        rec1 = conic(f);
+    };
+    prefetch(fb);
+#pragma unroll 1
+    for (int c0 = 0; c0 < fpart; c0 += FC) {  // the same chunk count in every wave (uniform barriers)
+        const int f0 = fb + c0;
+        const int nf = max(0, min(fe - f0, FC));
+        __syncthreads();  // the previous chunk's cameras and pose sums are consumed
+        for (int q = tid; q < SPLIT * FC; q += 64 * SPLIT) {
+            const int hh = q / FC, fi = q % FC;
+            const int ff = hh * fpart + c0 + fi;
+            if (ff < min((hh + 1) * fpart, a.frames)) {
+                const CamD c = load_camera(a.poses + 7 * ff);
+                for (int k = 0; k < 9; ++k) cam[hh][fi][k] = c.ok ? static_cast<float>(c.R[k]) : 0.0f;
+                for (int k = 0; k < 3; ++k) cam[hh][fi][9 + k] = c.ok ? static_cast<float>(c.t[k]) : 0.0f;
+            }
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int fi = 0; fi < nf; ++fi) {
+            const int f = f0 + fi;
+            uint32_t cnt = cnt1;
+            const uint32_t base = base1;
+            const float4 rec = rec1;
+            if (static_cast<int64_t>(base) + cnt > a.k_cap) cnt = 0u;  // only after an internal error
+            const float* camR = cam[h][fi];
+            const float* camT = cam[h][fi] + 9;
+            float pose[12];
+            for (int k = 0; k < 12; ++k) pose[k] = 0.0f;
+            if (cnt) {
+                PartialRound<PU> R;  // requested before the frame's geometry, which does not need it
+                R.load(a, base, cnt, 0u);
+                prefetch(f + 1);
+                const float t = a.times ? a.times[f] : a.t0;
+                for (int k = 0; k < 3; ++k) {
+                    P.mu[k] = mu0[k];
+                    if (CUBIC) P.mu[k] = mu0[k] + t * (mc[k] + t * (mc[3 + k] + t * mc[6 + k]));
+                }
+                frame_geometry(a, camR, camT, P);
+                P.A[0] = rec.x;
+                P.A[1] = rec.y;
+                P.A[2] = rec.z;
+                double s[PART] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+                for (uint32_t k0 = 0;;) {
+                    R.add(base, cnt, k0, s);
+                    k0 += PU;
+                    if (k0 >= cnt) break;
+                    R.load(a, base, cnt, k0);
+                }
+                float d[PART];
+                for (int k = 0; k < PART; ++k) d[k] = static_cast<float>(s[k]);
+                float go[14], gi[4];
+                projection_adjoint<true>(a, camR, P, d, go, pose, gi);
+                for (int k = 0; k < 4; ++k) iacc[k] += gi[k];
+                for (int k = 0; k < 14; ++k) acc[k] += go[k];
+                if (CUBIC) {
+                    const double t1 = t, t2 = t1 * t1, t3 = t2 * t1;
+                    for (int k = 0; k < 3; ++k) {
+                        acc[14 + k] += go[k] * t1;
+                        acc[17 + k] += go[k] * t2;
+                        acc[20 + k] += go[k] * t3;
+                    }
+                }
+            }
+            else prefetch(f + 1);
+            if (a.g_poses) {  // wave sums of this frame's pose contributions
+                float v[16];
+#pragma unroll
+                for (int k = 0; k < 12; ++k) v[k] = pose[k];
+#pragma unroll
+                for (int k = 12; k < 16; ++k) v[k] = 0.0f;
+                const float x = reduce_scatter16(v, lane);
+                const int idx = reduce_scatter16_index(lane);
+                if ((lane & 3) == 0 && idx < 12) wpose[h][fi][idx] = x;
+            }
+        }
+        if (a.g_poses) {
+            __syncthreads();
+            for (int q = tid; q < SPLIT * FC * 12; q += 64 * SPLIT) {
+                const int hh = q / (FC * 12), r = q % (FC * 12), fi = r / 12, k = r % 12;
+                const int ff = hh * fpart + c0 + fi;
+                if (ff < min((hh + 1) * fpart, a.frames))
+                    a.pose_part[(static_cast<int64_t>(blockIdx.x) * a.frames + ff) * 12 + k] =
+                        static_cast<double>(wpose[hh][fi][k]);
+            }
+        }
+    }
+    if (a.g_intr) {
+        for (int k = 0; k < 4; ++k) {
+            const double v = wave_sum_f64(iacc[k]);
+            if (lane == 0) red[h][k] = v;
+        }
+        __syncthreads();
+        if (tid < 4) {
+            double v = 0.0;
+            for (int hh = 0; hh < SPLIT; ++hh) v += red[hh][tid];
+            a.intr_part[static_cast<int64_t>(blockIdx.x) * 4 + tid] = v;
+        }
+    }
+    if (SPLIT > 1) {  // add the later parts' sums to part 0's, in order
+#pragma unroll
+        for (int k = 0; k < NA; ++k) {
+            __syncthreads();
+            red[h][lane] = acc[k];
+            __syncthreads();
+            if (h == 0)
+                for (int hh = 1; hh < SPLIT; ++hh) acc[k] += red[hh][lane];
+        }
+    }
+    if (!live || h != 0) return;
+    auto put = [&](float* dst, int64_t idx, double v) {
+        if (!dst) return;
+        if (a.accumulate) dst[idx] += static_cast<float>(v);
+        else dst[idx] = static_cast<float>(v);
+    };
+    double gsq[7];
+    static_shape_adjoint<T>(a, g, acc + 3, gsq);
+    for (int k = 0; k < 3; ++k) {
+        put(a.g_means, k * n + g, acc[k]);
+        put(a.g_log_scales, k * n + g, gsq[k]);
+        put(a.g_colors, k * n + g, acc[11 + k]);
+    }
+    for (int k = 0; k < 4; ++k) put(a.g_quats, k * n + g, gsq[3 + k]);
+    put(a.g_opacity, g, acc[10]);
+    if (CUBIC)
+        for (int k = 0; k < 9; ++k) put(a.g_coeffs, k * n + g, acc[14 + k]);
+}
+
+// The adjoint with dynamics or SH.  SPLIT waves share each Gaussian: wave h of
+// a workgroup takes the h-th
 // contiguous part of the frames for the workgroup's 64 Gaussians, and the
 // parts' accumulators are added in a fixed order at the end.  Shorter parts
 // keep more waves in flight for this latency-bound kernel and leave a shorter
@@ -318,7 +554,7 @@ __device__ __forceinline__ void sh_adjoint(const Args& a, int64_t g, const AdjIn
 // wave per Gaussian (its control-point window adds to memory as it moves) and
 // the SH variant two parts (its coefficient accumulators take LDS).
 template <bool DYN, bool SH>
-constexpr int pb_split() { return DYN ? 1 : SH ? 2 : 4; }
+constexpr int pb_split() { return DYN ? 1 : 2; }
 template <bool DYN, bool SH>
 constexpr int pb_threads() { return DYN ? 128 : 64 * pb_split<DYN, SH>(); }
 
@@ -570,21 +806,9 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
     if (DYN) {
         for (int k = 0; k < 7; ++k) gsq[k] = acc[3 + k][tid];
     } else {  // dL/dSig summed over the frames, through the shape once
-        // a Gaussian culled in every frame (e.g. for non-finite parameters)
-        // has dL/dSig = 0 exactly; its shape may hold NaN, so it is not taken
-        // through the chain (0 * NaN would poison its gradient)
         double Gs[6];
-        bool touched = false;
-        for (int k = 0; k < 6; ++k) {
-            Gs[k] = acc[3 + k][tid];
-            touched = touched || Gs[k] != 0.0;
-        }
-        for (int k = 0; k < 7; ++k) gsq[k] = 0.0;
-        if (touched) {
-            ShapeAdj S;
-            shape_f64<T>(a, g, S);
-            sigma_adjoint<double>(Gs, S, gsq);
-        }
+        for (int k = 0; k < 6; ++k) Gs[k] = acc[3 + k][tid];
+        static_shape_adjoint<T>(a, g, Gs, gsq);
     }
     for (int k = 0; k < 3; ++k) {
         if (a.n_ctrl == 0) put(a.g_means, k * n + g, acc[k][tid]);
@@ -664,20 +888,32 @@ __global__ __launch_bounds__(FIN_THREADS) void k_adjoint_finalize(Args a, int64_
 // Gaussians per workgroup of each variant.
 template <bool DYN, bool SH>
 constexpr int pb_gaussians() { return pb_threads<DYN, SH>() / pb_split<DYN, SH>(); }
-static_assert(pb_gaussians<false, false>() == 64 && pb_gaussians<false, true>() == 64 &&
-                  pb_gaussians<true, false>() >= 64 && pb_gaussians<true, true>() >= 64,
-              "the static variants have the most workgroups");
+constexpr int STATIC_GAUSSIANS = 64;  // of k_adjoint_static
+static_assert(pb_gaussians<false, true>() >= STATIC_GAUSSIANS && pb_gaussians<true, false>() >= STATIC_GAUSSIANS &&
+                  pb_gaussians<true, true>() >= STATIC_GAUSSIANS,
+              "the static kernel has the most workgroups");
 
 // Upper bound over the variants.
 int64_t project_bwd_blocks(int64_t n) {
-    constexpr int gpb = pb_gaussians<false, false>();
-    return (n + gpb - 1) / gpb;
+    return (n + STATIC_GAUSSIANS - 1) / STATIC_GAUSSIANS;
 }
 
 static int64_t blocks_for(int64_t n, bool dyn, bool sh) {
     const int gpb = dyn ? (sh ? pb_gaussians<true, true>() : pb_gaussians<true, false>())
-                        : (sh ? pb_gaussians<false, true>() : pb_gaussians<false, false>());
+                        : (sh ? pb_gaussians<false, true>() : STATIC_GAUSSIANS);
     return (n + gpb - 1) / gpb;
+}
+
+template <typename T>
+static void launch_static(const Args& a, dim3 grid, hipStream_t stream) {
+    // four parts of the frames per 64 Gaussians where there are four frames
+    if (a.frames >= 4) {
+        if (a.mean_coeffs) hipLaunchKernelGGL((k_adjoint_static<4, true, T>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((k_adjoint_static<4, false, T>), grid, dim3(256), 0, stream, a);
+    } else {
+        if (a.mean_coeffs) hipLaunchKernelGGL((k_adjoint_static<1, true, T>), grid, dim3(64), 0, stream, a);
+        else hipLaunchKernelGGL((k_adjoint_static<1, false, T>), grid, dim3(64), 0, stream, a);
+    }
 }
 
 template <bool DYN, bool SH, typename T>
@@ -695,7 +931,7 @@ hipError_t launch_project_bwd(const Args& a, hipStream_t stream) {
         if (dyn && sh) bf16 ? launch_adjoint<true, true, uint16_t>(a, grid, stream) : launch_adjoint<true, true, float>(a, grid, stream);
         else if (dyn) bf16 ? launch_adjoint<true, false, uint16_t>(a, grid, stream) : launch_adjoint<true, false, float>(a, grid, stream);
         else if (sh) bf16 ? launch_adjoint<false, true, uint16_t>(a, grid, stream) : launch_adjoint<false, true, float>(a, grid, stream);
-        else bf16 ? launch_adjoint<false, false, uint16_t>(a, grid, stream) : launch_adjoint<false, false, float>(a, grid, stream);
+        else bf16 ? launch_static<uint16_t>(a, grid, stream) : launch_static<float>(a, grid, stream);
     }
     const int pose_frames = a.g_poses ? a.frames : 0, intr = a.g_intr ? 1 : 0;
     if (pose_frames + intr > 0)

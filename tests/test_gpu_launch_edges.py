@@ -6,7 +6,7 @@ import torch
 
 from oracle import pyramid as pyr_ref
 from parity_util import device_inputs, workspace_for
-from test_gpu_parity import small_workload
+from test_gpu_parity import check_clip_against_oracle, small_workload
 from test_gpu_visibility_pyramid import check_visibility
 
 pytestmark = pytest.mark.gpu
@@ -95,3 +95,13 @@ def test_small_launches_match_the_one_wave_kernels(frames):
         if g is not None:
             assert torch.linalg.norm(g - b["grads"][k]) <= 256 * 2.0 ** -24 * torch.linalg.norm(g), k
             assert torch.equal(g, c["grads"][k]), k
+
+
+@pytest.mark.parametrize("frames", [1, 3, 4, 5, 9])
+@pytest.mark.parametrize("n", [1, 64, 129])
+def test_adjoint_parts_of_the_frames(frames, n):
+    """Fewer than four frames (one wave per 64 Gaussians), four parts of equal
+    and unequal length with empty ones, whole and cut groups of Gaussians, with
+    more tiles per Gaussian than a round of partial records holds."""
+    w = small_workload(90 + n, 96, 80, n, frames, trajectory=True, z=(2.0, 6.0), ls=(-1.9, 0.4))
+    check_clip_against_oracle(w, f"adjoint parts F={frames} n={n}")
