@@ -48,21 +48,20 @@ __device__ __forceinline__ float cubic_in_t(const Args& a, const void* coeffs, i
     return t * (c1 + t * (c2 + t * c3));
 }
 
-// Shape part of the adjoint inputs at time t: scales, normalised quaternion
-// (and 1/|q|), rotation, 3D covariance and opacity.  Static Gaussians (DYN
-// false) compute it once; t enters only through Eq. 3's polynomials.
-template <bool DYN, typename T>
+// Shape part of the adjoint inputs of a Gaussian with dynamics at time t:
+// scales, normalised quaternion (and 1/|q|), rotation, 3D covariance, opacity.
+template <typename T>
 __device__ __forceinline__ void shape_inputs(const Args& a, int64_t g, float t, AdjIn& P) {
     const int64_t n = a.n;
     float q[4];
     for (int k = 0; k < 3; ++k) {
         float ls = static_cast<float>(load_param<T>(a.log_scales, k * n + g));
-        if (DYN && a.scale_coeffs) ls = ls + cubic_in_t<T>(a, a.scale_coeffs, 3, k, g, t);
+        if (a.scale_coeffs) ls = ls + cubic_in_t<T>(a, a.scale_coeffs, 3, k, g, t);
         P.s[k] = expf(ls);
     }
     for (int k = 0; k < 4; ++k) {
         q[k] = static_cast<float>(load_param<T>(a.quats, k * n + g));
-        if (DYN && a.quat_coeffs) q[k] = q[k] + cubic_in_t<T>(a, a.quat_coeffs, 4, k, g, t);
+        if (a.quat_coeffs) q[k] = q[k] + cubic_in_t<T>(a, a.quat_coeffs, 4, k, g, t);
     }
     P.iqn = 1.0f / sqrtf(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
     for (int k = 0; k < 4; ++k) P.qh[k] = q[k] * P.iqn;
@@ -86,6 +85,12 @@ __device__ __forceinline__ void shape_inputs(const Args& a, int64_t g, float t, 
         P.Sig[4] = M[3] * M[6] + M[4] * M[7] + M[5] * M[8];
         P.Sig[5] = M[6] * M[6] + M[7] * M[7] + M[8] * M[8];
     }
+}
+
+// Without dynamics: the forward's frame-independent shape.
+__device__ __forceinline__ void static_inputs(const Args& a, int64_t g, AdjIn& P) {
+    for (int k = 0; k < 6; ++k) P.Sig[k] = static_cast<float>(a.shapes[g].Sig[k]);
+    P.o = static_cast<float>(a.shapes[g].o);
 }
 
 // Camera-space position of the mean P.mu and the projection Jacobian times the
@@ -398,8 +403,7 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
     for (int k = 0; k < 3; ++k) mu0[k] = static_cast<float>(load_param<T>(a.means, k * n + gs));
     if (CUBIC)
         for (int k = 0; k < 9; ++k) mc[k] = static_cast<float>(load_param<T>(a.mean_coeffs, k * n + gs));
-    for (int k = 0; k < 6; ++k) P.Sig[k] = static_cast<float>(a.shapes[gs].Sig[k]);
-    P.o = static_cast<float>(a.shapes[gs].o);
+    static_inputs(a, gs, P);
 
     double acc[NA], iacc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int k = 0; k < NA; ++k) acc[k] = 0.0;
@@ -545,8 +549,368 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
         for (int k = 0; k < 9; ++k) put(a.g_coeffs, k * n + g, acc[14 + k]);
 }
 
-// The adjoint with dynamics or SH.  SPLIT waves share each Gaussian: wave h of
-// a workgroup takes the h-th
+// ---------------------------------------------------------------------------
+// The adjoint with dynamics or SH, in two kernels.  One lane per (frame,
+// Gaussian) takes the chain rule down to the frame's parameter values and
+// stores them (k_adjoint_frames); one lane per Gaussian then sums them over the
+// frames in FP64 with the frames' weights (k_adjoint_sum).  In one kernel, the
+// frame's chain rule and up to 47 FP64 sums (and 45 SH sums) a lane held the
+// chip at one wave per SIMD, waiting on a Gaussian's records frame after frame:
+// on the 50-frame 960x540 clip of 200k Gaussians 2,180 us with B-spline
+// means and cubic covariance, 1,035 us so; 1,430 -> 822 us with SH of degree 3.
+// (Without either, one kernel with its 14 sums in registers is faster: 519 us
+// against 703, and 1,634 against 2,096 us on the 1080p clip.)  The stored values
+// cost 2 x 56 bytes per (frame, Gaussian); they lie in the sort's key
+// buffers, which nothing reads after the sort.  Where those are too small (less
+// than 1.75 intersections of capacity per (frame, Gaussian)) the one-kernel form
+// below runs.
+// ---------------------------------------------------------------------------
+template <bool DYN, bool SH>
+constexpr int frame_values() { return (DYN ? 14 : 13) + (DYN && SH ? 3 : 0); }
+
+struct FrameStore {
+    float *lo, *hi;     // frames [0, lo_frames) and the rest
+    int lo_frames;
+    int64_t stride;     // floats per frame
+    double* intr;       // [frame][block][4] intrinsics partials
+    int blocks;         // workgroups per frame of k_adjoint_frames
+    __device__ __forceinline__ float* frame(int f) const {
+        return f < lo_frames ? lo + f * stride : hi + (f - lo_frames) * stride;
+    }
+};
+
+// dL/dv of the view-dependent colour (see sh_adjoint) and the unit direction.
+template <typename T>
+__device__ __forceinline__ void sh_direction_adjoint(const Args& a, int64_t g, const float mu[3], const float* camC,
+                                                     const float dc[3], float d[3], float dv[3]) {
+    const int64_t n = a.n;
+    float v[3];
+    for (int i = 0; i < 3; ++i) v[i] = mu[i] - camC[i];
+    const float vn = sqrtf(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+    const float iv = vn > 0.0f ? 1.0f / vn : 0.0f;
+    for (int i = 0; i < 3; ++i) d[i] = v[i] * iv;
+    float Y[15], G[15][3];
+    sh_eval<float>(3, d[0], d[1], d[2], Y, G);
+    float dd[3] = {0.f, 0.f, 0.f};
+    // every degree, with no branch between the loads; the terms past the
+    // scene's degree repeat its last coefficients and weigh nothing
+    const int nb = sh_count(a.sh_degree);
+#pragma unroll
+    for (int k = 0; k < 15; ++k) {
+        const int kk = k < nb ? k : nb - 1;
+        float w = 0.f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            w += dc[c] * static_cast<float>(load_param<T>(a.sh, (static_cast<int64_t>(kk) * 3 + c) * n + g));
+        w = k < nb ? w : 0.0f;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) dd[j] += w * G[k][j];
+    }
+    const float dot = d[0] * dd[0] + d[1] * dd[1] + d[2] * dd[2];
+    for (int j = 0; j < 3; ++j) dv[j] = (dd[j] - d[j] * dot) * iv;
+}
+
+template <bool DYN, bool SH, typename T>
+__global__ __launch_bounds__(256) void k_adjoint_frames(Args a, FrameStore store) {
+    if (overflowed(a.status)) return;
+    // every frame of a block of Gaussians on one XCD, as in the projection
+    const int turn = static_cast<int>(blockIdx.x) / XCDS;
+    const int f = turn % a.frames, block = turn / a.frames * XCDS + static_cast<int>(blockIdx.x % XCDS);
+    if (block >= store.blocks) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t n = a.n, g = static_cast<int64_t>(block) * 256 + tid;
+    __shared__ float cam[15];  // R, t, centre
+    __shared__ float weights[4];
+    __shared__ int span;
+    __shared__ float wpose[4][12], gintr[4][256];
+    const float t = a.times ? a.times[f] : a.t0;
+    uint32_t cnt = 0u, base = 0u;
+    if (g < n) {
+        const int64_t i = static_cast<int64_t>(f) * n + g;
+        cnt = a.gcnt[i];
+        base = a.goff[i];
+        if (static_cast<int64_t>(base) + cnt > a.k_cap) cnt = 0u;  // only after an internal error
+    }
+    if (tid == 0) {
+        const CamD c = load_camera(a.poses + 7 * f);
+        for (int k = 0; k < 9; ++k) cam[k] = c.ok ? static_cast<float>(c.R[k]) : 0.0f;
+        for (int k = 0; k < 3; ++k) cam[9 + k] = c.ok ? static_cast<float>(c.t[k]) : 0.0f;
+        for (int i = 0; i < 3; ++i)
+            cam[12 + i] = c.ok ? static_cast<float>(-(c.R[0 * 3 + i] * c.t[0] + c.R[1 * 3 + i] * c.t[1] +
+                                                      c.R[2 * 3 + i] * c.t[2]))
+                               : 0.0f;
+    }
+    if (DYN && a.n_ctrl > 0 && tid == 64) {
+        float N[4];
+        span = spline_basis<float>(a.n_ctrl, fminf(fmaxf(t, 0.0f), 1.0f), N);
+        for (int r = 0; r < 4; ++r) weights[r] = N[r];
+    }
+    __syncthreads();
+    float pose[12], gi[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < 12; ++k) pose[k] = 0.0f;
+    if (cnt) {
+        PartialRound<PU> R;
+        R.load(a, base, cnt, 0u);
+        const float4 rec = *reinterpret_cast<const float4*>(&a.rec[static_cast<int64_t>(f) * n + g].a);
+        AdjIn P = {};
+        if (DYN) {
+            shape_inputs<T>(a, g, t, P);
+        } else {
+            static_inputs(a, g, P);
+        }
+        for (int k = 0; k < 3; ++k) {
+            float mu = 0.0f;
+            if (DYN && a.n_ctrl > 0) {
+                for (int r = 0; r < 4; ++r)
+                    if (weights[r] != 0.0f)
+                        mu += weights[r] * static_cast<float>(
+                                               load_param<T>(a.ctrl, (static_cast<int64_t>(span + r) * 3 + k) * n + g));
+            } else {
+                mu = static_cast<float>(load_param<T>(a.means, k * n + g));
+                if (a.mean_coeffs) mu = mu + cubic_in_t<T>(a, a.mean_coeffs, 3, k, g, t);
+            }
+            P.mu[k] = mu;
+        }
+        frame_geometry(a, cam, cam + 9, P);
+        P.A[0] = rec.x;
+        P.A[1] = rec.y;
+        P.A[2] = rec.z;
+        double s[PART] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        for (uint32_t k0 = 0;;) {
+            R.add(base, cnt, k0, s);
+            k0 += PU;
+            if (k0 >= cnt) break;
+            R.load(a, base, cnt, k0);
+        }
+        float d[PART];
+        for (int k = 0; k < PART; ++k) d[k] = static_cast<float>(s[k]);
+        float go[14];
+        projection_adjoint<!DYN>(a, cam, P, d, go, pose, gi);
+        float* out = store.frame(f) + g;
+        if (SH) {
+            const float dc[3] = {go[11], go[12], go[13]};
+            float dir[3], dv[3];
+            sh_direction_adjoint<T>(a, g, P.mu, cam + 12, dc, dir, dv);
+            for (int j = 0; j < 3; ++j) {
+                go[j] += dv[j];
+                // C = -Rc^T tc, dL/dC = -dv: dL/dtc = Rc dv, dL/dRc[j][i] = tc[j] dv[i]
+                pose[9 + j] += cam[j * 3 + 0] * dv[0] + cam[j * 3 + 1] * dv[1] + cam[j * 3 + 2] * dv[2];
+                for (int i = 0; i < 3; ++i) pose[j * 3 + i] += cam[9 + j] * dv[i];
+                if (DYN) out[(14 + j) * n] = dir[j];
+            }
+        }
+        for (int k = 0; k < (DYN ? 14 : 9); ++k) out[k * n] = go[k];
+        if (!DYN)
+            for (int k = 9; k < 13; ++k) out[k * n] = go[k + 1];
+    }
+    float v[16];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = pose[k];
+#pragma unroll
+    for (int k = 12; k < 16; ++k) v[k] = 0.0f;
+    const float x = reduce_scatter16(v, lane);
+    const int idx = reduce_scatter16_index(lane);
+    if ((lane & 3) == 0 && idx < 12) wpose[w][idx] = x;
+    for (int k = 0; k < 4; ++k) gintr[k][tid] = gi[k];
+    __syncthreads();
+    if (tid < 12) {
+        double sum = 0.0;
+        for (int ww = 0; ww < 4; ++ww) sum += static_cast<double>(wpose[ww][tid]);
+        a.pose_part[(static_cast<int64_t>(block) * a.frames + f) * 12 + tid] = sum;
+    }
+    // wave w sums intrinsics gradient w in FP64
+    double sum = 0.0;
+    for (int q = 0; q < 4; ++q) sum += static_cast<double>(gintr[w][lane + 64 * q]);
+    sum = wave_sum_f64(sum);
+    if (lane == 0) store.intr[(static_cast<int64_t>(f) * store.blocks + block) * 4 + w] = sum;
+}
+
+// Sums the stored values over the frames.
+template <bool DYN, bool SH, typename T>
+__global__ __launch_bounds__(128) void k_adjoint_sum(Args a, FrameStore store) {
+    if (overflowed(a.status)) return;
+    constexpr int NV = frame_values<DYN, SH>();
+    constexpr int FC = 64;
+    __shared__ float ft[FC], weights[FC][4], centre[FC][3];
+    __shared__ int spans[FC];
+    const int tid = threadIdx.x;
+    const int64_t n = a.n, g = static_cast<int64_t>(blockIdx.x) * 128 + tid;
+    const bool live = g < n;
+    const int64_t gs = live ? g : n - 1;
+    const bool spline = DYN && a.n_ctrl > 0;
+    const bool ctrl_out = spline && a.g_ctrl != nullptr;
+    double acc[14], win_acc[DYN ? 12 : 1], sc[DYN ? 9 : 1], qc[DYN ? 12 : 1], cubic[DYN ? 1 : 9], sh[SH ? 45 : 1];
+    for (int k = 0; k < 14; ++k) acc[k] = 0.0;
+    for (double& v : win_acc) v = 0.0;
+    for (double& v : sc) v = 0.0;
+    for (double& v : qc) v = 0.0;
+    for (double& v : cubic) v = 0.0;
+    for (double& v : sh) v = 0.0;
+    float mu0[3] = {0.f, 0.f, 0.f}, mc[9];
+    if (SH && !DYN) {
+        for (int k = 0; k < 3; ++k) mu0[k] = static_cast<float>(load_param<T>(a.means, k * n + gs));
+        for (int k = 0; k < 9; ++k)
+            mc[k] = a.mean_coeffs ? static_cast<float>(load_param<T>(a.mean_coeffs, k * n + gs)) : 0.0f;
+    }
+    // control-point window: sums of points win .. win + 3, flushed to memory
+    // (added) when a frame falls in another knot span
+    int win = -1;
+    auto flush_window = [&]() {
+        if (win < 0 || !live) return;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                a.g_ctrl[(static_cast<int64_t>(win + r) * 3 + k) * n + g] += static_cast<float>(win_acc[(3 * r + k) % (DYN ? 12 : 1)]);
+                win_acc[(3 * r + k) % (DYN ? 12 : 1)] = 0.0;
+            }
+    };
+    if (ctrl_out && live && !a.accumulate)
+        for (int64_t i = 0; i < static_cast<int64_t>(a.n_ctrl) * 3; ++i) a.g_ctrl[i * n + g] = 0.0f;
+    float nv[NV];  // the next frame's values
+    uint32_t ncnt = 0u;
+    auto fetch = [&](int f) {
+        ncnt = live ? a.gcnt[static_cast<int64_t>(f) * n + g] : 0u;
+        const float* src = store.frame(f) + gs;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) nv[k] = src[k * n];
+    };
+    fetch(0);
+#pragma unroll 1
+    for (int f0 = 0; f0 < a.frames; f0 += FC) {
+        const int nf = min(FC, a.frames - f0);
+        __syncthreads();
+        if (tid < nf) {
+            const float t = a.times ? a.times[f0 + tid] : a.t0;
+            ft[tid] = t;
+            if (spline) {
+                float N[4];
+                spans[tid] = spline_basis<float>(a.n_ctrl, fminf(fmaxf(t, 0.0f), 1.0f), N);
+                for (int r = 0; r < 4; ++r) weights[tid][r] = N[r];
+            }
+            if (SH && !DYN) {
+                const CamD c = load_camera(a.poses + 7 * (f0 + tid));
+                for (int i = 0; i < 3; ++i)
+                    centre[tid][i] = c.ok ? static_cast<float>(-(c.R[0 * 3 + i] * c.t[0] + c.R[1 * 3 + i] * c.t[1] +
+                                                                 c.R[2 * 3 + i] * c.t[2]))
+                                          : 0.0f;
+            }
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int fi = 0; fi < nf; ++fi) {
+            const uint32_t cnt = ncnt;
+            float x[NV];
+#pragma unroll
+            for (int k = 0; k < NV; ++k) x[k] = nv[k];
+            if (f0 + fi + 1 < a.frames) fetch(f0 + fi + 1);
+            if (ctrl_out) {
+                const int sp = __builtin_amdgcn_readfirstlane(spans[fi]);
+                if (sp != win) {
+                    flush_window();
+                    win = sp;
+                }
+            }
+            if (!cnt) continue;
+            const float t = ft[fi];
+            const double t1 = t, t2 = t1 * t1, t3 = t2 * t1;
+            float go[14];
+            if (DYN) {
+                for (int k = 0; k < 14; ++k) go[k] = x[k];
+            } else {
+                for (int k = 0; k < 9; ++k) go[k] = x[k];
+                go[9] = 0.0f;
+                for (int k = 9; k < 13; ++k) go[k + 1] = x[k];
+            }
+            for (int k = 0; k < 14; ++k) acc[k] += go[k];
+            if constexpr (DYN) {
+                if (ctrl_out)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) win_acc[3 * r + k] += weights[fi][r] * go[k];
+                if (a.scale_coeffs)
+                    for (int k = 0; k < 3; ++k) {
+                        sc[k] += go[3 + k] * t1;
+                        sc[3 + k] += go[3 + k] * t2;
+                        sc[6 + k] += go[3 + k] * t3;
+                    }
+                if (a.quat_coeffs)
+                    for (int k = 0; k < 4; ++k) {
+                        qc[k] += go[6 + k] * t1;
+                        qc[4 + k] += go[6 + k] * t2;
+                        qc[8 + k] += go[6 + k] * t3;
+                    }
+            } else if (a.mean_coeffs) {
+                for (int k = 0; k < 3; ++k) {
+                    cubic[k] += go[k] * t1;
+                    cubic[3 + k] += go[k] * t2;
+                    cubic[6 + k] += go[k] * t3;
+                }
+            }
+            if constexpr (SH) {
+                float d[3];
+                if constexpr (DYN) {
+                    for (int j = 0; j < 3; ++j) d[j] = x[14 + j];
+                } else {
+                    float v[3];
+                    for (int k = 0; k < 3; ++k)
+                        v[k] = mu0[k] + t * (mc[k] + t * (mc[3 + k] + t * mc[6 + k])) - centre[fi][k];
+                    const float vn = sqrtf(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+                    const float iv = vn > 0.0f ? 1.0f / vn : 0.0f;
+                    for (int j = 0; j < 3; ++j) d[j] = v[j] * iv;
+                }
+                float Y[15];
+                sh_eval<float>(3, d[0], d[1], d[2], Y, nullptr);
+                auto add = [&](auto from, auto to) {
+#pragma unroll
+                    for (int k = decltype(from)::value; k < decltype(to)::value; ++k)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) sh[3 * k + c] += Y[k] * go[11 + c];
+                };
+                add(std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
+                if (a.sh_degree >= 2) add(std::integral_constant<int, 3>{}, std::integral_constant<int, 8>{});
+                if (a.sh_degree >= 3) add(std::integral_constant<int, 8>{}, std::integral_constant<int, 15>{});
+            }
+        }
+    }
+    if (!live) return;
+    if (ctrl_out) flush_window();
+    auto put = [&](float* dst, int64_t idx, double v) {
+        if (!dst) return;
+        if (a.accumulate) dst[idx] += static_cast<float>(v);
+        else dst[idx] = static_cast<float>(v);
+    };
+    double gsq[7];
+    if (DYN) {
+        for (int k = 0; k < 7; ++k) gsq[k] = acc[3 + k];
+    } else {
+        static_shape_adjoint<T>(a, g, acc + 3, gsq);
+    }
+    for (int k = 0; k < 3; ++k) {
+        if (a.n_ctrl == 0) put(a.g_means, k * n + g, acc[k]);
+        put(a.g_log_scales, k * n + g, gsq[k]);
+        put(a.g_colors, k * n + g, acc[11 + k]);
+    }
+    for (int k = 0; k < 4; ++k) put(a.g_quats, k * n + g, gsq[3 + k]);
+    put(a.g_opacity, g, acc[10]);
+    if constexpr (DYN) {
+        if (a.scale_coeffs)
+            for (int k = 0; k < 9; ++k) put(a.g_scale_coeffs, k * n + g, sc[k]);
+        if (a.quat_coeffs)
+            for (int k = 0; k < 12; ++k) put(a.g_quat_coeffs, k * n + g, qc[k]);
+    } else if (a.mean_coeffs) {
+        for (int k = 0; k < 9; ++k) put(a.g_coeffs, k * n + g, cubic[k]);
+    }
+    if constexpr (SH) {
+#pragma unroll
+        for (int k = 0; k < 45; ++k)
+            if (k < 3 * sh_count(a.sh_degree)) put(a.g_sh, static_cast<int64_t>(k) * n + g, sh[k]);
+    }
+}
+
+// The one-kernel form of the adjoint with dynamics or SH.  SPLIT waves share
+// each Gaussian: wave h of a workgroup takes the h-th
 // contiguous part of the frames for the workgroup's 64 Gaussians, and the
 // parts' accumulators are added in a fixed order at the end.  Shorter parts
 // keep more waves in flight for this latency-bound kernel and leave a shorter
@@ -607,7 +971,7 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
     // a static Gaussian's shape (scales, rotation, 3D covariance, opacity) is
     // the same in every frame
     AdjIn Pstatic = {};
-    if (!DYN && live) shape_inputs<false, T>(a, g, 0.0f, Pstatic);
+    if (!DYN && live) static_inputs(a, g, Pstatic);
     // the next frame's count, slot offset and record are loaded one frame ahead
     uint32_t cnt_n = 0u, base_n = 0u;
     Record rec_n = {};
@@ -678,7 +1042,7 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
                 load_round(0);
                 const float t = a.times ? a.times[f] : a.t0;
                 AdjIn P = Pstatic;
-                if (DYN) shape_inputs<DYN, T>(a, g, t, P);
+                if (DYN) shape_inputs<T>(a, g, t, P);
                 frame_inputs<DYN, T>(a, g, rec, camR, camT, t, P);
                 double dd[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
                 for (uint32_t k0 = 0;;) {
@@ -859,8 +1223,11 @@ __device__ __forceinline__ void sum_parts(const double* part, int64_t stride, in
 
 // Workgroup f < pose_frames: the frame's pose gradient, its sums of dL/dRc and
 // dL/dtc mapped to the unnormalised pose quaternion and translation.  The
-// workgroup after them: the intrinsics gradient.
-__global__ __launch_bounds__(FIN_THREADS) void k_adjoint_finalize(Args a, int64_t n_blocks, int pose_frames) {
+// workgroups after them: the intrinsics gradient (one), or, with per-frame
+// partials frame_intr [frame][n_blocks][4], each frame's sum, left in the
+// frame's first partial (one per frame; k_intr_frames adds them).
+__global__ __launch_bounds__(FIN_THREADS) void k_adjoint_finalize(Args a, int64_t n_blocks, int pose_frames,
+                                                                  double* frame_intr) {
     __shared__ double red[FIN_THREADS], acc[12];
     const int f = blockIdx.x;
     if (f < pose_frames) {
@@ -876,6 +1243,10 @@ __global__ __launch_bounds__(FIN_THREADS) void k_adjoint_finalize(Args a, int64_
         const bool bad = overflowed(a.status);
         for (int k = 0; k < 4; ++k) out[k] = bad ? 0.0f : static_cast<float>(dq[k]);
         for (int k = 0; k < 3; ++k) out[4 + k] = bad ? 0.0f : static_cast<float>(acc[9 + k]);
+    } else if (frame_intr) {
+        double* part = frame_intr + static_cast<int64_t>(f - pose_frames) * n_blocks * 4;
+        sum_parts<4>(part, 4, n_blocks, red, acc);
+        if (threadIdx.x < 4) part[threadIdx.x] = acc[threadIdx.x];
     } else {
         sum_parts<4>(a.intr_part, 4, n_blocks, red, acc);
         if (threadIdx.x >= 4) return;
@@ -883,6 +1254,15 @@ __global__ __launch_bounds__(FIN_THREADS) void k_adjoint_finalize(Args a, int64_
         if (a.accumulate) a.g_intr[threadIdx.x] += g;
         else a.g_intr[threadIdx.x] = g;
     }
+}
+
+__global__ __launch_bounds__(64) void k_intr_frames(Args a, int64_t n_blocks, const double* frame_intr) {
+    if (threadIdx.x >= 4) return;
+    double v = 0.0;
+    for (int f = 0; f < a.frames; ++f) v += frame_intr[static_cast<int64_t>(f) * n_blocks * 4 + threadIdx.x];
+    const float g = overflowed(a.status) ? 0.0f : static_cast<float>(v);
+    if (a.accumulate) a.g_intr[threadIdx.x] += g;
+    else a.g_intr[threadIdx.x] = g;
 }
 
 // Gaussians per workgroup of each variant.
@@ -916,27 +1296,66 @@ static void launch_static(const Args& a, dim3 grid, hipStream_t stream) {
     }
 }
 
+// The two-kernel form of the adjoint with dynamics or SH, if the store fits in
+// the sort's key buffers and the intrinsics partials behind the pose partials;
+// false if not.  The projection's workspace holds 12 doubles per frame and 64
+// Gaussians for the pose partials, of which this form's 256 take a quarter.
 template <bool DYN, bool SH, typename T>
-static void launch_adjoint(const Args& a, dim3 grid, hipStream_t stream) {
-    hipLaunchKernelGGL((k_project_bwd<DYN, SH, T>), grid, dim3(pb_threads<DYN, SH>()), 0, stream, a);
+static bool launch_two_kernels(const Args& a, FrameStore& store, hipStream_t stream) {
+    constexpr int64_t NV = frame_values<DYN, SH>();
+    const int64_t blocks = (a.n + 255) / 256;
+    store.stride = (NV * a.n + 63) / 64 * 64;
+    const int64_t fit = static_cast<int64_t>(sizeof(KeySlot)) * a.k_cap / 4 / store.stride;
+    if (2 * fit < a.frames || blocks * 16 > project_bwd_blocks(a.n) * 12) return false;
+    store.lo = reinterpret_cast<float*>(a.kv);
+    store.hi = reinterpret_cast<float*>(a.tkv);
+    store.lo_frames = static_cast<int>(fit < a.frames ? fit : a.frames);
+    store.blocks = static_cast<int>(blocks);
+    store.intr = a.pose_part + blocks * a.frames * 12;
+    const dim3 grid(static_cast<uint32_t>((blocks + XCDS - 1) / XCDS * XCDS * a.frames));
+    hipLaunchKernelGGL((k_adjoint_frames<DYN, SH, T>), grid, dim3(256), 0, stream, a, store);
+    hipLaunchKernelGGL((k_adjoint_sum<DYN, SH, T>), dim3(static_cast<uint32_t>((a.n + 127) / 128)), dim3(128), 0, stream,
+                       a, store);
+    return true;
+}
+
+template <bool DYN, bool SH, typename T>
+static void launch_adjoint(const Args& a, int64_t& nb, double*& frame_intr, hipStream_t stream) {
+    FrameStore store;
+    if (launch_two_kernels<DYN, SH, T>(a, store, stream)) {
+        nb = store.blocks;
+        frame_intr = store.intr;
+        return;
+    }
+    nb = blocks_for(a.n, DYN, SH);
+    hipLaunchKernelGGL((k_project_bwd<DYN, SH, T>), dim3(static_cast<uint32_t>(nb)), dim3(pb_threads<DYN, SH>()), 0,
+                       stream, a);
+}
+
+template <typename T>
+static void launch_adjoint_as(const Args& a, int64_t& nb, double*& frame_intr, hipStream_t stream) {
+    const bool dyn = a.n_ctrl > 0 || a.scale_coeffs || a.quat_coeffs, sh = a.sh_degree > 0;
+    if (dyn && sh) launch_adjoint<true, true, T>(a, nb, frame_intr, stream);
+    else if (dyn) launch_adjoint<true, false, T>(a, nb, frame_intr, stream);
+    else if (sh) launch_adjoint<false, true, T>(a, nb, frame_intr, stream);
+    else {
+        nb = blocks_for(a.n, false, false);
+        launch_static<T>(a, dim3(static_cast<uint32_t>(nb)), stream);
+    }
 }
 
 hipError_t launch_project_bwd(const Args& a, hipStream_t stream) {
-    const bool dyn = a.n_ctrl > 0 || a.scale_coeffs || a.quat_coeffs;
-    const bool sh = a.sh_degree > 0;
-    const int64_t nb = blocks_for(a.n, dyn, sh);
-    const dim3 grid(static_cast<uint32_t>(nb > 0 ? nb : 1));
-    if (nb > 0) {
-        const bool bf16 = a.dtype == GV_BF16;
-        if (dyn && sh) bf16 ? launch_adjoint<true, true, uint16_t>(a, grid, stream) : launch_adjoint<true, true, float>(a, grid, stream);
-        else if (dyn) bf16 ? launch_adjoint<true, false, uint16_t>(a, grid, stream) : launch_adjoint<true, false, float>(a, grid, stream);
-        else if (sh) bf16 ? launch_adjoint<false, true, uint16_t>(a, grid, stream) : launch_adjoint<false, true, float>(a, grid, stream);
-        else bf16 ? launch_static<uint16_t>(a, grid, stream) : launch_static<float>(a, grid, stream);
+    int64_t nb = 0;
+    double* frame_intr = nullptr;
+    if (a.n > 0) {
+        if (a.dtype == GV_BF16) launch_adjoint_as<uint16_t>(a, nb, frame_intr, stream);
+        else launch_adjoint_as<float>(a, nb, frame_intr, stream);
     }
-    const int pose_frames = a.g_poses ? a.frames : 0, intr = a.g_intr ? 1 : 0;
+    const int pose_frames = a.g_poses ? a.frames : 0, intr = !a.g_intr ? 0 : frame_intr ? a.frames : 1;
     if (pose_frames + intr > 0)
         hipLaunchKernelGGL(k_adjoint_finalize, dim3(static_cast<uint32_t>(pose_frames + intr)), dim3(FIN_THREADS), 0,
-                           stream, a, nb, pose_frames);
+                           stream, a, nb, pose_frames, a.g_intr ? frame_intr : nullptr);
+    if (a.g_intr && frame_intr) hipLaunchKernelGGL(k_intr_frames, dim3(1), dim3(64), 0, stream, a, nb, frame_intr);
     return hipGetLastError();
 }
 

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import gv_synth
 from oracle import pyramid as pyr_ref
 from parity_util import device_inputs, workspace_for
 from test_gpu_parity import check_clip_against_oracle, small_workload
@@ -105,3 +106,38 @@ def test_adjoint_parts_of_the_frames(frames, n):
     more tiles per Gaussian than a round of partial records holds."""
     w = small_workload(90 + n, 96, 80, n, frames, trajectory=True, z=(2.0, 6.0), ls=(-1.9, 0.4))
     check_clip_against_oracle(w, f"adjoint parts F={frames} n={n}")
+
+
+@pytest.mark.parametrize("n_ctrl,poly_cov,sh", [(6, True, 0), (0, False, 2), (5, True, 3), (0, True, 1)])
+@pytest.mark.parametrize("n,frames", [(64, 2), (65, 1), (257, 3), (700, 67)])
+def test_adjoint_of_dynamics_and_sh_in_one_and_two_kernels(n_ctrl, poly_cov, sh, n, frames):
+    """With room in the sort's buffers the adjoint runs as two kernels, with
+    little (three quarters of the Gaussians off screen, a tight capacity) as one:
+    the same gradients.  They differ in FP32 sums over at most 67 frames in the
+    one-kernel form's SH sums (FP64 in the other): 67 roundings of 2^-24."""
+    rng = np.random.default_rng(60 + n)
+    scene_np = gv_synth.make_scene(rng, n, z=(2.0, 8.0), log_scale=(-4.2, 0.3), n_ctrl=n_ctrl, poly_cov=poly_cov,
+                                   sh_degree=sh)
+    away = 3 * n // 4
+    scene_np.means[0, :away] += 40.0
+    if n_ctrl:
+        scene_np.ctrl[:, 0, :away] += 40.0
+    cam_np = gv_synth.make_camera(64, 48, 64.0)
+    w = dict(scene=scene_np, camera=cam_np, poses=gv_synth.make_trajectory(rng, frames),
+             times=gv_synth.make_times(frames), frames=frames, n=n)
+    scene, cam, poses, times = device_inputs(w)
+    dl = torch.from_numpy(rng.normal(0, 1, (frames, 3, 48, 64)).astype(np.float32)).cuda()
+    wide = raster.Workspace(cam, n, frames, 4 * frames * n + 4096)
+    a = raster.render_batch(scene, cam, poses, times, wide, dL_dimages=dl)
+    torch.cuda.synchronize()
+    k = wide.status()["intersections"]
+    assert 0 < k < 1.5 * frames * n
+    tight = raster.Workspace(cam, n, frames, k)
+    b = raster.render_batch(scene, cam, poses, times, tight, dL_dimages=dl)
+    torch.cuda.synchronize()
+    assert tight.status()["overflow"] == 0 and torch.equal(a["images"], b["images"])
+    tol = 67 * 2.0 ** -24
+    assert torch.linalg.norm(a["dL_dposes"] - b["dL_dposes"]) <= tol * torch.linalg.norm(a["dL_dposes"])
+    for name, g in a["grads"].items():
+        if g is not None:
+            assert torch.linalg.norm(g - b["grads"][name]) <= tol * torch.linalg.norm(g), name
