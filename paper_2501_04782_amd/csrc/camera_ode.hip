@@ -1,17 +1,31 @@
 // Camera-motion Neural ODE (Eq. 1, Sec. 3.4): fused MLP + RK4 forward and its
-// discrete adjoint, each in one single-wave workgroup.
+// discrete adjoint, each in one workgroup of four waves.
 //
 // The integration is a serial chain of (F-1) * S * 4 evaluations of the
-// 8 -> 64 -> 64 -> 7 tanh MLP, so latency, not throughput, is what matters:
-// lane j owns hidden unit j and keeps its weights in VGPRs (row j of W1 and W2,
-// column j of W3, and for the adjoint also column j of W2); the hidden layer
-// is exchanged through LDS (broadcast reads) and the 7 outputs are summed over
-// the lanes by one reduce-scatter.  The state z is carried in FP64, the MLP runs in FP32.
-// The forward pass records every evaluation's input and both hidden
-// activations so that the adjoint needs no recomputation; the adjoint's
-// serial chain records each evaluation's cotangents, and the parameter
-// gradient (outer products summed over the evaluations) is formed from those
-// records by parallel kernels afterwards.
+// 8 -> 64 -> 64 -> 7 tanh MLP, so latency, not throughput, is what matters: the
+// instructions on the chain, the exchanges between lanes and nothing else.
+//  - The hidden-to-hidden product is the longest link.  Every wave computes the
+//    whole first hidden layer itself, lane u unit u, so each 16-lane row holds
+//    16 of its values; lane (row c, l) of wave w then sums the terms of row c
+//    for unit 16 w + l, reading them as row broadcasts of the DPP operand (no
+//    LDS, no barrier), and two row swaps add the four rows.  So the product's
+//    4,096 terms are 16 instructions on each of a CU's four SIMDs.
+//  - The 7 outputs: row c of a wave sums its wave's 16 units for outputs 2 c
+//    and 2 c + 1; the four waves' sums meet in LDS, the one exchange (one
+//    barrier) of an evaluation.
+//  - The state needs no exchange: the 8 lanes of output i hold component i of
+//    the state in every wave, and the RK4 arithmetic is done for one component
+//    per lane.  The next input goes to all lanes as scalars (readlane).
+//  - Nothing else is on the chain: poses are written from the recorded states
+//    afterwards, the adjoint's pose cotangents are formed before it starts, and
+//    the next evaluation's recorded activations are requested one ahead.
+// The state z is carried in FP64, the MLP runs in FP32.  The forward pass
+// records every evaluation's input and both hidden activations so that the
+// adjoint needs no recomputation; the adjoint's chain records each
+// evaluation's cotangents, and the parameter gradient (outer products summed
+// over the evaluations) is formed from those records by parallel kernels.
+// 100 frames, 4 substeps (1,584 evaluations): forward 885 us in one wave, 478 us
+// so; adjoint 701 -> 477 us.
 #include "gv_internal.h"
 
 namespace gv {
@@ -46,137 +60,180 @@ OdeLayout ode_layout(int frames, int substeps) {
     return L;
 }
 
-__device__ __forceinline__ float ode_tanh(float x) { return tanhf(x); }
+constexpr int ODE_WG = 256;
 
-// Sum of 8 values over the 64 lanes at once: cross-half and cross-row swaps,
-// then DPP within rows; afterwards lanes 8 i .. 8 i + 7 hold the wave total of
-// value i.  The order of the additions is fixed.
-__device__ __forceinline__ float reduce_scatter8(float (&v)[8], int lane) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 4]), false, false);
-        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 2]), false, false);
-        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
+// tanh, to about 2 ulp: an odd polynomial (a weighted least-squares fit of
+// (tanh x / x - 1) / x^2 on [0, 0.55], relative error 1e-9) for small |x|, else
+// 1 - 2 / (1 + e^2|x|) by the hardware's exp2 and reciprocal.  Both are computed
+// and one selected: a third of the instructions of the library's branching
+// form, which was a quarter of an evaluation.
+__device__ __forceinline__ float ode_tanh(float x) {
+    const float a = fabsf(x), u = x * x;
+    float q = -6.274235900e-03f;
+    q = __builtin_fmaf(q, u, 2.107167616e-02f);
+    q = __builtin_fmaf(q, u, -5.385230854e-02f);
+    q = __builtin_fmaf(q, u, 1.333258599e-01f);
+    q = __builtin_fmaf(q, u, -3.333331645e-01f);
+    float small = __builtin_fmaf(x * u, q, x);
+    const float e = __builtin_amdgcn_exp2f(a * 2.8853900817779268f);  // e^(2a)
+    float large = __builtin_fmaf(-2.0f, __builtin_amdgcn_rcpf(e + 1.0f), 1.0f);
+    asm volatile("" : "+v"(small), "+v"(large));  // both, and a select: a branch costs more than either
+    return a < 0.55f ? small : copysignf(large, x);
+}
+
+// acc + sum over k of w[k] times lane k of the 16-lane row, in order: 16 FMAs
+// whose first operand is a row broadcast.  Written out because the compiler
+// keeps the broadcast a move of its own, with a wait between the two: 48 issue
+// slots instead of 16.  (The leading wait covers a value written just before.)
+__device__ __forceinline__ float row_dot(const float (&w)[16], float x, float acc) {
+    asm("s_nop 1\n"
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %10 row_newbcast:8 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %12 row_newbcast:10 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %13 row_newbcast:11 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %14 row_newbcast:12 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f32_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf\n"
+        "s_nop 1"
+        : "+v"(acc)
+        : "v"(x), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]),
+          "v"(w[9]), "v"(w[10]), "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
+    return acc;
+}
+
+// Sum over the wave's four rows, in every one of them (each addition pairs the
+// same two values in both: equal bits).
+__device__ __forceinline__ float rows_sum(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sums over the 16 lanes of each row of two values: lanes 0-7 get the first's,
+// lanes 8-15 the second's.
+__device__ __forceinline__ float row_sum2(float v0, float v1, int lane) {
     const bool b3 = lane & 8;
-    const float keep = b3 ? v[1] : v[0], send = b3 ? v[0] : v[1];
+    const float keep = b3 ? v1 : v0, send = b3 ? v0 : v1;
     float x = keep + dpp_f(send, 0x128);
-    x = x + dpp_f(x, 0x141);
-    x = x + dpp_f(x, 0x4E);
+    x += dpp_f(x, 0x141);
+    x += dpp_f(x, 0x4E);
     return x + dpp_f(x, 0xB1);
 }
 
-// Copy a 64-float LDS row into registers: every read is issued, then a
-// scheduling barrier keeps the arithmetic that uses them after the reads.
-__device__ __forceinline__ void lds_row(const float* row, float (&r)[ODE_H]) {
-    const float4* q = reinterpret_cast<const float4*>(row);
-#pragma unroll
-    for (int k = 0; k < ODE_H / 4; ++k) {
-        const float4 v = q[k];
-        r[4 * k] = v.x;
-        r[4 * k + 1] = v.y;
-        r[4 * k + 2] = v.z;
-        r[4 * k + 3] = v.w;
+// Who does what: lane (= the unit whose first-layer value it forms), row c, the
+// unit whose second-layer terms of row c it sums, output (or state component) i.
+struct OdeLane {
+    uint32_t w, lane, c, unit, i;
+    __device__ OdeLane() {
+        lane = threadIdx.x & 63;
+        w = threadIdx.x >> 6;
+        c = lane >> 4;
+        unit = 16 * w + (lane & 15);
+        i = lane >> 3;
     }
+};
+
+// The four waves' sums of component i, exchanged through one of two buffers in
+// turn (a wave writes a buffer again only after a barrier that every wave
+// reached with its reads of it done).
+struct OdeExchange {
+    float4 part[2][8];
+    __device__ __forceinline__ float sum(int& turn, const OdeLane& L, float x) {
+        reinterpret_cast<float*>(&part[turn][L.i])[L.w] = x;  // the component's lanes hold the same value
+        __syncthreads();
+        const float4 v = part[turn][L.i];
+        turn ^= 1;
+        return (v.x + v.y) + (v.z + v.w);
+    }
+};
+
+// The N components of a value held by lanes 0, 8, 16, ..., as scalars.  All are
+// read before the first use: read one at a time, each waits out the hazard
+// between the lane read and its use.
+template <int N>
+__device__ __forceinline__ void components(float v, float (&s)[N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) s[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 8 * k));
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// One MLP evaluation at (y, t); lanes hold hidden unit j = lane.  Returns the
-// 7 outputs (uniform).  If rec != nullptr, stores x, h1, h2 there.
-__device__ __forceinline__ void mlp_eval(const double y[ODE_S], double t, const float w1[8], float b1,
-                                         const float w2[ODE_H], float b2, const float w3[ODE_S],
-                                         const float* b3, float* h1s, float* rec, float out[ODE_S]) {
-    const int j = threadIdx.x;
-    float x[8];
-    for (int k = 0; k < ODE_S; ++k) x[k] = static_cast<float>(y[k]);
-    x[7] = static_cast<float>(t);
-    float a1 = b1;
-    for (int k = 0; k < 8; ++k) a1 = __builtin_fmaf(w1[k], x[k], a1);
-    const float h1 = ode_tanh(a1);
-    h1s[j] = h1;
-    __syncthreads();
-    // the single wave cannot hide LDS latency behind other waves: all of the
-    // hidden layer's reads are issued before the first product
-    float hv[ODE_H];
-    lds_row(h1s, hv);
-    float a2 = b2;
-    for (int k = 0; k < ODE_H; ++k) a2 = __builtin_fmaf(w2[k], hv[k], a2);
-    const float h2 = ode_tanh(a2);
-    float v[8];
-    for (int i = 0; i < ODE_S; ++i) v[i] = w3[i] * h2;
-    v[7] = 0.0f;
-    const float sum = reduce_scatter8(v, j);
-    for (int i = 0; i < ODE_S; ++i) out[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum), 8 * i)) + b3[i];
-    if (rec) {
-        if (j == 0) {  // x is uniform: one lane writes it (records are 16-byte aligned)
-            reinterpret_cast<float4*>(rec)[0] = make_float4(x[0], x[1], x[2], x[3]);
-            reinterpret_cast<float4*>(rec)[1] = make_float4(x[4], x[5], x[6], x[7]);
-        }
-        rec[8 + j] = h1;
-        rec[8 + ODE_H + j] = h2;
-    }
-    __syncthreads();
-}
-
-__device__ __forceinline__ void write_pose(const double z[ODE_S], float* pose) {
-    if (threadIdx.x != 0) return;
+__device__ __forceinline__ void write_pose(const double* z, float* pose) {
     const double n = sqrt(z[0] * z[0] + z[1] * z[1] + z[2] * z[2] + z[3] * z[3]);
     for (int k = 0; k < 4; ++k) pose[k] = static_cast<float>(z[k] / n);
     for (int k = 4; k < ODE_S; ++k) pose[k] = static_cast<float>(z[k]);
 }
 
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_ode_fwd(const float* __restrict__ theta, const float* __restrict__ z0,
-                                                int frames, int substeps, float* __restrict__ poses,
-                                                float* __restrict__ acts, double* __restrict__ zf) {
-    const int j = threadIdx.x;
-    __shared__ __align__(16) float h1s[ODE_H];
-    float w1[8], w2[ODE_H], w3[ODE_S], b3[ODE_S];
-    for (int k = 0; k < 8; ++k) w1[k] = theta[OFF_W1 + j * 8 + k];
-    const float b1 = theta[OFF_B1 + j];
-    for (int k = 0; k < ODE_H; ++k) w2[k] = theta[OFF_W2 + j * ODE_H + k];
-    const float b2 = theta[OFF_B2 + j];
-    for (int i = 0; i < ODE_S; ++i) w3[i] = theta[OFF_W3 + i * ODE_H + j];
-    for (int i = 0; i < ODE_S; ++i) b3[i] = theta[OFF_B3 + i];
-    double z[ODE_S];
-    for (int k = 0; k < ODE_S; ++k) z[k] = z0[k];
-    write_pose(z, poses);
-    if (j < ODE_S) zf[j] = z[j];
-    if (frames < 2) return;
-    const double h = 1.0 / (static_cast<double>(substeps) * (frames - 1));
-    int e = 0;
+__global__ __launch_bounds__(ODE_WG) void k_ode_fwd(const float* __restrict__ theta, const float* __restrict__ z0,
+                                                    int frames, int substeps, float* __restrict__ poses,
+                                                    float* __restrict__ acts, double* zf) {
+    const OdeLane L;
+    __shared__ OdeExchange X;
+    float w1[8], w2[16];
+    for (int k = 0; k < 8; ++k) w1[k] = theta[OFF_W1 + L.lane * 8 + k];
+    const float b1 = theta[OFF_B1 + L.lane];
+    for (int k = 0; k < 16; ++k) w2[k] = theta[OFF_W2 + L.unit * ODE_H + 16 * L.c + k];
+    const float b2 = L.c == 0 ? theta[OFF_B2 + L.unit] : 0.0f;
+    const float w3a = theta[OFF_W3 + 2 * L.c * ODE_H + L.unit];
+    const float w3b = 2 * L.c + 1 < ODE_S ? theta[OFF_W3 + (2 * L.c + 1) * ODE_H + L.unit] : 0.0f;
+    const float b3 = L.i < ODE_S ? theta[OFF_B3 + L.i] : 0.0f;
+    // component 7 of the input is the time: its "state" is set at every step
+    // and its slope is 1
+    const bool time = L.i == ODE_S;
+    double z = L.i < ODE_S ? z0[L.i] : 0.0;
+    const bool writer = L.w == 0 && (L.lane & 7) == 0 && !time;  // one lane per component
+    if (writer) zf[L.i] = z;
+    const double h = frames > 1 ? 1.0 / (static_cast<double>(substeps) * (frames - 1)) : 0.0;
+    float* rec = acts;
+    int turn = 0;
+    auto eval = [&](double y) {
+        const float x = static_cast<float>(y);
+        float xs[8];
+        components(x, xs);
+        float a1 = b1;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a1 = __builtin_fmaf(w1[k], xs[k], a1);
+        const float h1 = ode_tanh(a1);
+        const float h2 = ode_tanh(rows_sum(row_dot(w2, h1, b2)));
+        const float o = X.sum(turn, L, row_sum2(w3a * h2, w3b * h2, L.lane)) + b3;
+        // the record, without branches: lanes that hold the same value write it
+        // to the same place
+        rec[static_cast<uint32_t>(L.i)] = x;
+        rec[8u + L.lane] = h1;
+        rec[8u + ODE_H + L.unit] = h2;
+        rec += ODE_REC;
+        return time ? 1.0f : o;
+    };
     for (int f = 1; f < frames; ++f) {
         for (int s = 0; s < substeps; ++s) {
-            const double t = (static_cast<double>(f - 1) * substeps + s) * h;
-            float k1[ODE_S], k2[ODE_S], k3[ODE_S], k4[ODE_S];
-            double y[ODE_S];
-            mlp_eval(z, t, w1, b1, w2, b2, w3, b3, h1s, acts + static_cast<size_t>(e++) * ODE_REC, k1);
-            for (int k = 0; k < ODE_S; ++k) y[k] = z[k] + 0.5 * h * k1[k];
-            mlp_eval(y, t + 0.5 * h, w1, b1, w2, b2, w3, b3, h1s, acts + static_cast<size_t>(e++) * ODE_REC, k2);
-            for (int k = 0; k < ODE_S; ++k) y[k] = z[k] + 0.5 * h * k2[k];
-            mlp_eval(y, t + 0.5 * h, w1, b1, w2, b2, w3, b3, h1s, acts + static_cast<size_t>(e++) * ODE_REC, k3);
-            for (int k = 0; k < ODE_S; ++k) y[k] = z[k] + h * k3[k];
-            mlp_eval(y, t + h, w1, b1, w2, b2, w3, b3, h1s, acts + static_cast<size_t>(e++) * ODE_REC, k4);
-            for (int k = 0; k < ODE_S; ++k)
-                z[k] = z[k] + (h / 6.0) * (static_cast<double>(k1[k]) + 2.0 * k2[k] + 2.0 * k3[k] + k4[k]);
+            if (time) z = (static_cast<double>(f - 1) * substeps + s) * h;
+            const float k1 = eval(z);
+            const float k2 = eval(z + 0.5 * h * k1);
+            const float k3 = eval(z + 0.5 * h * k2);
+            const float k4 = eval(z + h * k3);
+            z = z + (h / 6.0) * (static_cast<double>(k1) + 2.0 * k2 + 2.0 * k3 + k4);
         }
-        write_pose(z, poses + ODE_S * f);
-        if (j < ODE_S) zf[ODE_S * f + j] = z[j];
+        if (writer) zf[ODE_S * f + L.i] = z;
+    }
+    __threadfence();
+    __syncthreads();
+    for (int f = threadIdx.x; f < frames; f += ODE_WG) {
+        double zk[ODE_S];
+        for (int k = 0; k < ODE_S; ++k) zk[k] = __builtin_nontemporal_load(zf + ODE_S * f + k);
+        write_pose(zk, poses + ODE_S * f);
     }
 }
 
 // Cotangent of the state from the cotangent of the pose (q/|q|, t).
-// The value lane k holds (wave-uniform result).
-__device__ __forceinline__ double lane_value(double v, int k) {
-    const uint64_t b = __double_as_longlong(v);
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(b), k);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(b >> 32), k);
-    return __longlong_as_double((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 __device__ __forceinline__ void pose_cotangent(const double* z, const float* dp, double out[ODE_S]) {
     const double n = sqrt(z[0] * z[0] + z[1] * z[1] + z[2] * z[2] + z[3] * z[3]);
     double qh[4], dot = 0.0;
@@ -188,104 +245,88 @@ __device__ __forceinline__ void pose_cotangent(const double* z, const float* dp,
     for (int k = 4; k < ODE_S; ++k) out[k] = dp[k];
 }
 
-// Vector-Jacobian product of one recorded evaluation with upstream dy: returns
-// dL/dy (state part) and records the evaluation's cotangents (da1, da2 of the
-// hidden pre-activations, dy) in adj; the parameter gradient is summed from
-// these records afterwards, off the serial chain.
-__device__ __forceinline__ void mlp_vjp(float h1, float h2, const double dy[ODE_S], const float w1[8],
-                                        const float w2c[ODE_H], const float w3[ODE_S], float* da2s, float* adj,
-                                        double gx[ODE_S]) {
-    const int j = threadIdx.x;
-    float dyf[ODE_S];
-    for (int i = 0; i < ODE_S; ++i) dyf[i] = static_cast<float>(dy[i]);
-    float dh2 = 0.0f;
-    for (int i = 0; i < ODE_S; ++i) dh2 = __builtin_fmaf(w3[i], dyf[i], dh2);
-    const float da2 = dh2 * (1.0f - h2 * h2);
-    da2s[j] = da2;
+// The adjoint's chain.  Frame f's pose cotangent (f >= 1) waits in the first
+// cotangent record of the frame's own evaluations, which are differentiated,
+// and the record written, only after it has been taken; frame 0's in LDS.
+__global__ __launch_bounds__(ODE_WG) void k_ode_bwd(const float* __restrict__ theta, int frames, int substeps,
+                                                    const float* __restrict__ dposes, const float* __restrict__ acts,
+                                                    const double* __restrict__ zf, float* adj,
+                                                    float* __restrict__ dz0) {
+    const OdeLane L;
+    __shared__ OdeExchange X;
+    __shared__ double cot0[8];
+    float w2c[16], w3[ODE_S];
+    for (int k = 0; k < ODE_S; ++k) w3[k] = theta[OFF_W3 + k * ODE_H + L.lane];
+    for (int k = 0; k < 16; ++k) w2c[k] = theta[OFF_W2 + (16 * L.c + k) * ODE_H + L.unit];
+    const float w1a = theta[OFF_W1 + L.unit * 8 + 2 * L.c];
+    const float w1b = 2 * L.c + 1 < ODE_S ? theta[OFF_W1 + L.unit * 8 + 2 * L.c + 1] : 0.0f;
+    auto cotangent = [&](int f) {
+        return reinterpret_cast<double*>(adj + static_cast<size_t>(f - 1) * substeps * 4 * ODE_ADJ);
+    };
+    for (int f = threadIdx.x; f < frames; f += ODE_WG) {
+        double c[ODE_S];
+        pose_cotangent(zf + ODE_S * f, dposes + ODE_S * f, c);
+        double* to = f > 0 ? cotangent(f) : cot0;
+        for (int k = 0; k < ODE_S; ++k) to[k] = c[k];
+    }
+    __threadfence();
     __syncthreads();
-    float dv[ODE_H];
-    lds_row(da2s, dv);
-    float dh1 = 0.0f;
-    for (int k = 0; k < ODE_H; ++k) dh1 = __builtin_fmaf(w2c[k], dv[k], dh1);
-    const float da1 = dh1 * (1.0f - h1 * h1);
-    adj[j] = da1;
-    adj[ODE_H + j] = da2;
-    if (j == 0)
-        for (int i = 0; i < ODE_S; ++i) adj[2 * ODE_H + i] = dyf[i];
-    float v[8];
-    for (int m = 0; m < ODE_S; ++m) v[m] = w1[m] * da1;
-    v[7] = 0.0f;
-    const float sum = reduce_scatter8(v, j);
-    for (int m = 0; m < ODE_S; ++m)
-        gx[m] = static_cast<double>(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum), 8 * m)));
-    __syncthreads();
-}
-
-__global__ __launch_bounds__(64) void k_ode_bwd(const float* __restrict__ theta, int frames, int substeps,
-                                                const float* __restrict__ dposes, const float* __restrict__ acts,
-                                                const double* __restrict__ zf, float* __restrict__ adj,
-                                                float* __restrict__ dz0) {
-    const int j = threadIdx.x;
-    __shared__ __align__(16) float da2s[ODE_H];
-    float w1[8], w2c[ODE_H], w3[ODE_S];
-    for (int k = 0; k < 8; ++k) w1[k] = theta[OFF_W1 + j * 8 + k];
-    for (int k = 0; k < ODE_H; ++k) w2c[k] = theta[OFF_W2 + k * ODE_H + j];
-    for (int i = 0; i < ODE_S; ++i) w3[i] = theta[OFF_W3 + i * ODE_H + j];
-
-    double lam[ODE_S];
-    pose_cotangent(zf + ODE_S * (frames - 1), dposes + ODE_S * (frames - 1), lam);
+    const bool comp = L.i < ODE_S;
+    auto take = [&](int f) {  // component i of frame f's pose cotangent
+        if (!comp) return 0.0;
+        return f > 0 ? __builtin_nontemporal_load(cotangent(f) + L.i) : cot0[L.i];
+    };
+    double lam = take(frames - 1);
     if (frames > 1) {
         const double h = 1.0 / (static_cast<double>(substeps) * (frames - 1));
         // The evaluations are taken in descending order; this lane's hidden
         // activations of the next one are requested while the current one is
-        // differentiated (one wave: nothing else hides their latency).
-        const size_t elast = static_cast<size_t>(frames - 1) * substeps * 4 - 1;
-        float nh1 = acts[elast * ODE_REC + 8 + j], nh2 = acts[elast * ODE_REC + 8 + ODE_H + j];
+        // differentiated.
+        int64_t e = static_cast<int64_t>(frames - 1) * substeps * 4 - 1;
+        float nh1 = acts[e * ODE_REC + 8 + L.unit], nh2 = acts[e * ODE_REC + 8 + ODE_H + L.lane];
+        int turn = 0;
+        __syncthreads();  // every lane has its first cotangent
+        auto vjp = [&](double dy) {
+            const float h1 = nh1, h2 = nh2;
+            const int64_t before = e > 0 ? e - 1 : 0;
+            nh1 = acts[before * ODE_REC + 8 + L.unit];
+            nh2 = acts[before * ODE_REC + 8 + ODE_H + L.lane];
+            float* out = adj + e * ODE_ADJ;
+            --e;
+            const float dyf = static_cast<float>(dy);
+            float dys[ODE_S];
+            components(dyf, dys);
+            float dh2 = 0.0f;
+#pragma unroll
+            for (int k = 0; k < ODE_S; ++k) dh2 = __builtin_fmaf(w3[k], dys[k], dh2);
+            const float da2 = dh2 * (1.0f - h2 * h2);
+            const float da1 = rows_sum(row_dot(w2c, da2, 0.0f)) * (1.0f - h1 * h1);
+            const float gx = X.sum(turn, L, row_sum2(w1a * da1, w1b * da1, L.lane));
+            out[static_cast<uint32_t>(L.unit)] = da1;
+            out[static_cast<uint32_t>(ODE_H + L.lane)] = da2;
+            out[static_cast<uint32_t>(2 * ODE_H + L.i)] = dyf;  // (the record's last word is a pad)
+            return static_cast<double>(gx);
+        };
         for (int f = frames - 1; f >= 1; --f) {
-            // frame f - 1's state and pose cotangent, needed after this
-            // frame's substeps: requested now, one component per lane (vector
-            // loads, which the LDS waits of the substeps do not wait for)
-            const double zl = j < ODE_S ? zf[ODE_S * (f - 1) + j] : 0.0;
-            const float dl = j < ODE_S ? dposes[ODE_S * (f - 1) + j] : 0.0f;
+            const double next = take(f - 1);  // needed after this frame's substeps
             for (int s = substeps - 1; s >= 0; --s) {
-                const size_t e0 = (static_cast<size_t>(f - 1) * substeps + s) * 4;
-                double dz[ODE_S], dk[4][ODE_S], gx[ODE_S];
-                for (int k = 0; k < ODE_S; ++k) {
-                    dz[k] = lam[k];
-                    dk[0][k] = (h / 6.0) * lam[k];
-                    dk[1][k] = (h / 3.0) * lam[k];
-                    dk[2][k] = (h / 3.0) * lam[k];
-                    dk[3][k] = (h / 6.0) * lam[k];
-                }
-                auto vjp = [&](size_t e, const double dy[ODE_S]) {
-                    const float h1 = nh1, h2 = nh2;
-                    if (e > 0) {
-                        nh1 = acts[(e - 1) * ODE_REC + 8 + j];
-                        nh2 = acts[(e - 1) * ODE_REC + 8 + ODE_H + j];
-                    }
-                    mlp_vjp(h1, h2, dy, w1, w2c, w3, da2s, adj + e * ODE_ADJ, gx);
-                };
-                vjp(e0 + 3, dk[3]);
-                for (int k = 0; k < ODE_S; ++k) { dz[k] += gx[k]; dk[2][k] += h * gx[k]; }
-                vjp(e0 + 2, dk[2]);
-                for (int k = 0; k < ODE_S; ++k) { dz[k] += gx[k]; dk[1][k] += 0.5 * h * gx[k]; }
-                vjp(e0 + 1, dk[1]);
-                for (int k = 0; k < ODE_S; ++k) { dz[k] += gx[k]; dk[0][k] += 0.5 * h * gx[k]; }
-                vjp(e0, dk[0]);
-                for (int k = 0; k < ODE_S; ++k) lam[k] = dz[k] + gx[k];
+                double dz = lam, dk1 = (h / 6.0) * lam, dk2 = (h / 3.0) * lam, dk3 = (h / 3.0) * lam;
+                double gx = vjp((h / 6.0) * lam);
+                dz += gx;
+                dk3 += h * gx;
+                gx = vjp(dk3);
+                dz += gx;
+                dk2 += 0.5 * h * gx;
+                gx = vjp(dk2);
+                dz += gx;
+                dk1 += 0.5 * h * gx;
+                gx = vjp(dk1);
+                lam = dz + gx;
             }
-            double zk[ODE_S], c[ODE_S];
-            float dp[ODE_S];
-            for (int k = 0; k < ODE_S; ++k) {
-                zk[k] = lane_value(zl, k);
-                dp[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dl), k));
-            }
-            pose_cotangent(zk, dp, c);
-            for (int k = 0; k < ODE_S; ++k) lam[k] += c[k];
+            lam += next;
         }
     }
-    if (j == 0)
-        for (int k = 0; k < ODE_S; ++k) dz0[k] = static_cast<float>(lam[k]);
+    if (L.w == 0 && (L.lane & 7) == 0 && comp) dz0[L.i] = static_cast<float>(lam);
 }
 
 // Parameter gradient from the recorded evaluations (x, h1, h2 in acts; da1,
@@ -320,6 +361,7 @@ __global__ __launch_bounds__(256) void k_ode_grad_final(const float* __restrict_
     const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= N_THETA) return;
     float acc = 0.0f;
+#pragma unroll 16
     for (int64_t c = 0; c < chunks; ++c) acc += part[c * N_THETA + p];
     dtheta[p] = acc;
 }
@@ -401,7 +443,7 @@ gv_status gv_camera_ode_fwd(const float* theta, const float* z0, int32_t frames,
     const OdeLayout L = ode_layout(frames, substeps);
     if (!ws || ws_bytes < L.total || (reinterpret_cast<uintptr_t>(ws) & 255u)) return GV_ERR_WORKSPACE;
     char* b = static_cast<char*>(ws);
-    hipLaunchKernelGGL(k_ode_fwd, dim3(1), dim3(64), 0, static_cast<hipStream_t>(stream), theta, z0, frames, substeps,
+    hipLaunchKernelGGL(k_ode_fwd, dim3(1), dim3(ODE_WG), 0, static_cast<hipStream_t>(stream), theta, z0, frames, substeps,
                        poses, reinterpret_cast<float*>(b + L.acts), reinterpret_cast<double*>(b + L.zf));
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? GV_OK : GV_ERR_HIP;
@@ -420,7 +462,7 @@ gv_status gv_camera_ode_bwd(const float* theta, const float* z0, int32_t frames,
     const float* acts = reinterpret_cast<const float*>(b + L.acts);
     float* adj = reinterpret_cast<float*>(b + L.adj);
     float* part = reinterpret_cast<float*>(b + L.part);
-    hipLaunchKernelGGL(k_ode_bwd, dim3(1), dim3(64), 0, st, theta, frames, substeps, dL_dposes, acts,
+    hipLaunchKernelGGL(k_ode_bwd, dim3(1), dim3(ODE_WG), 0, st, theta, frames, substeps, dL_dposes, acts,
                        reinterpret_cast<const double*>(b + L.zf), adj, dz0);
     const dim3 pg((N_THETA + 255) / 256, static_cast<uint32_t>(L.chunks));
     hipLaunchKernelGGL(k_ode_grad_part, pg, dim3(256), 0, st, acts, adj, static_cast<int64_t>(L.evals),
