@@ -141,3 +141,12 @@ def test_adjoint_of_dynamics_and_sh_in_one_and_two_kernels(n_ctrl, poly_cov, sh,
     for name, g in a["grads"].items():
         if g is not None:
             assert torch.linalg.norm(g - b["grads"][name]) <= tol * torch.linalg.norm(g), name
+
+
+@pytest.mark.parametrize("tiles_x,tiles_y", [(8, 8), (13, 5), (16, 8), (43, 3), (21, 9)])
+def test_gaussians_of_whole_grids(tiles_x, tiles_y):
+    """Rectangles of 64 tiles (a mask), 65, 128, 129 and 189 tiles (walked by a
+    wave, whole and cut chunks of 64), with tiles inside that the ellipses miss,
+    several in one wave and among smaller ones."""
+    w = small_workload(tiles_x, 16 * tiles_x, 16 * tiles_y, 90, 2, trajectory=True, z=(2.0, 3.0), ls=(-1.4, 1.0))
+    check_clip_against_oracle(w, f"whole grids {tiles_x}x{tiles_y}")
