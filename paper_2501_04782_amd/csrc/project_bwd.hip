@@ -367,6 +367,43 @@ struct PartialRound {
 };
 constexpr uint32_t PU = 4;
 
+// dL/dSig (xx xy xz yy yz zz) of one (frame, Gaussian) in FP64: from the sums s
+// of its partial records and the conic A through dL/dcov = -A G A and T^T C T.
+// In FP32 the rounding of the conic's and T's products, amplified by a needle's
+// axis ratio, was most of the quaternion gradient's error: 1.3e-6 of its norm
+// on one 960x540 frame of 100k Gaussians, 0.25e-6 so (medians of 20 scenes).
+__device__ __forceinline__ void sigma_gradient_f64(const Args& a, const double* Rc, const double* tc,
+                                                   const float mu[3], const float A[3], const double s[PART],
+                                                   double G[6]) {
+    double m[3], T[6];
+    for (int i = 0; i < 3; ++i) m[i] = tc[i] + Rc[i * 3 + 0] * mu[0] + Rc[i * 3 + 1] * mu[1] + Rc[i * 3 + 2] * mu[2];
+    const double iz = 1.0 / m[2];
+    const double j00 = a.fx * iz, j02 = -a.fx * m[0] * iz * iz;
+    const double j11 = a.fy * iz, j12 = -a.fy * m[1] * iz * iz;
+    for (int j = 0; j < 3; ++j) {
+        T[j] = j00 * Rc[0 * 3 + j] + j02 * Rc[2 * 3 + j];
+        T[3 + j] = j11 * Rc[1 * 3 + j] + j12 * Rc[2 * 3 + j];
+    }
+    const double A0 = A[0], A1 = A[1], A2 = A[2];
+    const double G00 = s[2], G01 = 0.5 * s[3], G11 = s[4];
+    const double AG00 = A0 * G00 + A1 * G01, AG01 = A0 * G01 + A1 * G11;
+    const double AG10 = A1 * G00 + A2 * G01, AG11 = A1 * G01 + A2 * G11;
+    const double C00 = -(AG00 * A0 + AG01 * A1);
+    const double C01 = -0.5 * ((AG00 * A1 + AG01 * A2) + (AG10 * A0 + AG11 * A1));
+    const double C11 = -(AG10 * A1 + AG11 * A2);
+    double CT[6];
+    for (int j = 0; j < 3; ++j) {
+        CT[j] = C00 * T[j] + C01 * T[3 + j];
+        CT[3 + j] = C01 * T[j] + C11 * T[3 + j];
+    }
+    G[0] = T[0] * CT[0] + T[3] * CT[3];
+    G[1] = T[0] * CT[1] + T[3] * CT[4];
+    G[2] = T[0] * CT[2] + T[3] * CT[5];
+    G[3] = T[1] * CT[1] + T[4] * CT[4];
+    G[4] = T[1] * CT[2] + T[4] * CT[5];
+    G[5] = T[2] * CT[2] + T[5] * CT[5];
+}
+
 // The adjoint of Gaussians without dynamics or SH: one lane per Gaussian and
 // SPLIT waves per 64 Gaussians, each taking a contiguous part of the frames
 // (quarters rather than halves shorten the last round of workgroups, which runs
@@ -387,6 +424,10 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
     if (overflowed(a.status)) return;
     constexpr int FC = 16;  // frames whose cameras and pose sums are in LDS
     constexpr int NA = CUBIC ? 23 : 14;
+    // FP64 for dL/dSig wherever the registers leave three waves per SIMD (the
+    // 1080p clip with cubic means took 1,815 us at two, 1,641 without)
+    constexpr bool SIGMA_F64 = SPLIT == 1 || !CUBIC;
+    __shared__ double camd[SIGMA_F64 ? SPLIT : 1][SIGMA_F64 ? FC : 1][12];
     __shared__ float cam[SPLIT][FC][12], wpose[SPLIT][FC][12];
     __shared__ double red[SPLIT][64];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -434,6 +475,10 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
             const int ff = hh * fpart + c0 + fi;
             if (ff < min((hh + 1) * fpart, a.frames)) {
                 const CamD c = load_camera(a.poses + 7 * ff);
+                if (SIGMA_F64) {
+                    for (int k = 0; k < 9; ++k) camd[hh][fi][k] = c.ok ? c.R[k] : 0.0;
+                    for (int k = 0; k < 3; ++k) camd[hh][fi][9 + k] = c.ok ? c.t[k] : 0.0;
+                }
                 for (int k = 0; k < 9; ++k) cam[hh][fi][k] = c.ok ? static_cast<float>(c.R[k]) : 0.0f;
                 for (int k = 0; k < 3; ++k) cam[hh][fi][9 + k] = c.ok ? static_cast<float>(c.t[k]) : 0.0f;
             }
@@ -475,6 +520,14 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
                 float go[14], gi[4];
                 projection_adjoint<true>(a, camR, P, d, go, pose, gi);
                 for (int k = 0; k < 4; ++k) iacc[k] += gi[k];
+                if (SIGMA_F64) {
+                    double G[6];
+                    sigma_gradient_f64(a, camd[h][fi], camd[h][fi] + 9, P.mu, P.A, s, G);
+                    for (int k = 0; k < 6; ++k) {
+                        acc[3 + k] += G[k];
+                        go[3 + k] = 0.0f;
+                    }
+                }
                 for (int k = 0; k < 14; ++k) acc[k] += go[k];
                 if (CUBIC) {
                     const double t1 = t, t2 = t1 * t1, t3 = t2 * t1;
