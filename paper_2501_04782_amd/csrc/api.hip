@@ -211,6 +211,7 @@ static gv_status make_args(const gv_scene* s, const gv_camera* c, int frames, co
     a.tcur = reinterpret_cast<uint32_t*>(b + L.tcur);
     a.bhist = L.bin_blocks > 0 ? reinterpret_cast<uint32_t*>(b + L.bhist) : nullptr;
     a.bin_blocks = static_cast<int>(L.bin_blocks);
+    a.bin_rounds = BIN_GROUP / 256;
     a.tfin = reinterpret_cast<float*>(b + L.tfin);
     a.nlast = reinterpret_cast<uint32_t*>(b + L.nlast);
     a.loss_part = reinterpret_cast<float*>(b + L.loss_part);
@@ -224,6 +225,21 @@ static gv_status make_args(const gv_scene* s, const gv_camera* c, int frames, co
     a.pused = reinterpret_cast<uint32_t*>(b + L.pused);
     a.tkv = reinterpret_cast<KeySlot*>(b + L.tkv);
     a.k_cap = L.k_cap;
+    // Binning workgroups of 256 Gaussians where those of BIN_GROUP would leave
+    // CUs idle, if their histograms (four times as many) fit in the sort's merge
+    // scratch, which nothing uses before the sort.  Projection and scatter with
+    // the larger and the smaller ones, by number of the larger: 2 (2k Gaussians,
+    // 64 tiles) 26 + 12 against 15 + 8 us, 20 (20k, 300 tiles) 26 + 12 against
+    // 16 + 9, 98 (100k, 2,040 tiles) 39 + 21 against 28 + 20; 392 (four such frames)
+    // 43 + 52 against 58 + 59, as every workgroup stores a count for every tile.
+    constexpr int64_t BIN_FEW = 128;
+    const int64_t fine = (s->n + 255) / 256;
+    if (L.bin_blocks > 0 && L.bin_blocks * frames < BIN_FEW &&
+        4 * fine * frames * L.tiles <= static_cast<int64_t>(sizeof(KeySlot)) * L.k_cap) {
+        a.bhist = reinterpret_cast<uint32_t*>(a.tkv);
+        a.bin_blocks = static_cast<int>(fine);
+        a.bin_rounds = 1;
+    }
     a.tune = current_tuning();
     return GV_OK;
 }

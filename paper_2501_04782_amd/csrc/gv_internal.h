@@ -30,8 +30,8 @@ constexpr float K_EXP = -0.72134752044448170368f;
 constexpr double BIN_Q_SLACK = 9.0 * (1.0 + 1e-5) + 1e-6;
 constexpr float SUB_Q_SLACK = 9.0f * (1.0f + 1e-4f) + 1e-4f;
 
-// Gaussians per workgroup of the LDS-histogram binning kernels, and the
-// largest tile grid whose histogram fits in LDS (64 KiB).
+// Gaussians per workgroup of the LDS-histogram binning kernels (small launches
+// take 256), and the largest tile grid whose histogram fits in LDS (64 KiB).
 constexpr int XCDS = 8;  // dies with an L2 each; workgroups are dealt to them in turn
 constexpr int BIN_GROUP = 1024;
 constexpr int LDS_TILE_LIMIT = 16384;
@@ -153,6 +153,7 @@ struct Args {
     uint32_t* tcur;       // [F*T]
     uint32_t* bhist;      // [F][bin_blocks][T] workgroup tile histograms, or nullptr (global-atomic binning)
     int bin_blocks;
+    int bin_rounds;       // Gaussians per binning workgroup / 256
     float* tfin;          // [F][P]
     uint32_t* nlast;      // [F][P]
     float* loss_part;     // [F*T]

@@ -242,9 +242,9 @@ struct WaveCells {
 };
 
 // Binning with workgroup-local tile histograms in LDS: each workgroup
-// projects BIN_GROUP Gaussians of one frame, counts their intersections per
-// tile with LDS atomics (16-bit counts, two tiles per word: a count never
-// exceeds BIN_GROUP), stores its histogram and adds it to the frame's tile
+// projects a.bin_rounds x 256 Gaussians of one frame, counts their
+// intersections per tile with LDS atomics (16-bit counts, two tiles per word: a
+// count never exceeds BIN_GROUP), stores its histogram and adds it to the frame's tile
 // counts with one global atomic per non-empty tile.  The workgroup's pre-sort
 // slots are one contiguous range taken with a single atomic and dealt out in
 // order of the Gaussians; where the range lies does not matter to any result,
@@ -265,7 +265,7 @@ template <bool DYN, bool SH, typename T>
 __global__ __launch_bounds__(256) void k_project_lds(Args a) {
     extern __shared__ uint32_t hist[];
     __shared__ WaveCells wc[4];
-    constexpr int ROUNDS = BIN_GROUP / 256;
+    constexpr int ROUNDS = BIN_GROUP / 256;  // at most; a small launch takes one
     __shared__ uint16_t counts[ROUNDS][256];  // a Gaussian meets at most LDS_TILE_LIMIT tiles
     __shared__ uint32_t wtotal[ROUNDS][4];
     __shared__ uint32_t slot0;
@@ -283,10 +283,10 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
     __shared__ SplineD basis;
     if (DYN && a.n_ctrl > 0 && threadIdx.x == 0) basis = spline_at(a.n_ctrl, tt);
     __syncthreads();
-    const int64_t g0 = static_cast<int64_t>(block) * BIN_GROUP;
+    const int64_t g0 = static_cast<int64_t>(block) * a.bin_rounds * 256;
     WaveCells& W = wc[w];
 #pragma unroll 1
-    for (int k = 0; k < ROUNDS; ++k) {
+    for (int k = 0; k < a.bin_rounds; ++k) {
         const int64_t g = g0 + k * 256 + threadIdx.x;
         BinShape S;
         const bool has = g < a.n && project_one<DYN, SH, T>(a, f, g, cam, tt, basis, S);
@@ -325,9 +325,10 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
         __builtin_amdgcn_wave_barrier();
     }
     // the workgroup's slots, in order of the Gaussians
-    uint32_t before[ROUNDS];
+    uint32_t before[ROUNDS] = {};
 #pragma unroll
     for (int k = 0; k < ROUNDS; ++k) {
+        if (k >= a.bin_rounds) break;
         uint32_t total;
         before[k] = wave_exclusive_scan(counts[k][threadIdx.x], lane, total);
         if (lane == 0) wtotal[k][w] = total;
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t run = 0;
-        for (int k = 0; k < ROUNDS * 4; ++k) {
+        for (int k = 0; k < a.bin_rounds * 4; ++k) {
             const uint32_t v = wtotal[k >> 2][k & 3];
             wtotal[k >> 2][k & 3] = run;
             run += v;
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
 #pragma unroll
     for (int k = 0; k < ROUNDS; ++k) {
         const int64_t g = g0 + k * 256 + threadIdx.x;
-        if (g < a.n) a.goff[static_cast<int64_t>(f) * a.n + g] = slot0 + wtotal[k][w] + before[k];
+        if (k < a.bin_rounds && g < a.n) a.goff[static_cast<int64_t>(f) * a.n + g] = slot0 + wtotal[k][w] + before[k];
     }
 }
 
@@ -461,7 +462,7 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
     // if the counts disagreed, which the reservation above reports)
     auto next = [&](int tl) { return atomicAdd(&base[tl], 1u); };
     auto end = [&](int) { return static_cast<uint32_t>(a.k_cap); };
-    const int64_t g0 = static_cast<int64_t>(blockIdx.x) * BIN_GROUP;
+    const int64_t g0 = static_cast<int64_t>(blockIdx.x) * a.bin_rounds * 256;
     WaveKeys& W = wk[w];
     // A Gaussian's count, depth, rectangle, mask and slot offset, requested
     // together (one memory round trip; a Gaussian without intersections
@@ -488,10 +489,10 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
     static_assert(BIN_GROUP / 256 <= 32, "one bit per round");
     uint32_t big = 0u;  // rounds whose Gaussian has no mask, scattered after the loop
 #pragma unroll 1
-    for (int k = 0; k < BIN_GROUP / 256; ++k) {
+    for (int k = 0; k < a.bin_rounds; ++k) {
         const int64_t g = g0 + k * 256 + threadIdx.x;
         const In cur = nxt;
-        if (k + 1 < BIN_GROUP / 256) load_in(k + 1, nxt);
+        if (k + 1 < a.bin_rounds) load_in(k + 1, nxt);
         const uint32_t cnt = cur.cnt;
         const uint2 rc = cur.rc;
         const uint64_t tm = cur.tm;
@@ -535,7 +536,7 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
     // 50 us against 21 so, clip of 50 with 200k 475 against 444, 1080p clip of
     // 32 with 500k 1,990 against 1,810.
 #pragma unroll 1
-    for (int k = 0; k < BIN_GROUP / 256; ++k) {
+    for (int k = 0; k < a.bin_rounds; ++k) {
         uint64_t m = __ballot((big >> k) & 1u);
         while (m) {
             const int64_t g = g0 + k * 256 + w * 64 + __builtin_ctzll(m);

@@ -150,3 +150,36 @@ def test_gaussians_of_whole_grids(tiles_x, tiles_y):
     several in one wave and among smaller ones."""
     w = small_workload(tiles_x, 16 * tiles_x, 16 * tiles_y, 90, 2, trajectory=True, z=(2.0, 3.0), ls=(-1.4, 1.0))
     check_clip_against_oracle(w, f"whole grids {tiles_x}x{tiles_y}")
+
+
+@pytest.mark.parametrize("kw", [{}, dict(n_ctrl=5, poly_cov=True), dict(sh_degree=1)])
+@pytest.mark.parametrize("n,frames", [(1, 1), (255, 2), (257, 1), (1024, 3), (1025, 1), (5000, 2)])
+def test_binning_groups_of_small_launches(kw, n, frames):
+    """With room in the sort's buffers a small launch bins 256 Gaussians to a
+    workgroup, with little (most Gaussians off screen, a tight capacity) 1,024:
+    the same images and gradients bit for bit."""
+    rng = np.random.default_rng(n)
+    scene_np = gv_synth.make_scene(rng, n, z=(2.0, 8.0), log_scale=(-6.0, 0.3), **kw)
+    away = 7 * n // 8
+    scene_np.means[0, :away] += 40.0
+    if "n_ctrl" in kw:
+        scene_np.ctrl[:, 0, :away] += 40.0
+    cam_np = gv_synth.make_camera(640, 480, 640.0)
+    w = dict(scene=scene_np, camera=cam_np, poses=gv_synth.make_trajectory(rng, frames),
+             times=gv_synth.make_times(frames), frames=frames, n=n)
+    scene, cam, poses, times = device_inputs(w)
+    dl = torch.from_numpy(rng.normal(0, 1, (frames, 3, 480, 640)).astype(np.float32)).cuda()
+    wide = raster.Workspace(cam, n, frames, 4 * frames * n + 300 * frames * ((n + 255) // 256))
+    a = raster.render_batch(scene, cam, poses, times, wide, dL_dimages=dl)
+    torch.cuda.synchronize()
+    k = wide.status()["intersections"]
+    tight = raster.Workspace(cam, n, frames, max(k, 1))
+    b = raster.render_batch(scene, cam, poses, times, tight, dL_dimages=dl)
+    torch.cuda.synchronize()
+    assert wide.status()["overflow"] == 0 and tight.status()["overflow"] == 0
+    assert tight.status()["intersections"] == k < 300 * frames * ((n + 255) // 256)
+    assert torch.equal(a["images"], b["images"])
+    if not kw:  # with dynamics or SH the capacity also chooses the adjoint's form
+        assert torch.equal(a["dL_dposes"], b["dL_dposes"])
+        for name, g in a["grads"].items():
+            assert g is None or torch.equal(g, b["grads"][name]), name
