@@ -424,9 +424,11 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
     if (overflowed(a.status)) return;
     constexpr int FC = 16;  // frames whose cameras and pose sums are in LDS
     constexpr int NA = CUBIC ? 23 : 14;
-    // FP64 for dL/dSig wherever the registers leave three waves per SIMD (the
-    // 1080p clip with cubic means took 1,815 us at two, 1,641 without)
-    constexpr bool SIGMA_F64 = SPLIT == 1 || !CUBIC;
+    // FP64 for dL/dSig where a few frames do not average its rounding out.  Over
+    // twelve frames it changes the quaternion gradient's error by 3 % (median of
+    // 30 scenes), and with cubic means its registers would leave two waves per
+    // SIMD (1080p clip 1,641 -> 1,815 us).
+    constexpr bool SIGMA_F64 = SPLIT == 1;
     __shared__ double camd[SIGMA_F64 ? SPLIT : 1][SIGMA_F64 ? FC : 1][12];
     __shared__ float cam[SPLIT][FC][12], wpose[SPLIT][FC][12];
     __shared__ double red[SPLIT][64];
