@@ -70,8 +70,9 @@ struct __align__(16) ColorOp {
 };
 
 // Status word at the start of every workspace.
-// (ST_SLOTS: pre-sort slots handed out by the count pass).
-enum : int { ST_OVERFLOW = 0, ST_NONFINITE = 1, ST_K_LO = 2, ST_K_HI = 3, ST_SLOTS = 4, ST_WORDS = 16 };
+// (ST_SLOTS: pre-sort slots handed out by the count pass; ST_CROWDED: buckets
+// left to the merge sort).
+enum : int { ST_OVERFLOW = 0, ST_NONFINITE = 1, ST_K_LO = 2, ST_K_HI = 3, ST_SLOTS = 4, ST_CROWDED = 5, ST_WORDS = 16 };
 
 struct Tuning {
     int batch;      // 64 / 128 / 256 entries per LDS round of the forward compositing kernel

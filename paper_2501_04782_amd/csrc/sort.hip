@@ -1,14 +1,31 @@
 // Per-tile depth sort.  The binning pass already grouped the intersections by
 // (frame, tile) (a counting sort on the tile digit); each tile's bucket is
-// then sorted by the 64-bit key (fp32 depth bits, Gaussian index) in LDS by
-// one workgroup: ranks by comparison within chunks of 16 keys, then by merging
-// pairs of sorted runs level by level (binary search in the other run, the
-// searches of a thread's elements interleaved).  Keys are unique within a
-// bucket, so the order is fully determined (depth, ties by lower index)
-// whatever order the atomics of the scatter produced.  Buckets longer than the
-// LDS capacity are sorted in LDS chunks and merged in global memory (each
-// element finds its place in the partner run by binary search).
+// then sorted by the 64-bit key (fp32 depth bits, Gaussian index) by one
+// workgroup.  Keys are unique within a bucket, so the order is fully determined
+// (depth, ties by lower index) whatever order the atomics of the scatter
+// produced and whichever of the ways below sorts it:
+//
+// * by depth bins in LDS (buckets of up to 2,048 keys at the default setting)
+//   or in the merge scratch (longer ones);
+// * where more than BIN_KEYS keys fall in one bin (a surface, clusters and
+//   outliers), by fine bins, laid out after the keys' distribution;
+// * where even those crowd, by merging in a second launch: ranks by comparison
+//   within chunks of 16 keys, then by merging pairs of sorted runs level by
+//   level (binary search in the other run, the searches of a thread's elements
+//   interleaved).  Buckets longer than the LDS capacity are sorted in LDS chunks
+//   and merged in global memory (each element finds its place in the partner
+//   run by binary search).
+//
+// Bound by the latency of a bucket's few dependent steps; registers and LDS are
+// kept to eight waves per SIMD.  Merging alone took 445 us on the 50-frame
+// 960x540 clip of 200k Gaussians, 1,485 us on the 32-frame 1080p clip of 500k
+// and 800 us on 24 frames of 400k (buckets beyond 2,048 keys); by bins 295, 960
+// and 490 us.  Eight 540p frames of 200k with 80 % of the depths on a wavy
+// surface 144 against 111 us, all depths equal 107 against 54; half the depths
+// within 0.001 and half spread, the worst found, 139 against 250 us.
 #include "gv_internal.h"
+
+#include <algorithm>
 
 namespace gv {
 
@@ -182,16 +199,315 @@ __device__ __forceinline__ int64_t lower_rank(const KeySlot* R, int64_t len, uin
     return lo;
 }
 
+// ---------------------------------------------------------------------------
+// Sorting by depth bins.  The bucket's depths (as bit patterns) are cut into
+// bins of one power-of-two width between the smallest and the largest; a key's
+// rank is the number of keys in the bins before its own (a prefix sum of LDS
+// counts) plus the smaller keys of its own bin, found by comparing with each.
+// With at least as many bins as keys that is a handful of LDS accesses per key,
+// where merging runs of n keys takes about (log2 n)^2 / 2 dependent ones.
+
+// Inclusive prefix sum over the wave's 64 lanes.
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
+    x += __builtin_amdgcn_update_dpp(0u, x, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0u, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0u, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0u, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0u, x, 0x142, 0xa, 0xf, false);  // row_bcast 15, 31
+    x += __builtin_amdgcn_update_dpp(0u, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// Largest x of the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+    x = max(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0u, x, 0x111, 0xf, 0xf, false)));
+    x = max(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0u, x, 0x112, 0xf, 0xf, false)));
+    x = max(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0u, x, 0x114, 0xf, 0xf, false)));
+    x = max(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0u, x, 0x118, 0xf, 0xf, false)));
+    x = max(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0u, x, 0x142, 0xa, 0xf, false)));
+    x = max(x, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0u, x, 0x143, 0xc, 0xf, false)));
+    return __builtin_amdgcn_readlane(x, 63);
+}
+
+// Bins (d - lo) >> shift of the keys' upper words d (the depths) or, where
+// those are all equal, their lower words (the indices).
+struct DepthBins {
+    uint32_t lo;
+    int shift, word;  // word: 32 or 0
+    __device__ __forceinline__ int operator()(uint64_t key) const {
+        return static_cast<int>((static_cast<uint32_t>(key >> word) - lo) >> shift);
+    }
+};
+
+// 2^log_nb bins between the smallest and the largest of the words that for_keys
+// passes to its argument.  Uniform over the workgroup; one barrier, two for
+// equal depths.  `red` holds four words per wave.
+template <typename ForKeys>
+__device__ __forceinline__ DepthBins depth_bins(int log_nb, uint32_t* red, const ForKeys& for_keys) {
+    const int w = static_cast<int>(threadIdx.x) >> 6;
+    DepthBins B;
+    for (B.word = 32;; B.word = 0) {
+        uint32_t lo = ~0u, hi = 0u;
+        for_keys([&](uint64_t x) {
+            const uint32_t d = static_cast<uint32_t>(x >> B.word);
+            lo = min(lo, d);
+            hi = max(hi, d);
+        });
+        lo = ~wave_max(~lo);
+        hi = wave_max(hi);
+        if ((threadIdx.x & 63) == 0) {
+            red[w] = lo;
+            red[WG / 64 + w] = hi;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < WG / 64; ++k) {
+            lo = min(lo, red[k]);
+            hi = max(hi, red[WG / 64 + k]);
+        }
+        B.lo = lo;
+        const int bits = 32 - __builtin_clz((hi - lo) | 1u);  // hi - lo < 2^bits
+        B.shift = bits > log_nb ? bits - log_nb : 0;
+        if (hi != lo || B.word == 0) return B;
+        red += 2 * (WG / 64);  // the other words may still be read
+    }
+}
+
+// Counts of K * WG bins to the number of keys in the bins before each.  The
+// largest count is returned in every thread; `red` holds two words per wave.
+// Contains one barrier; the sums may be read after another.
+template <int K>
+__device__ __forceinline__ uint32_t scan_bins_of(uint32_t* bins, uint32_t* red) {
+    const int t = static_cast<int>(threadIdx.x), w = t >> 6;
+    uint32_t c[K], sum = 0u, top = 0u;
+#pragma unroll
+    for (int k = 0; k < K; ++k) c[k] = bins[t * K + k];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        sum += c[k];
+        top = max(top, c[k]);
+    }
+    const uint32_t incl = wave_inclusive_sum(sum);
+    top = wave_max(top);
+    if ((t & 63) == 63) {
+        red[w] = incl;
+        red[WG / 64 + w] = top;
+    }
+    __syncthreads();
+    uint32_t run = incl - sum;
+#pragma unroll
+    for (int k = 0; k < WG / 64; ++k) {
+        run += k < w ? red[k] : 0u;
+        top = max(top, red[WG / 64 + k]);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        bins[t * K + k] = run;
+        run += c[k];
+    }
+    return top;
+}
+
+__device__ __forceinline__ uint32_t scan_bins(uint32_t* bins, int log_nb, uint32_t* red) {
+    static_assert(WG == 256, "one to sixteen bins per thread");
+    switch (log_nb) {
+        case 8: return scan_bins_of<1>(bins, red);
+        case 9: return scan_bins_of<2>(bins, red);
+        case 10: return scan_bins_of<4>(bins, red);
+        case 11: return scan_bins_of<8>(bins, red);
+        default: return scan_bins_of<16>(bins, red);
+    }
+}
+
+constexpr int64_t MERGE_GROUPS = 1536;  // six per CU, as many as are resident
+
+// A bin with more keys than this costs as much as the merges.
+constexpr uint32_t BIN_KEYS = 64;
+
+// Words of LDS that a sort of buckets of up to CAP keys takes: the bins, and
+// then, in their place, the keys.
 template <int CAP>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CAP <= 1024 ? 7 : 1))) void k_tile_sort(Args a) {
+constexpr int SORT_LDS = CAP < 2048 ? 4096 : 2 * CAP;
+
+// Bins for crowded depths (a surface, or clusters and outliers): 256 coarse
+// bins by depth, each cut into bins in proportion to its keys between its own
+// smallest and largest key.  The keys' whole 64 bits count, so equal depths are
+// told apart by their indices.
+struct FineBins {
+    const uint64_t *lo, *hi;  // [256] keys
+    const uint32_t* start;    // [256] keys before
+    DepthBins coarse;
+    uint32_t n;
+    float per_key;  // bins
+    int last;       // bin
+    // Never falls from a key to a larger one: each float step is monotone.
+    __device__ __forceinline__ int operator()(uint64_t x) const {
+        const int c = coarse(x);
+        const uint32_t s = start[c], cnt = (c < 255 ? start[c + 1] : n) - s;
+        const uint64_t l = lo[c], h = hi[c];
+        const float f = h > l ? fminf(static_cast<float>(x - l) * (1.0f / static_cast<float>(h - l)), 1.0f) : 0.0f;
+        return min(static_cast<int>((static_cast<float>(s) + f * static_cast<float>(cnt)) * per_key), last);
+    }
+};
+constexpr int FINE_WORDS = 5 * 256;  // FineBins' tables, in front of the bins
+
+// Fills the coarse tables in `lds` from the keys that for_keys passes to its
+// argument and clears 2^log_nb fine bins behind them.  Ends with a barrier.
+template <typename ForKeys>
+__device__ __forceinline__ FineBins fine_bins(uint32_t* lds, uint32_t* red, DepthBins coarse, uint32_t n, int log_nb,
+                                              const ForKeys& for_keys) {
+    static_assert(WG == 256, "a thread per coarse bin");
+    const int t = static_cast<int>(threadIdx.x);
+    unsigned long long* lo = reinterpret_cast<unsigned long long*>(lds);
+    unsigned long long* hi = lo + 256;
+    uint32_t* start = lds + 1024;
+    __syncthreads();  // the depth bins are no longer read
+    lo[t] = ~0ull;
+    hi[t] = 0ull;
+    start[t] = 0u;
+    for (int b = t; b < 1 << log_nb; b += WG) lds[FINE_WORDS + b] = 0u;
+    __syncthreads();
+    for_keys([&](uint64_t x) {
+        const int c = coarse(x);
+        atomicMin(&lo[c], static_cast<unsigned long long>(x));
+        atomicMax(&hi[c], static_cast<unsigned long long>(x));
+        atomicAdd(&start[c], 1u);
+    });
+    __syncthreads();
+    scan_bins_of<1>(start, red);
+    __syncthreads();
+    FineBins F;
+    F.lo = reinterpret_cast<const uint64_t*>(lo);
+    F.hi = reinterpret_cast<const uint64_t*>(hi);
+    F.start = start;
+    F.coarse = coarse;
+    F.n = n;
+    F.last = (1 << log_nb) - 1;
+    F.per_key = static_cast<float>(1 << log_nb) / static_cast<float>(n);
+    return F;
+}
+
+// Sort of a bucket of n <= CAP keys by depth bins in LDS; false, with nothing
+// written, if the depths crowd in one bin.
+template <int CAP>
+__device__ __forceinline__ bool bin_sort_lds(const Args& a, uint32_t s, int n, uint32_t* bins, uint32_t* red) {
+    constexpr int EPT = CAP / WG;
+    constexpr int LOG_MAX = CAP >= 2048 ? 11 : 10;
+    static_assert(CAP <= 0xffff, "a bin's start and count share a word");
+    const int t = static_cast<int>(threadIdx.x);
+    const KeySlot* src = a.kv + s;
+    const int log_nb = min(max(33 - __builtin_clz(n), 8), LOG_MAX);  // one to four bins a key, or as many as there are
+    uint64_t x[EPT];
+    uint32_t v[EPT];
+#pragma unroll
+    for (int j = 0; j < EPT; ++j)
+        if (t + WG * j < n) {
+            const KeySlot ks = src[t + WG * j];
+            x[j] = ks.key;
+            v[j] = ks.slot;
+        }
+    for (int b = t; b < 1 << log_nb; b += WG) bins[b] = 0u;
+    const DepthBins B = depth_bins(log_nb, red, [&](const auto& each) {
+#pragma unroll
+        for (int j = 0; j < EPT; ++j)
+            if (t + WG * j < n) each(x[j]);
+    });
+    uint32_t at[EPT], fc[EPT];  // place within the bin, then in the bucket; the bin's start and count
+#pragma unroll
+    for (int j = 0; j < EPT; ++j)
+        if (t + WG * j < n) at[j] = atomicAdd(&bins[B(x[j])], 1u);
+    __syncthreads();
+    if (scan_bins(bins, log_nb, red + 2 * (WG / 64)) > BIN_KEYS) return false;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < EPT; ++j)
+        if (t + WG * j < n) {
+            const int b = B(x[j]);
+            const uint32_t first = bins[b], end = b + 1 < 1 << log_nb ? bins[b + 1] : static_cast<uint32_t>(n);
+            at[j] += first;
+            fc[j] = first | (end - first) << 16;
+        }
+    __syncthreads();
+    uint64_t* keys = reinterpret_cast<uint64_t*>(bins);
+#pragma unroll
+    for (int j = 0; j < EPT; ++j)
+        if (t + WG * j < n) keys[at[j]] = x[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < EPT; ++j)
+        if (t + WG * j < n) {
+            const uint32_t first = fc[j] & 0xffffu, end = first + (fc[j] >> 16);
+            uint32_t r = first;
+            for (uint32_t k = first; k < end; ++k) r += keys[k] < x[j] ? 1u : 0u;
+            a.sgid[s + r] = static_cast<uint32_t>(x[j]);
+            a.sslot[s + r] = v[j];
+        }
+    return true;
+}
+
+// The same for a longer bucket, or by fine bins: the keys are put in order of
+// their bins in the merge scratch, and each is then compared with its bin's keys
+// there.
+template <bool FINE>
+__device__ __forceinline__ bool bin_sort_global(const Args& a, uint32_t s, int64_t n, uint32_t* lds, uint32_t* red) {
+    constexpr int LOG_NB = 12, LOG_FINE = 11;
+    const int t = static_cast<int>(threadIdx.x);
+    const KeySlot* src = a.kv + s;
+    KeySlot* dst = a.tkv + s;
+    auto for_keys = [&](const auto& each) {
+        for (int64_t i = t; i < n; i += WG) each(src[i].key);
+    };
+    auto place = [&](uint32_t* bins, int log_nb, const auto& bin_of) {
+        for (int64_t i = t; i < n; i += WG) atomicAdd(&bins[bin_of(src[i].key)], 1u);
+        __syncthreads();
+        if (scan_bins(bins, log_nb, red + 2 * (WG / 64)) > BIN_KEYS) return false;
+        __syncthreads();
+        for (int64_t i = t; i < n; i += WG) {
+            const KeySlot e = src[i];
+            dst[atomicAdd(&bins[bin_of(e.key)], 1u)] = e;
+        }
+        __syncthreads();  // bins[b] is now the end of bin b
+        for (int64_t i = t; i < n; i += WG) {
+            const KeySlot e = dst[i];
+            const int b = bin_of(e.key);
+            const uint32_t first = b ? bins[b - 1] : 0u, end = bins[b];
+            uint32_t r = first;
+            for (uint32_t k = first; k < end; ++k) r += dst[k].key < e.key ? 1u : 0u;
+            a.sgid[s + r] = static_cast<uint32_t>(e.key);
+            a.sslot[s + r] = e.slot;
+        }
+        return true;
+    };
+    if (FINE) {
+        const DepthBins B = depth_bins(8, red, for_keys);
+        return place(lds + FINE_WORDS, LOG_FINE, fine_bins(lds, red, B, static_cast<uint32_t>(n), LOG_FINE, for_keys));
+    }
+    for (int b = t; b < 1 << LOG_NB; b += WG) lds[b] = 0u;
+    return place(lds, LOG_NB, depth_bins(LOG_NB, red, for_keys));
+}
+
+// One workgroup per bucket.  A bucket whose keys crowd even in one of the fine
+// bins goes on the list of k_tile_merge (in the scatter's cursors, which are no longer needed).
+template <int CAP>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CAP <= 2048 ? 8 : 1))) void k_tile_sort(Args a) {
     if (overflowed(a.status)) return;
-    const int64_t seg = blockIdx.x;
+    const uint32_t seg = blockIdx.x;
     uint32_t s, e;
     bucket_range(a, seg, s, e);
-    const int64_t n = static_cast<int64_t>(e) - s;
-    if (n <= 0) return;
+    if (e <= s) return;
+    const uint32_t n = e - s;
+    __shared__ __align__(16) uint32_t lds[SORT_LDS<CAP>];
+    __shared__ uint32_t red[4 * (WG / 64)];
+    if (n <= CAP ? bin_sort_lds<CAP>(a, s, static_cast<int>(n), lds, red) : bin_sort_global<false>(a, s, n, lds, red))
+        return;
+    __syncthreads();
+    if (!bin_sort_global<true>(a, s, n, lds, red) && threadIdx.x == 0) a.tcur[atomicAdd(&a.status[ST_CROWDED], 1u)] = seg;
+}
+
+// Sort of one bucket by merging.
+template <int CAP>
+__device__ __forceinline__ void merge_sort(const Args& a, uint32_t s, int64_t n, uint64_t* SA, uint64_t* SB) {
     constexpr int EPT = CAP / WG;
-    __shared__ uint64_t SA[CAP], SB[CAP];
     uint64_t x[EPT];
     uint32_t v[EPT];
     int rank[EPT];
@@ -300,14 +616,37 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CAP <= 1024 
     }
 }
 
+// The buckets that k_tile_sort listed, in turn.
+template <int CAP>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CAP <= 1024 ? 6 : 1))) void k_tile_merge(Args a) {
+    if (overflowed(a.status)) return;
+    __shared__ uint64_t SA[CAP], SB[CAP];
+    const uint32_t listed = a.status[ST_CROWDED];
+#pragma unroll 1
+    for (uint32_t i = blockIdx.x; i < listed; i += gridDim.x) {
+        uint32_t s, e;
+        bucket_range(a, a.tcur[i], s, e);
+        merge_sort<CAP>(a, s, static_cast<int64_t>(e) - s, SA, SB);
+        __syncthreads();
+    }
+}
+
+template <int CAP>
+static void launch_sort(const Args& a, int64_t segments, hipStream_t stream) {
+    // buckets of up to twice the merges' run length are sorted in LDS
+    hipLaunchKernelGGL(k_tile_sort<(CAP < 2048 ? 2 * CAP : 4096)>, dim3(static_cast<uint32_t>(segments)), dim3(WG), 0,
+                       stream, a);
+    hipLaunchKernelGGL(k_tile_merge<CAP>, dim3(static_cast<uint32_t>(std::min<int64_t>(segments, MERGE_GROUPS))),
+                       dim3(WG), 0, stream, a);
+}
+
 hipError_t launch_tile_sort(const Args& a, int64_t segments, hipStream_t stream) {
     if (segments <= 0) return hipSuccess;
-    const dim3 grid(static_cast<uint32_t>(segments)), block(WG);
     switch (a.tune.sort_cap) {
-        case 512: hipLaunchKernelGGL(k_tile_sort<512>, grid, block, 0, stream, a); break;
-        case 1024: hipLaunchKernelGGL(k_tile_sort<1024>, grid, block, 0, stream, a); break;
-        case 2048: hipLaunchKernelGGL(k_tile_sort<2048>, grid, block, 0, stream, a); break;
-        default: hipLaunchKernelGGL(k_tile_sort<4096>, grid, block, 0, stream, a); break;
+        case 512: launch_sort<512>(a, segments, stream); break;
+        case 1024: launch_sort<1024>(a, segments, stream); break;
+        case 2048: launch_sort<2048>(a, segments, stream); break;
+        default: launch_sort<4096>(a, segments, stream); break;
     }
     return hipGetLastError();
 }

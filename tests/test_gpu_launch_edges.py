@@ -6,8 +6,8 @@ import torch
 
 import gv_synth
 from oracle import pyramid as pyr_ref
-from parity_util import device_inputs, workspace_for
-from test_gpu_parity import check_clip_against_oracle, small_workload
+from parity_util import PixelTally, colour_range, compare_image, device_inputs, oracle_frame, workspace_for
+from test_gpu_parity import check_clip_against_oracle, run_clip, small_workload
 from test_gpu_visibility_pyramid import check_visibility
 
 pytestmark = pytest.mark.gpu
@@ -183,3 +183,38 @@ def test_binning_groups_of_small_launches(kw, n, frames):
         assert torch.equal(a["dL_dposes"], b["dL_dposes"])
         for name, g in a["grads"].items():
             assert g is None or torch.equal(g, b["grads"][name]), name
+
+
+@pytest.mark.parametrize("depths", ["ties", "plane", "crowd"])
+@pytest.mark.parametrize("n,cap", [(64, 1024), (65, 1024), (250, 512), (900, 512), (1300, 1024), (2100, 1024),
+                                   (2500, 2048), (4200, 4096), (5000, 512), (1600, 1024), (2500, 4096)])
+def test_depth_bins_and_merges(depths, n, cap):
+    """Buckets sorted by depth bins with equal depths in a bin (ties go by
+    index), in bins of the index (all depths equal), and in fine bins or by
+    merging (depths of 21 values within 1e-5 between two outliers, up to and
+    above 64 to a value).  Sizes within one run, two runs and more of every
+    merge, and past what the bins sort in LDS.
+    Images of one tile against the oracle.  Alphas of 0.0067 let 1,400 entries
+    count, and pass the stop's band of 2 x 2e-4 of the transmittance in steps of
+    that size: 6 % of the pixels may be set aside, here up to 10 %."""
+    w = small_workload(n, 16, 16, n, 1, z=(2.0, 6.0), ls=(1.5, 0.1))
+    rng = np.random.default_rng(n)
+    s = w["scene"]
+    s.means[0:2] *= 0.1
+    s.opacity_logits[:] = -5.0
+    s.opacity_logits[:: max(n // 20, 1)] = -3.0
+    z = {"ties": 2.0 + 0.05 * rng.integers(0, max(n // 20, 4), n), "plane": np.full(n, 4.0),
+         "crowd": 4.0 + 1e-5 * rng.random(n)}[depths]
+    if depths == "crowd":
+        z[n // 2], z[n // 3] = 2.0, 9.0
+    s.means[2] = z
+    ref = oracle_frame(w, 0)
+    old = raster.get_tuning()
+    raster.set_tuning(old["batch"], cap, old["compact"], old["bwd_batch"])
+    try:
+        out, ws, _ = run_clip(w, backward=False)
+    finally:
+        raster.set_tuning(old["batch"], old["sort_cap"], old["compact"], old["bwd_batch"])
+    tally = PixelTally(f"depth bins {depths} n={n} cap={cap}")
+    compare_image(out["images"].cpu().numpy()[0], ref, tally.label, colour_range(w), tally)
+    tally.finish(set_aside_max=0.1)
