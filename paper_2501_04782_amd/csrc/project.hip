@@ -417,28 +417,53 @@ struct WaveKeys {
 // handed out by LDS atomics.  A wave deals out its Gaussians' intersections
 // (the set bits of their masks) one per lane and step; the k-th set bit of a
 // mask gets pre-sort slot goff + k, as the count pass ordered them.
-__global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
+//
+// STAGED: written one by one, keys reach memory as 16-byte pieces of lines that
+// the L2s cannot hold until their neighbours come (the workgroups in flight
+// write some 100 MB): 28 M write requests for the 30 M keys of the 50-frame
+// 960x540 clip of 200k Gaussians, most of 32 bytes, and 446 us, with three
+// workgroups on a CU as with eight.  So the workgroup collects its keys in LDS
+// in order of the tiles, 8 bytes each, and writes a tile's run at once (25 keys
+// there): 335 us; 24 frames of 400k 452 -> 341.  For tile grids of up to
+// STAGE_TILES tiles, whose tables leave room for two workgroups of eight waves
+// on a CU; a workgroup with more than STAGE_KEYS keys writes them one by one.
+constexpr int STAGE_TILES = 2304;
+constexpr int STAGE_KEYS = 5120;
+constexpr int STAGE_THREADS = 512;
+template <bool STAGED>
+__global__ __launch_bounds__(STAGED ? STAGE_THREADS : 256) void k_scatter_lds(Args a) {
     if (overflowed(a.status)) return;
-    // base[t]: next position of this workgroup's range in tile t's bucket
+    constexpr int NT = STAGED ? STAGE_THREADS : 256;
+    // base[t]: next position of this workgroup's range in tile t's bucket; when
+    // keys are collected, what to add to a collected key's index to get there
     extern __shared__ uint32_t base[];
-    __shared__ WaveKeys wk[4];
+    // collected keys (depth bits; bit 30, tile << 16, Gaussian << 6, its
+    // intersection), the next index of each tile (16 bits, two tiles per word),
+    // and the Gaussians' first slots
+    __shared__ uint2 stage[STAGED ? STAGE_KEYS : 1];
+    __shared__ uint32_t cursor[STAGED ? STAGE_TILES / 2 : 1];
+    __shared__ uint32_t slots[STAGED ? BIN_GROUP : 1];
+    __shared__ uint32_t wsum[NT / 64];
+    __shared__ WaveKeys wk[NT / 64];
+    static_assert(STAGE_TILES <= 1 << 14 && BIN_GROUP <= 1 << 10 && STAGE_KEYS <= 0xffff, "packed");
     const int f = blockIdx.y;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t* bh = a.bhist + (static_cast<int64_t>(f) * a.bin_blocks + blockIdx.x) * a.tiles;
     const int64_t tile0 = static_cast<int64_t>(f) * a.tiles;
     // eight tiles per thread at a time: all counts are requested, then all
     // reservations, so each batch costs two memory round trips, not sixteen
-    constexpr int RT = 8;
-    for (int t0 = 0; t0 < a.tiles; t0 += 256 * RT) {
+    constexpr int RT = STAGED ? 5 : 8;
+    uint32_t mine = 0u;
+    for (int t0 = 0; t0 < a.tiles; t0 += NT * RT) {
         uint32_t v[RT], o[RT], lo[RT], hi[RT];
 #pragma unroll
         for (int k = 0; k < RT; ++k) {
-            const int t = t0 + k * 256 + threadIdx.x;
+            const int t = t0 + k * NT + threadIdx.x;
             v[k] = t < a.tiles ? bh[t] : 0u;
         }
 #pragma unroll
         for (int k = 0; k < RT; ++k) {
-            const int t = t0 + k * 256 + threadIdx.x;
+            const int t = t0 + k * NT + threadIdx.x;
             o[k] = lo[k] = hi[k] = 0u;
             if (v[k]) {
                 o[k] = atomicAdd(&a.tcur[tile0 + t], v[k]);
@@ -448,21 +473,55 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
         }
 #pragma unroll
         for (int k = 0; k < RT; ++k) {
-            const int t = t0 + k * 256 + threadIdx.x;
+            const int t = t0 + k * NT + threadIdx.x;
             if (t < a.tiles) {
                 const uint32_t b = v[k] ? lo[k] + o[k] : 0u;
                 base[t] = b;
+                mine += v[k];
                 if (v[k] && b + v[k] > hi[k]) a.status[ST_OVERFLOW] = 2u;  // counts disagree: internal error
             }
         }
     }
+    bool staged = false;
+    uint32_t total_keys = 0u;
+    if (STAGED) {
+        uint32_t wave_total;
+        uint32_t run = wave_exclusive_scan(mine, lane, wave_total);
+        if (lane == 0) wsum[w] = wave_total;
+        for (int t = threadIdx.x; t < STAGE_TILES / 2; t += NT) cursor[t] = 0u;
+        __syncthreads();
+        for (int k = 0; k < NT / 64; ++k) {
+            run += k < w ? wsum[k] : 0u;
+            total_keys += wsum[k];
+        }
+        staged = total_keys <= STAGE_KEYS;
+        if (staged)
+            for (int t = threadIdx.x; t < a.tiles; t += NT) {  // this thread's tiles, as above
+                const uint32_t v = bh[t];
+                if (!v) continue;
+                atomicAdd(&cursor[t >> 1], run << ((t & 1) << 4));
+                base[t] -= run;
+                run += v;
+            }
+    }
     __syncthreads();
+    // next index of a collected key of tile tl
+    auto collect = [&](int tl) {
+        const uint32_t sh = (tl & 1) << 4;
+        return (atomicAdd(&cursor[tl >> 1], 1u << sh) >> sh) & 0xffffu;
+    };
     // a workgroup emits exactly its histogram's count per tile; the end
     // checked per key is only the workspace's (no write out of bounds even
     // if the counts disagreed, which the reservation above reports)
-    auto next = [&](int tl) { return atomicAdd(&base[tl], 1u); };
+    auto next = [&](int tl) {
+        if (!staged) return atomicAdd(&base[tl], 1u);
+        const uint32_t li = collect(tl);
+        if (li < STAGE_KEYS) stage[li].y = 0u;  // written here, not with the others
+        return base[tl] + li;
+    };
     auto end = [&](int) { return static_cast<uint32_t>(a.k_cap); };
     const int64_t g0 = static_cast<int64_t>(blockIdx.x) * a.bin_rounds * 256;
+    const int rounds = STAGED ? BIN_GROUP / NT : a.bin_rounds;
     WaveKeys& W = wk[w];
     // A Gaussian's count, depth, rectangle, mask and slot offset, requested
     // together (one memory round trip; a Gaussian without intersections
@@ -476,7 +535,7 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
         uint32_t go;
     };
     auto load_in = [&](int k, In& x) {
-        const int64_t g = g0 + k * 256 + threadIdx.x;
+        const int64_t g = g0 + k * NT + threadIdx.x;
         const int64_t i = static_cast<int64_t>(f) * a.n + (g < a.n ? g : 0);
         x.cnt = g < a.n ? a.gcnt[i] : 0u;
         x.depth = a.dkey[i];
@@ -489,16 +548,17 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
     static_assert(BIN_GROUP / 256 <= 32, "one bit per round");
     uint32_t big = 0u;  // rounds whose Gaussian has no mask, scattered after the loop
 #pragma unroll 1
-    for (int k = 0; k < a.bin_rounds; ++k) {
-        const int64_t g = g0 + k * 256 + threadIdx.x;
+    for (int k = 0; k < rounds; ++k) {
+        const int64_t g = g0 + k * NT + threadIdx.x;
         const In cur = nxt;
-        if (k + 1 < a.bin_rounds) load_in(k + 1, nxt);
+        if (k + 1 < rounds) load_in(k + 1, nxt);
         const uint32_t cnt = cur.cnt;
         const uint2 rc = cur.rc;
         const uint64_t tm = cur.tm;
         const uint32_t go = cur.go;
         const bool small =
             cnt && ((rc.x >> 16) - (rc.x & 0xffff) + 1) * ((rc.y >> 16) - (rc.y & 0xffff) + 1) <= 64u;
+        if (staged) slots[k * NT + threadIdx.x] = go;
         uint32_t total;
         const uint32_t first = wave_exclusive_scan(small ? cnt : 0u, lane, total);
         W.start[lane] = first;
@@ -523,7 +583,15 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
                 }
                 const int bit = kth_set_bit(m, kk);
                 const int ry = bit / W.rw[o];
-                emit_key(a, W.key[o], W.goff[o] + kk, W.tx0[o] + (bit - ry * W.rw[o]), W.ty0[o] + ry, next, end);
+                const int tx = W.tx0[o] + (bit - ry * W.rw[o]), ty = W.ty0[o] + ry;
+                if (staged) {
+                    const int tl = ty * a.tiles_x + tx;
+                    const uint32_t li = collect(tl), gl = static_cast<uint32_t>(k * NT + w * 64 + o);
+                    if (li >= STAGE_KEYS) a.status[ST_OVERFLOW] = 2u;  // counts disagree: internal error
+                    else stage[li] = make_uint2(static_cast<uint32_t>(W.key[o] >> 32), 1u << 30 | tl << 16 | gl << 6 | kk);
+                } else {
+                    emit_key(a, W.key[o], W.goff[o] + kk, tx, ty, next, end);
+                }
             }
         }
         __builtin_amdgcn_wave_barrier();
@@ -536,10 +604,10 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
     // 50 us against 21 so, clip of 50 with 200k 475 against 444, 1080p clip of
     // 32 with 500k 1,990 against 1,810.
 #pragma unroll 1
-    for (int k = 0; k < a.bin_rounds; ++k) {
+    for (int k = 0; k < rounds; ++k) {
         uint64_t m = __ballot((big >> k) & 1u);
         while (m) {
-            const int64_t g = g0 + k * 256 + w * 64 + __builtin_ctzll(m);
+            const int64_t g = g0 + k * NT + w * 64 + __builtin_ctzll(m);
             m &= m - 1;
             const int64_t i = static_cast<int64_t>(f) * a.n + g;
             const Record r = a.rec[i];
@@ -561,6 +629,23 @@ __global__ __launch_bounds__(256) void k_scatter_lds(Args a) {
                 before += static_cast<uint32_t>(__popcll(pass));
             }
         }
+    }
+    if (!staged) return;
+    __syncthreads();
+    for (uint32_t li = threadIdx.x; li < total_keys; li += NT) {
+        const uint2 e = stage[li];
+        if (!(e.y >> 30)) continue;
+        const int tl = static_cast<int>(e.y >> 16 & 0x3fffu);
+        const uint32_t gl = e.y >> 6 & 0x3ffu, pos = tl < a.tiles ? base[tl] + li : ~0u;
+        if (pos >= end(tl)) {
+            a.status[ST_OVERFLOW] = 2u;
+            continue;
+        }
+        KeySlot ks;
+        ks.key = static_cast<uint64_t>(e.x) << 32 | static_cast<uint64_t>(g0 + gl);
+        ks.slot = slots[gl] + (e.y & 63u);
+        ks.pad = 0u;
+        a.kv[pos] = ks;
     }
 }
 
@@ -696,8 +781,12 @@ hipError_t launch_project(const Args& a, hipStream_t stream) {
 hipError_t launch_scatter(const Args& a, hipStream_t stream) {
     if (a.n <= 0) return hipSuccess;
     if (a.bhist) {
-        hipLaunchKernelGGL(k_scatter_lds, dim3(static_cast<uint32_t>(a.bin_blocks), a.frames), dim3(256),
-                           sizeof(uint32_t) * a.tiles, stream, a);
+        const dim3 grid(static_cast<uint32_t>(a.bin_blocks), a.frames);
+        const size_t lds = sizeof(uint32_t) * a.tiles;
+        if (a.tiles <= STAGE_TILES && a.bin_rounds == BIN_GROUP / 256)
+            hipLaunchKernelGGL(k_scatter_lds<true>, grid, dim3(STAGE_THREADS), lds, stream, a);
+        else
+            hipLaunchKernelGGL(k_scatter_lds<false>, grid, dim3(256), lds, stream, a);
     } else {
         hipLaunchKernelGGL(k_scatter, dim3(static_cast<uint32_t>((a.n + 255) / 256), a.frames), dim3(256), 0, stream,
                            a);

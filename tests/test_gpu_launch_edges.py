@@ -218,3 +218,30 @@ def test_depth_bins_and_merges(depths, n, cap):
     tally = PixelTally(f"depth bins {depths} n={n} cap={cap}")
     compare_image(out["images"].cpu().numpy()[0], ref, tally.label, colour_range(w), tally)
     tally.finish(set_aside_max=0.1)
+
+
+@pytest.mark.parametrize("tiles_x,tiles_y,n,frames,ls", [(20, 9, 1000, 128, (-4.0, 0.3)), (20, 9, 1100, 70, (-3.0, 0.3)),
+                                                         (20, 9, 1024, 128, (-2.5, 1.0)), (48, 48, 33000, 4, (-4.5, 0.8)),
+                                                         (47, 50, 33000, 4, (-4.5, 0.8))])
+def test_scatter_of_collected_keys(tiles_x, tiles_y, n, frames, ls):
+    """Workgroups that collect their keys in LDS, ones with more keys than fit,
+    Gaussians without a mask among them, and the largest tile grid that does and
+    the smallest that does not: images of single frames (small launches, which
+    do not collect) bit for bit, and their pose gradients up to the order of the
+    sums of at most 256 pixels per tile."""
+    w = small_workload(n, 16 * tiles_x, 16 * tiles_y, n, frames, trajectory=True, z=(2.0, 6.0), ls=ls)
+    scene, cam, poses, times = device_inputs(w)
+    dl = torch.randn(frames, 3, 16 * tiles_y, 16 * tiles_x, device="cuda")
+    ws = workspace_for(scene, cam, poses, times)
+    a = raster.render_batch(scene, cam, poses, times, ws, dL_dimages=dl)
+    torch.cuda.synchronize()
+    st = ws.status()
+    assert st["overflow"] == 0
+    one = workspace_for(scene, cam, poses[:1], times[:1], margin=4.0)
+    for f in sorted({0, 1, frames // 2, frames - 1}):
+        b = raster.render_batch(scene, cam, poses[f:f + 1], times[f:f + 1], one, dL_dimages=dl[f:f + 1])
+        torch.cuda.synchronize()
+        assert one.status()["overflow"] == 0
+        assert torch.equal(a["images"][f], b["images"][0]), f
+        ga, gb = a["dL_dposes"][f], b["dL_dposes"][0]
+        assert torch.linalg.norm(ga - gb) <= 256 * 2.0 ** -24 * torch.linalg.norm(gb), f
