@@ -169,6 +169,7 @@ struct Args {
     ShapeD* shapes;       // [N] static shapes of this call (scenes without dynamics)
     KeySlot* tkv;         // [K] merge scratch of the sort
     int64_t k_cap;
+    unsigned long long* total_out;  // host memory that takes the intersection count plus one, or nullptr
     // image-space inputs/outputs
     float* images;            // [F][3][H][W]
     const float* targets;     // [F][3][H][W] or nullptr

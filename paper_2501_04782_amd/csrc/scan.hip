@@ -75,6 +75,7 @@ __device__ __forceinline__ void finish_scan(const Args& a, int64_t count, unsign
     a.status[ST_K_LO] = static_cast<uint32_t>(total);
     a.status[ST_K_HI] = static_cast<uint32_t>(total >> 32);
     if (total > static_cast<uint64_t>(a.k_cap)) a.status[ST_OVERFLOW] = 1u;
+    if (a.total_out) __hip_atomic_store(a.total_out, total + 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_one(Args a, int64_t count) {

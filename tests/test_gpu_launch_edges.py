@@ -1,5 +1,7 @@
 """GPU parity at the sizes where the kernels' work split changes: edges of
 strips and groups, remainders, the smallest sizes, misaligned buffers."""
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 import torch
@@ -13,6 +15,7 @@ from test_gpu_visibility_pyramid import check_visibility
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
+    from paper_2501_04782_amd import _lib as L
     from paper_2501_04782_amd import raster
 
 
@@ -245,3 +248,37 @@ def test_scatter_of_collected_keys(tiles_x, tiles_y, n, frames, ls):
         assert torch.equal(a["images"][f], b["images"][0]), f
         ga, gb = a["dL_dposes"][f], b["dL_dposes"][0]
         assert torch.linalg.norm(ga - gb) <= 256 * 2.0 ** -24 * torch.linalg.norm(gb), f
+
+
+def test_frames_of_several_threads_and_streams():
+    """The intersection count of a frame reaches its own call: four threads on
+    streams of their own, every third call with a workspace too small for it."""
+    w = small_workload(5, 96, 80, 3000, 4, trajectory=True, z=(2.0, 6.0), ls=(-3.0, 0.3))
+    scene, cam, poses, _ = device_inputs(w)
+    want, counts = [], []
+    for f in range(4):
+        ws = workspace_for(scene, cam, poses[f:f + 1], None, margin=2.0)
+        want.append(raster.render_fwd(scene, cam, poses[f], 0.0, ws).clone())
+        counts.append(ws.status()["intersections"])
+    torch.cuda.synchronize()
+
+    def calls(f):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            ws = raster.Workspace(cam, 3000, 1, counts[f])
+            small = raster.Workspace(cam, 3000, 1, counts[f] // 2)
+            bad = []
+            for k in range(30):
+                if k % 3 == 2:
+                    try:
+                        raster.render_fwd(scene, cam, poses[f], 0.0, small)
+                        bad.append(k)
+                    except L.GvError as e:
+                        if e.status != L.GV_ERR_CAPACITY:
+                            bad.append((k, e.status))
+                elif not torch.equal(raster.render_fwd(scene, cam, poses[f], 0.0, ws), want[f]):
+                    bad.append(k)
+            torch.cuda.current_stream().synchronize()
+            return bad
+
+    with ThreadPoolExecutor(4) as pool:
+        assert list(pool.map(calls, range(4))) == [[]] * 4
