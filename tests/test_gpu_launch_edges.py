@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 if torch.cuda.is_available():
     from paper_2501_04782_amd import _lib as L
     from paper_2501_04782_amd import raster
+    from paper_2501_04782_amd.optim import Adan
 
 
 @pytest.mark.parametrize("H,W,offset", [(1, 1, 0), (2, 2, 0), (3, 3, 0), (2, 4, 0), (5, 8, 0), (16, 12, 0),
@@ -282,3 +283,27 @@ def test_frames_of_several_threads_and_streams():
 
     with ThreadPoolExecutor(4) as pool:
         assert list(pool.map(calls, range(4))) == [[]] * 4
+
+
+@pytest.mark.parametrize("counts", [(1, 4, 3), (1023, 1024, 1025), (4096, 5, 2048), (1028, 4100, 2)])
+def test_adan_accesses(counts):
+    """Tensors that take 16-byte accesses and tensors that do not (lengths that
+    are no multiple of four, addresses off by one element), whole and cut
+    workgroups: two steps equal those of the same values one tensor at a time at
+    an odd address, up to the rounding of eight operations."""
+    g = torch.Generator(device="cuda").manual_seed(sum(counts))
+    values = [torch.randn(c, device="cuda", generator=g) for c in counts]
+    grads = [[torch.randn(c, device="cuda", generator=g) for c in counts] for _ in range(2)]
+    params = [v.clone() for v in values]
+    opt = Adan(params, lr=0.01, weight_decay=0.02)
+    for gr in grads:
+        opt.step(gr)
+    for i, c in enumerate(counts):
+        odd = torch.zeros(c + 1, device="cuda")[1:]
+        odd.copy_(values[i])
+        one = Adan([odd], lr=0.01, weight_decay=0.02)
+        for gr in grads:
+            one.step([gr[i]])
+        tol = 8 * 2.0 ** -24
+        assert torch.allclose(params[i], odd, rtol=tol, atol=tol), c
+        assert torch.allclose(opt.states[i], one.states[0], rtol=tol, atol=tol * 8), c
