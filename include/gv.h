@@ -140,9 +140,10 @@ typedef struct {
 
 /* Tunables of the rasterizer kernels (chosen by gv_autotune, or set directly).
  * batch: entries staged in LDS per round of a tile's compositing loop
- * (64, 128 or 256); sort_cap: longest per-tile list sorted in one LDS pass
- * (512, 1024, 2048 or 4096; lists up to twice that merge two LDS-sorted
- * runs, longer lists are sorted in chunks and merged in global memory);
+ * (64, 128 or 256); sort_cap: run length of the per-tile sort
+ * (512, 1024, 2048 or 4096): lists of up to twice that (at most 4096) are
+ * sorted by depth bins in LDS, longer ones through memory, and lists whose
+ * depths crowd in a bin by merging LDS-sorted runs of that length;
  * compact: compositing kernel choice, 0..63.  With bit 2 set the forward lets
  * each wave walk the entries meeting its 8x8 quadrant; with it clear each
  * 16-lane row of a wave walks the entries meeting its 4x4 pixel block; with
@@ -194,9 +195,10 @@ gv_status gv_project_fwd(const gv_scene *scene, const gv_camera *cam, const floa
                          float *records, int32_t *tile_counts, void *ws, size_t ws_bytes, void *stream);
 
 /* Forward render of one frame (the plain per-frame path).  image [3][H][W];
- * T_final [H][W] (final transmittance) may be NULL.  Reads the intersection
- * count back to the host once (synchronises `stream`) and returns
- * GV_ERR_CAPACITY, with nothing rendered, if it exceeds the workspace.
+ * T_final [H][W] (final transmittance) may be NULL.  Waits once for the
+ * intersection count (for all that `stream` held before and the binning, not
+ * for the kernels behind it) and returns GV_ERR_CAPACITY, with nothing
+ * rendered, if it exceeds the workspace.
  * The workspace then holds what gv_render_bwd needs. */
 gv_status gv_render_fwd(const gv_scene *scene, const gv_camera *cam, const float *pose7, float t,
                         float *image, float *T_final, void *ws, size_t ws_bytes, void *stream);
