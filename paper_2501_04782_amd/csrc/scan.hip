@@ -7,8 +7,9 @@
 // 2,040); above, each workgroup scans SCAN_TILE counts and a second launch adds
 // what lies before, every workgroup summing the earlier workgroups' totals
 // itself.  With the clears in one kernel and the two last reductions of the
-// adjoint in another, a 128x128 step went from 17 launches to 9 and from 143 to
-// 129 us, one 960x540 frame of 100k Gaussians from 359 to 328 us.
+// adjoint in another, a 128x128 step went from 17 launches to 9 (the sort has
+// since taken a second) and from 143 to 129 us, one 960x540 frame of 100k
+// Gaussians from 359 to 328 us.
 #include "gv_internal.h"
 
 namespace gv {
