@@ -12,7 +12,8 @@
 // form (rows inside, columns outside), so the values are the same bit for bit.
 // 50 960x540 frames, 4 levels: 340 us with one output per thread (25
 // four-byte loads each), 105 us now; reading and writing every level
-// once at the copy rate would take 82 us.
+// once at the copy rate would take 82 us.  Narrow planes without 16-byte rows
+// keep one output per thread (k_pyr_narrow).
 #include "gv_internal.h"
 
 namespace gv {
@@ -20,7 +21,9 @@ namespace gv {
 // Rows per strip: 8 read an input row 1.2 times; 2 (1.75 times) give four times
 // the threads, for levels that would not fill the chip with strips of 8 (below
 // PYR_FEW threads: 16 waves on each of 256 CUs; 5 levels of a 1920x1080 frame
-// 33 us with one output per thread, 27 us so).
+// 33 us with one output per thread, 27 us so), and for heights that would leave
+// more than three tenths of a strip of 8 empty (65,536 planes of 20x20: 59 us
+// in strips of 8, 54 of 2; of 4x4, 1,048,576 planes: 169 and 56).
 constexpr int64_t PYR_FEW = 256 * 16 * 64;
 
 // i mirrored into [0, n) without repeating the edges.
@@ -140,8 +143,13 @@ __global__ __launch_bounds__(256) void k_pyr_reduce(const float* __restrict__ in
 // microseconds do not each wait for a launch.  One thread per output, the sums
 // in the same order.  Taken when at least two levels remain and the plane has
 // at most PYR_TAIL samples.  64 frames of 206x139, 6 levels: 37 us with a
-// launch per level, 24 us with two launches.
+// launch per level, 24 us with two launches.  And for at most PYR_TAIL_PLANES
+// planes, four to each workgroup that the chip holds at a time: small planes
+// leave most of a workgroup idle (2,048 planes of 32x32, 4 launches 27 us
+// against 19; 4,096 27 against 36; 1,048,576 planes of 8x8 154 us against
+// 4,442), and a launch holds fewer than 2^32 threads.
 constexpr int PYR_TAIL = 8192;
+constexpr int64_t PYR_TAIL_PLANES = 2048;
 constexpr int TAIL_WG = 1024;
 
 __global__ __launch_bounds__(TAIL_WG) void k_pyr_tail(const float* __restrict__ in, float* __restrict__ out,
@@ -180,6 +188,38 @@ __global__ __launch_bounds__(TAIL_WG) void k_pyr_tail(const float* __restrict__ 
     }
 }
 
+// Rows of up to PYR_NARROW outputs that take no 16-byte loads: one thread per
+// output, so that a wave reads neighbouring samples.  A wave of strips reads as
+// many distant rows as it has strips side by side: 65,536 planes of 64x1 88 us
+// against 41, of 300x11 1,274 against 987, 1,048,576 of 14x14 1,057 against
+// 915; beyond (64x17) 356 us in strips against 479.
+constexpr int PYR_NARROW = 8;
+
+__global__ __launch_bounds__(256) void k_pyr_narrow(const float* __restrict__ in, float* __restrict__ out,
+                                                    int64_t outputs, int H, int W, int Ho, int Wo) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= outputs) return;
+    const int64_t per = static_cast<int64_t>(Ho) * Wo;
+    const int64_t p = i / per;
+    const int r = static_cast<int>(i - p * per);
+    const int y = r / Wo, x = r - y * Wo;
+    const float k[5] = {0.0625f, 0.25f, 0.375f, 0.25f, 0.0625f};
+    const float* src = in + p * static_cast<int64_t>(H) * W;
+    int xs[5];
+#pragma unroll
+    for (int d = 0; d < 5; ++d) xs[d] = mirror_index(2 * x + d - 2, W);
+    float acc = 0.0f;
+#pragma unroll
+    for (int dy = 0; dy < 5; ++dy) {
+        const float* row = src + static_cast<int64_t>(mirror_index(2 * y + dy - 2, H)) * W;
+        float h = 0.0f;
+#pragma unroll
+        for (int dx = 0; dx < 5; ++dx) h += k[dx] * row[xs[dx]];
+        acc += k[dy] * h;
+    }
+    out[i] = acc;
+}
+
 template <bool VEC, int ROWS>
 static void launch_strips(const float* src, float* dst, int64_t planes, int h, int w, int ho, int wo, hipStream_t st) {
     const int64_t threads = planes * ((ho + ROWS - 1) / ROWS) * ((wo + 1) / 2);
@@ -199,7 +239,14 @@ static hipError_t launch_pyr_reduce(const float* src, float* dst, int64_t planes
     // 4-byte accesses
     const bool vec = w % 4 == 0 && (reinterpret_cast<uintptr_t>(src) & 15u) == 0u &&
                      (reinterpret_cast<uintptr_t>(dst) & 7u) == 0u;
-    const bool few = planes * ((ho + 7) / 8) * ((wo + 1) / 2) < PYR_FEW;
+    if (!vec && wo <= PYR_NARROW) {
+        const int64_t n = planes * static_cast<int64_t>(ho) * wo;
+        hipLaunchKernelGGL(k_pyr_narrow, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256), 0, st, src, dst, n, h, w,
+                           ho, wo);
+        return hipGetLastError();
+    }
+    const int strips = (ho + 7) / 8;
+    const bool few = 80 * strips > 13 * ho || planes * strips * ((wo + 1) / 2) < PYR_FEW;
     if (vec && few) launch_strips<true, 2>(src, dst, planes, h, w, ho, wo, st);
     else if (vec) launch_strips<true, 8>(src, dst, planes, h, w, ho, wo, st);
     else if (few) launch_strips<false, 2>(src, dst, planes, h, w, ho, wo, st);
@@ -239,7 +286,7 @@ extern "C" gv_status gv_gaussian_pyramid(const float* images, int64_t planes, in
     float* dst = out;
     int h = height, w = width;
     for (int l = 1; l < levels; ++l) {
-        if (levels - l >= 2 && static_cast<int64_t>(h) * w <= PYR_TAIL && planes <= 0x7fffffffLL) {
+        if (levels - l >= 2 && static_cast<int64_t>(h) * w <= PYR_TAIL && planes <= PYR_TAIL_PLANES) {
             hipLaunchKernelGGL(k_pyr_tail, dim3(static_cast<uint32_t>(planes)), dim3(TAIL_WG), 0, st, src, dst, planes, h, w,
                                levels - l);
             return hipGetLastError() == hipSuccess ? GV_OK : GV_ERR_HIP;

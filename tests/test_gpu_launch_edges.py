@@ -307,3 +307,30 @@ def test_adan_accesses(counts):
         tol = 8 * 2.0 ** -24
         assert torch.allclose(params[i], odd, rtol=tol, atol=tol), c
         assert torch.allclose(opt.states[i], one.states[0], rtol=tol, atol=tol * 8), c
+
+
+@pytest.mark.parametrize("planes", [2 ** 22 - 1, 2 ** 22, 2 ** 22 + 3])
+def test_pyramid_of_many_planes(planes):
+    """More planes than a launch has workgroups of 1,024 threads for (2^32
+    threads): equal bits to the levels computed one call at a time."""
+    img = torch.rand(planes, 3, 5, device="cuda")
+    got = raster.gaussian_pyramid(img, 4)
+    for lvl in range(1, 4):
+        assert torch.equal(got[lvl], raster.gaussian_pyramid(got[lvl - 1].clone(), 2)[1]), lvl
+
+
+@pytest.mark.parametrize("planes", [2048, 2049])
+@pytest.mark.parametrize("H,W", [(8, 8), (20, 15), (18, 16), (19, 17), (21, 19), (40, 9), (3, 33)])
+def test_pyramid_of_small_planes(H, W, planes):
+    """Plane counts on both sides of the line where the last levels leave their
+    common launch; widths that take one output per thread, vector loads and
+    neither, heights in strips of two and of eight rows: equal bits to one
+    plane at a time, and within 10 roundings of 2^-24 per level of 64 bits."""
+    img = torch.rand(planes, H, W, device="cuda")
+    got = raster.gaussian_pyramid(img, 4)
+    for p in (0, planes // 2, planes - 1):
+        one = raster.gaussian_pyramid(img[p].clone(), 4)
+        ref = pyr_ref.pyramid(img[p].cpu().numpy().astype(np.float64)[None], 4)
+        for lvl in range(1, 4):
+            assert torch.equal(got[lvl][p], one[lvl]), (p, lvl)
+            np.testing.assert_allclose(got[lvl][p].cpu().numpy(), ref[lvl][0], rtol=0, atol=(lvl + 1) * 10 * 2.0 ** -24)
