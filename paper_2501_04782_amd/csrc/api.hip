@@ -476,6 +476,10 @@ gv_status gv_project_fwd(const gv_scene* scene, const gv_camera* cam, const floa
     if (s != GV_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     a.t0 = t;
+    // the slots of a forward on this workspace stay (the count pass hands them
+    // out in another order every time), so that its backward still finds them
+    a.goff = nullptr;
+    a.pused = nullptr;
     GV_TRY(launch_project(a, st));
     GV_TRY(launch_export_records(a, records, tile_counts, st));
     return GV_OK;

@@ -148,7 +148,7 @@ struct Args {
     uint64_t* tmask;      // [F][N]: tiles that passed the ellipse test, row-major bits over the rectangle
                           // (rectangles of at most 64 tiles; larger ones are tested again by the scatter)
     uint32_t* gcnt;       // [F*N]
-    uint32_t* goff;       // [F*N] first pre-sort slot of each (frame, Gaussian)
+    uint32_t* goff;       // [F*N] first pre-sort slot of each (frame, Gaussian), or nullptr (projection only)
     uint32_t* tcnt;       // [F*T]
     uint32_t* toff;       // [F*T + 1]
     uint32_t* tcur;       // [F*T]

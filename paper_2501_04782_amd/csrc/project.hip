@@ -354,7 +354,8 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
 #pragma unroll
     for (int k = 0; k < ROUNDS; ++k) {
         const int64_t g = g0 + k * 256 + threadIdx.x;
-        if (k < a.bin_rounds && g < a.n) a.goff[static_cast<int64_t>(f) * a.n + g] = slot0 + wtotal[k][w] + before[k];
+        if (a.goff && k < a.bin_rounds && g < a.n)
+            a.goff[static_cast<int64_t>(f) * a.n + g] = slot0 + wtotal[k][w] + before[k];
     }
 }
 
@@ -684,7 +685,7 @@ __global__ __launch_bounds__(256) void k_project(Args a) {
     slot0 = static_cast<uint32_t>(__shfl(static_cast<int>(slot0), 0, 64));
     if (live) {
         a.gcnt[i] = cnt;
-        a.goff[i] = slot0 + before;
+        if (a.goff) a.goff[i] = slot0 + before;
     }
 }
 
@@ -760,7 +761,7 @@ static void launch_projection(const Args& a, hipStream_t stream) {
 template <typename T>
 static hipError_t launch_project_as(const Args& a, hipStream_t stream) {
     const bool dyn = a.n_ctrl > 0 || a.scale_coeffs || a.quat_coeffs, sh = a.sh_degree > 0;
-    const int64_t ft = static_cast<int64_t>(a.frames) * a.tiles, marks = a.k_cap / 32 + 2;
+    const int64_t ft = static_cast<int64_t>(a.frames) * a.tiles, marks = a.pused ? a.k_cap / 32 + 2 : 0;
     const int64_t threads = std::max({static_cast<int64_t>(ST_WORDS), ft, marks, dyn ? int64_t(0) : a.n});
     hipLaunchKernelGGL(k_begin<T>, dim3(static_cast<uint32_t>((threads + 255) / 256)), dim3(256), 0, stream, a, !dyn, ft,
                        marks);
@@ -774,6 +775,7 @@ static hipError_t launch_project_as(const Args& a, hipStream_t stream) {
 
 // Clears the counters (and the adjoint's marks) and projects; the
 // instantiations without dynamics read the shapes the first kernel leaves.
+// Without a.goff and a.pused the slots are counted but not handed out.
 hipError_t launch_project(const Args& a, hipStream_t stream) {
     return a.dtype == GV_BF16 ? launch_project_as<uint16_t>(a, stream) : launch_project_as<float>(a, stream);
 }
