@@ -293,8 +293,9 @@ __device__ __forceinline__ void projection_adjoint(const Args& a, const float* R
 // (3-8; slot 9 unused), opacity (10) and colour (11-13), and the cubic mean
 // coefficients 14-22.  The dynamic layout (B-spline means and/or polynomial
 // log-scales and quaternions, Eq. 2-3) holds the 14 at 0-13, a window of four
-// control points 14-25 (point span + r, axis k at 14 + 3 r + k), the
-// log-scale coefficients 26-34 and the quaternion coefficients 35-46.
+// control points 14-25 (point span + r, axis k at 14 + 3 r + k) or, as the two
+// exclude each other, the cubic mean coefficients 14-22, the log-scale
+// coefficients 26-34 and the quaternion coefficients 35-46.
 template <bool DYN>
 struct AccLayout {
     static constexpr int N = DYN ? 47 : 23;
@@ -808,7 +809,8 @@ __global__ __launch_bounds__(128) void k_adjoint_sum(Args a, FrameStore store) {
             mc[k] = a.mean_coeffs ? static_cast<float>(load_param<T>(a.mean_coeffs, k * n + gs)) : 0.0f;
     }
     // control-point window: sums of points win .. win + 3, flushed to memory
-    // (added) when a frame falls in another knot span
+    // (added) when a frame falls in another knot span; cubic means, which
+    // exclude control points, take its place
     int win = -1;
     auto flush_window = [&]() {
         if (win < 0 || !live) return;
@@ -884,6 +886,12 @@ __global__ __launch_bounds__(128) void k_adjoint_sum(Args a, FrameStore store) {
                     for (int r = 0; r < 4; ++r)
 #pragma unroll
                         for (int k = 0; k < 3; ++k) win_acc[3 * r + k] += weights[fi][r] * go[k];
+                else if (a.mean_coeffs)
+                    for (int k = 0; k < 3; ++k) {
+                        win_acc[k] += go[k] * t1;
+                        win_acc[3 + k] += go[k] * t2;
+                        win_acc[6 + k] += go[k] * t3;
+                    }
                 if (a.scale_coeffs)
                     for (int k = 0; k < 3; ++k) {
                         sc[k] += go[3 + k] * t1;
@@ -950,6 +958,8 @@ __global__ __launch_bounds__(128) void k_adjoint_sum(Args a, FrameStore store) {
     for (int k = 0; k < 4; ++k) put(a.g_quats, k * n + g, gsq[3 + k]);
     put(a.g_opacity, g, acc[10]);
     if constexpr (DYN) {
+        if (a.mean_coeffs)
+            for (int k = 0; k < 9; ++k) put(a.g_coeffs, k * n + g, win_acc[k]);
         if (a.scale_coeffs)
             for (int k = 0; k < 9; ++k) put(a.g_scale_coeffs, k * n + g, sc[k]);
         if (a.quat_coeffs)
@@ -1131,7 +1141,7 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
                 }
                 for (int k = 0; k < 14; ++k) acc[k][tid] += go[k];
                 const double t1 = t, t2 = t1 * t1, t3 = t2 * t1;
-                if (!DYN && a.mean_coeffs)
+                if (a.mean_coeffs)
                     for (int k = 0; k < 3; ++k) {
                         acc[LA::CUBIC + k][tid] += go[k] * t1;
                         acc[LA::CUBIC + 3 + k][tid] += go[k] * t2;
@@ -1236,7 +1246,7 @@ __global__ __launch_bounds__((pb_threads<DYN, SH>())) void k_project_bwd(Args a)
     }
     for (int k = 0; k < 4; ++k) put(a.g_quats, k * n + g, gsq[3 + k]);
     put(a.g_opacity, g, acc[10][tid]);
-    if (!DYN && a.mean_coeffs)
+    if (a.mean_coeffs)
         for (int c = 0; c < 3; ++c)
             for (int k = 0; k < 3; ++k) put(a.g_coeffs, (c * 3 + k) * n + g, acc[LA::CUBIC + c * 3 + k][tid]);
     if (DYN && a.scale_coeffs)

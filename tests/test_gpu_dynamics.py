@@ -105,3 +105,49 @@ def test_spline_time_outside_domain_drops_gaussians():
     for f in range(2):  # the oracle drops them too
         ref = oracle_frame(w, f)
         assert np.allclose(ref["color"], [0.1, 0.2, 0.3])
+
+
+@pytest.mark.parametrize("sh", [0, 2])
+@pytest.mark.parametrize("coeffs", ["both", "scale", "quat"])
+def test_cubic_means_with_cubic_covariance(coeffs, sh):
+    """Cubic means together with cubic log-scales and / or quaternions: every
+    gradient against the oracle, in the adjoint's two-kernel form."""
+    rng = np.random.default_rng(60 + sh)
+    scene = gv_synth.make_scene(rng, 1500, z=(2.0, 10.0), log_scale=(-3.2, 0.5), cubic=True, poly_cov=True,
+                                coeff_std=0.1, sh_degree=sh)
+    if coeffs == "scale":
+        scene.quat_coeffs = None
+    if coeffs == "quat":
+        scene.scale_coeffs = None
+    w = dict(scene=scene, camera=gv_synth.make_camera(128, 80, 128.0), poses=gv_synth.make_trajectory(rng, 5),
+             times=gv_synth.make_times(5), frames=5, n=1500)
+    check_clip_against_oracle(w, f"cubic means, {coeffs} coefficients, SH {sh}")
+
+
+@pytest.mark.parametrize("sh", [0, 1])
+def test_cubic_means_with_cubic_covariance_in_one_kernel(sh):
+    """The same in the one-kernel form (three quarters of the Gaussians off
+    screen and a tight capacity), against the two-kernel form.  Both sum the
+    same terms over 9 frames in FP64, which may each differ by a few roundings
+    of 2^-24."""
+    rng = np.random.default_rng(61)
+    n, frames = 700, 9
+    scene_np = gv_synth.make_scene(rng, n, z=(2.0, 8.0), log_scale=(-4.2, 0.3), cubic=True, poly_cov=True, sh_degree=sh)
+    scene_np.means[0, :3 * n // 4] += 40.0
+    w = dict(scene=scene_np, camera=gv_synth.make_camera(64, 48, 64.0), poses=gv_synth.make_trajectory(rng, frames),
+             times=gv_synth.make_times(frames), frames=frames, n=n)
+    scene, cam, poses, times = device_inputs(w)
+    dl = torch.from_numpy(rng.normal(0, 1, (frames, 3, 48, 64)).astype(np.float32)).cuda()
+    wide = raster.Workspace(cam, n, frames, 4 * frames * n + 4096)
+    a = raster.render_batch(scene, cam, poses, times, wide, dL_dimages=dl)
+    torch.cuda.synchronize()
+    k = wide.status()["intersections"]
+    assert 0 < k < 1.5 * frames * n
+    tight = raster.Workspace(cam, n, frames, k)
+    b = raster.render_batch(scene, cam, poses, times, tight, dL_dimages=dl)
+    torch.cuda.synchronize()
+    assert tight.status()["overflow"] == 0
+    for name, g in a["grads"].items():
+        if g is not None:
+            assert torch.linalg.norm(g) > 0 and (
+                torch.linalg.norm(g - b["grads"][name]) <= 16 * 2.0 ** -24 * torch.linalg.norm(g)), name
