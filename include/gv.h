@@ -159,10 +159,12 @@ typedef struct {
  * take precedence, select kernels that first build per-pixel entry lists
  * from closed-form coverage masks;
  * bwd_batch: the backward's LDS batch (0 = same as batch).
- * Defaults: batch 128, sort_cap 1024, compact 52, bwd_batch 64.  While the
- * defaults or an autotuned setting are in force, launches of few tiles run
- * the one-quadrant-per-wave kernels in place of the one-wave-per-tile ones;
- * any other setting given to gv_set_tuning is taken as it is.  Images are
+ * Defaults: batch 128, sort_cap 1024, compact 52, bwd_batch 64.  Under the
+ * defaults, launches of few tiles run the one-quadrant-per-wave kernels in
+ * place of the one-wave-per-tile ones; under a setting that gv_autotune found,
+ * those of few tiles and fewer than it was tuned on do.  gv_set_tuning with the
+ * values of the defaults or of the last autotuned setting restores that
+ * setting; any other is taken as it is.  Images are
  * identical under every setting and gradients equal up to floating-point
  * rounding (order of summation, and the compacted backward's arithmetic);
  * only the speed differs. */
@@ -322,12 +324,15 @@ gv_status gv_fit_graph_create(const gv_scene *scene, const gv_camera *cam, const
  * width, height, N to a quarter octave, frames, parameter dtype, dynamics,
  * SH degree) and installs that line's setting without timing anything;
  * otherwise it times the options of each stage (forward kernel x LDS batch,
- * backward LDS batch, sort capacity: nine runs per round, three timed rounds
+ * backward LDS batch, sort capacity: twelve runs per round, three timed rounds
  * after a warm-up round, each stage keeping its own fastest option since no
  * stage's output depends on another's kernel) by running gv_render_batch on
  * the caller's buffers (overwriting its outputs; synchronises) and, with
  * cache_path, appends the choice as one JSON line.  `chosen` (host, or NULL)
- * receives the installed setting. */
+ * receives the installed setting; it runs as it was measured on launches of
+ * that many tiles and more (where it has the defaults' values on a launch of
+ * few tiles, which the defaults would give other kernels, bwd_batch says 128:
+ * its backward kernel ignores it). */
 gv_status gv_get_tuning(gv_tuning *out);
 gv_status gv_set_tuning(const gv_tuning *t);
 gv_status gv_autotune(const gv_scene *scene, const gv_camera *cam, const float *poses, const float *times,

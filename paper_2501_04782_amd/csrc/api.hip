@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <limits>
 #include <mutex>
 #include <new>
 
@@ -30,8 +31,10 @@ hipError_t launch_tile_scan(const Args& a, unsigned long long* tmp, hipStream_t 
 
 static thread_local int32_t g_last_hip = 0;
 static std::mutex g_tune_mu;
-constexpr Tuning DEFAULT_TUNE = {128, 1024, 64, 52, true};  // the autotuner's choice on the 960x540 benchmark clip
+// the autotuner's choice on the 960x540 benchmark clip
+constexpr Tuning DEFAULT_TUNE = {128, 1024, 64, 52, std::numeric_limits<int64_t>::max()};
 static Tuning g_tune = DEFAULT_TUNE;
+static Tuning g_autotuned = DEFAULT_TUNE;  // the last setting that gv_autotune installed
 
 Tuning current_tuning() {
     std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -41,6 +44,33 @@ Tuning current_tuning() {
 void install_tuning(const Tuning& t) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     g_tune = t;
+}
+
+static bool same_kernels(const Tuning& a, const Tuning& b) {
+    return a.batch == b.batch && a.sort_cap == b.sort_cap && a.bwd_batch == b.bwd_batch && a.compact == b.compact;
+}
+
+// The setting that gv_set_tuning's four values stand for: the defaults and the
+// last autotuned setting with the launches they adapt to, so that saving and
+// restoring them changes nothing, any other as it is.
+static void install_values(Tuning t) {
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    t.adapt_below = same_kernels(t, DEFAULT_TUNE)  ? DEFAULT_TUNE.adapt_below
+                    : same_kernels(t, g_autotuned) ? g_autotuned.adapt_below
+                                                   : 0;
+    g_tune = t;
+}
+
+// Installs the setting measured fastest on launches of `tiles` tiles; on
+// those, and larger ones, it runs as it was measured.  Where it has the values
+// of the defaults, and they would run other kernels there, it is named by
+// another bwd_batch: the one-wave adjoint runs batches of 64 whatever that says.
+static Tuning install_autotuned(Tuning t, int64_t tiles) {
+    if (same_kernels(t, DEFAULT_TUNE) && tiles <= FWD_QUADRANT_ITEMS) t.bwd_batch = 128;
+    t.adapt_below = tiles;
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    g_tune = g_autotuned = t;
+    return t;
 }
 
 static inline size_t align_up(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
@@ -696,10 +726,7 @@ gv_status gv_set_tuning(const gv_tuning* t) {
     n.bwd_batch = t->bwd_batch ? t->bwd_batch : t->batch;
     n.sort_cap = t->sort_cap;
     n.compact = t->compact;
-    // setting the defaults again restores the process's initial state
-    n.adaptive = n.batch == DEFAULT_TUNE.batch && n.bwd_batch == DEFAULT_TUNE.bwd_batch &&
-                 n.sort_cap == DEFAULT_TUNE.sort_cap && n.compact == DEFAULT_TUNE.compact;
-    install_tuning(n);
+    install_values(n);
     return GV_OK;
 }
 
@@ -768,9 +795,9 @@ gv_status gv_autotune(const gv_scene* scene, const gv_camera* cam, const float* 
         key.sh_degree = scene->sh_degree;
     }
     Tuning best = current_tuning();
+    const int64_t tiles = static_cast<int64_t>((cam->width + TILE - 1) / TILE) * ((cam->height + TILE - 1) / TILE) * frames;
     if (cache_path && cached_tuning(cache_path, key, best) && tuning_valid(best)) {
-        best.adaptive = true;
-        install_tuning(best);
+        best = install_autotuned(best, tiles);
         if (chosen) {
             memset(chosen, 0, sizeof(*chosen));
             chosen->batch = best.batch;
@@ -821,7 +848,7 @@ gv_status gv_autotune(const gv_scene* scene, const gv_camera* cam, const float* 
             t.batch = batches[fc % 3];
             t.bwd_batch = b_batch[c % NB];
             t.sort_cap = caps[c % NS];
-            t.adaptive = false;  // time the kernel named
+            t.adapt_below = 0;  // time the kernel named
             install_tuning(t);
             gv_status s = enqueue_batch(scene, cam, poses, times, frames, targets, nullptr, flags, images, loss,
                                         grads, dL_dposes, ws, ws_bytes, st, &tm);
@@ -857,9 +884,9 @@ gv_status gv_autotune(const gv_scene* scene, const gv_camera* cam, const float* 
         best.batch = batches[bf % 3];
         best.bwd_batch = b_batch[bb];
         best.sort_cap = caps[bs];
-        best.adaptive = true;
     }
-    install_tuning(result == GV_OK ? best : saved);
+    if (result == GV_OK) best = install_autotuned(best, tiles);
+    else install_tuning(saved);
     for (int i = 0; i < made && i <= GV_STAGES; ++i) hipEventDestroy(tm.ev[i]);
     hipStreamDestroy(st);
     if (result != GV_OK) return result;

@@ -1820,9 +1820,9 @@ __global__ __launch_bounds__(WG) void k_composite_fwd_sb(Args a) {
 //  8,160 (four)                       170 -> 129     345 -> 364 / 314
 //  8,160 (1920x1080, 500k)            116 -> 116     251 -> 337 / 281
 // 16,320 (960x540, 200k, 8 frames)    249 -> 274     549 -> 845 / 675
-constexpr int64_t FWD_QUADRANT_ITEMS = 8192;
-constexpr int64_t BWD_QUADRANT_ITEMS = 6144;
+constexpr int64_t BWD_QUADRANT_ITEMS = 6144;  // forward: FWD_QUADRANT_ITEMS
 constexpr int64_t BWD_QUADRANT_ITEMS_256 = 3072;
+static_assert(BWD_QUADRANT_ITEMS_256 <= BWD_QUADRANT_ITEMS && BWD_QUADRANT_ITEMS <= FWD_QUADRANT_ITEMS, "the last line");
 
 static int64_t items(const Args& a) { return static_cast<int64_t>(a.tiles) * a.frames; }
 
@@ -1842,7 +1842,7 @@ hipError_t launch_composite_fwd(const Args& a, hipStream_t stream) {
         }
         return hipGetLastError();
     }
-    if ((c & 32) && a.tune.adaptive && items(a) <= FWD_QUADRANT_ITEMS) {
+    if ((c & 32) && items(a) < a.tune.adapt_below && items(a) <= FWD_QUADRANT_ITEMS) {
         c = 4;
         batch = 256;
     }
@@ -1911,7 +1911,7 @@ hipError_t launch_composite_bwd(const Args& a, hipStream_t stream) {
         return hipGetLastError();
     }
     int c = a.tune.compact, batch = a.tune.bwd_batch;
-    if ((c & 16) && a.tune.adaptive && items(a) <= BWD_QUADRANT_ITEMS) {
+    if ((c & 16) && items(a) < a.tune.adapt_below && items(a) <= BWD_QUADRANT_ITEMS) {
         c = 0;
         batch = items(a) <= BWD_QUADRANT_ITEMS_256 ? 256 : 128;
     }

@@ -74,6 +74,11 @@ struct __align__(16) ColorOp {
 // left to the merge sort).
 enum : int { ST_OVERFLOW = 0, ST_NONFINITE = 1, ST_K_LO = 2, ST_K_HI = 3, ST_SLOTS = 4, ST_CROWDED = 5, ST_WORDS = 16 };
 
+// Tiles (over all frames) up to which the forward of a setting that adapts to
+// small launches runs the quadrant kernels (the sweep is beside the launchers of
+// the compositing kernels).
+constexpr int64_t FWD_QUADRANT_ITEMS = 8192;
+
 struct Tuning {
     int batch;      // 64 / 128 / 256 entries per LDS round of the forward compositing kernel
     int sort_cap;   // 512 / 1024 / 2048 / 4096
@@ -81,8 +86,9 @@ struct Tuning {
     int compact;    // bit 0 / bit 1: compacted forward / backward compositing (coverage masks + per-lane entry
                     // walks); else bit 2: quadrant forward (clear: 4x4-block forward); bit 4 / bit 3: the
                     // backward walks four / two quadrant lists per wave (clear: one)
-    bool adaptive;  // launches too small for the one-wave kernels take the quadrant kernels instead (the built-in
-                    // defaults and an autotuned setting; clear: a caller's own setting, taken as given)
+    int64_t adapt_below;  // launches of fewer tiles (over all frames) that are too small for the one-wave kernels
+                          // take the quadrant kernels instead: every launch for the built-in defaults, those
+                          // smaller than the tuned one for an autotuned setting, none for a caller's own
 };
 
 // Byte offsets of the workspace regions (host-computed).
