@@ -30,9 +30,11 @@ constexpr float K_EXP = -0.72134752044448170368f;
 constexpr double BIN_Q_SLACK = 9.0 * (1.0 + 1e-5) + 1e-6;
 constexpr float SUB_Q_SLACK = 9.0f * (1.0f + 1e-4f) + 1e-4f;
 
+// Dies with an L2 each, to which a launch's workgroups are dealt in turn.
+constexpr int XCDS = 8;
+
 // Gaussians per workgroup of the LDS-histogram binning kernels (small launches
 // take 256), and the largest tile grid whose histogram fits in LDS (64 KiB).
-constexpr int XCDS = 8;  // dies with an L2 each; workgroups are dealt to them in turn
 constexpr int BIN_GROUP = 1024;
 constexpr int LDS_TILE_LIMIT = 16384;
 
@@ -204,6 +206,22 @@ struct Args {
 // ---------------------------------------------------------------------------
 // device helpers
 // ---------------------------------------------------------------------------
+
+// Work order of the kernels that read a Gaussian's parameters in every frame
+// (about 200 bytes with dynamics or SH): each XCD takes a contiguous eighth of
+// the (block of Gaussians, frame) pairs, every frame of a block before the next
+// block, so that a block's parameters come into one L2, once.  (With the blocks
+// dealt to the XCDs in turn, few blocks left most XCDs idle: projection of 1,000
+// frames of 2,000 Gaussians 394 us, 124 us so.)  False for the workgroups that
+// pad the grid to a multiple of XCDS.
+__host__ __device__ __forceinline__ int xcd_share(int blocks, int frames) { return (blocks * frames + XCDS - 1) / XCDS; }
+__device__ __forceinline__ bool block_and_frame(int blocks, int frames, int& block, int& f) {
+    const int id = static_cast<int>(blockIdx.x);
+    const int item = id % XCDS * xcd_share(blocks, frames) + id / XCDS;
+    block = item / frames;
+    f = item - block * frames;
+    return block < blocks;
+}
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
     return __uint_as_float(static_cast<uint32_t>(h) << 16);

@@ -254,13 +254,9 @@ struct WaveCells {
 // are also recorded as a row-major mask over its rectangle (rectangles of at
 // most 64 tiles), which the scatter walks.
 //
-// Work order with dynamics or SH: workgroups are dealt to the 8 XCDs in turn,
-// and each XCD takes the blocks of Gaussians b = xcd mod 8 one after the other,
-// every frame of a block before the next block, so that a block's parameters
-// (about 200 bytes per Gaussian) come into that XCD's L2 once and not once per
-// frame: B-spline clip 1,050 -> 948 us, SH clip 937 -> 898 us.  Static scenes
-// (76 bytes) keep the frame-major order: 425 us against 448, and 1,349 against
-// 1,564 us at 1080p.
+// Work order with dynamics or SH (block_and_frame): B-spline clip 1,050 -> 948
+// us, SH clip 937 -> 898 us.  Static scenes (76 bytes) keep the frame-major
+// order: 425 us against 448, and 1,349 against 1,564 us at 1080p.
 template <bool DYN, bool SH, typename T>
 __global__ __launch_bounds__(256) void k_project_lds(Args a) {
     extern __shared__ uint32_t hist[];
@@ -270,11 +266,8 @@ __global__ __launch_bounds__(256) void k_project_lds(Args a) {
     __shared__ uint32_t wtotal[ROUNDS][4];
     __shared__ uint32_t slot0;
     static_assert(LDS_TILE_LIMIT <= 0xffff, "16-bit counts");
-    const int turn = static_cast<int>(blockIdx.x) / XCDS;
-    constexpr bool EXT = DYN || SH;
-    const int f = EXT ? turn % a.frames : blockIdx.y;
-    const int block = EXT ? turn / a.frames * XCDS + static_cast<int>(blockIdx.x % XCDS) : blockIdx.x;
-    if (EXT && block >= a.bin_blocks) return;
+    int block = blockIdx.x, f = blockIdx.y;
+    if ((DYN || SH) && !block_and_frame(a.bin_blocks, a.frames, block, f)) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int words = (a.tiles + 1) >> 1;
     for (int t = threadIdx.x; t < words; t += 256) hist[t] = 0u;
@@ -754,7 +747,7 @@ static void launch_projection(const Args& a, hipStream_t stream) {
     }
     const size_t lds = sizeof(uint32_t) * ((a.tiles + 1) / 2);
     const uint32_t blocks = static_cast<uint32_t>(a.bin_blocks), frames = static_cast<uint32_t>(a.frames);
-    const dim3 grid = DYN || SH ? dim3((blocks + XCDS - 1) / XCDS * XCDS * frames) : dim3(blocks, frames);
+    const dim3 grid = DYN || SH ? dim3(XCDS * xcd_share(a.bin_blocks, a.frames)) : dim3(blocks, frames);
     hipLaunchKernelGGL((k_project_lds<DYN, SH, T>), grid, block, lds, stream, a);
 }
 

@@ -669,10 +669,8 @@ __device__ __forceinline__ void sh_direction_adjoint(const Args& a, int64_t g, c
 template <bool DYN, bool SH, typename T>
 __global__ __launch_bounds__(256) void k_adjoint_frames(Args a, FrameStore store) {
     if (overflowed(a.status)) return;
-    // every frame of a block of Gaussians on one XCD, as in the projection
-    const int turn = static_cast<int>(blockIdx.x) / XCDS;
-    const int f = turn % a.frames, block = turn / a.frames * XCDS + static_cast<int>(blockIdx.x % XCDS);
-    if (block >= store.blocks) return;
+    int block, f;
+    if (!block_and_frame(store.blocks, a.frames, block, f)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t n = a.n, g = static_cast<int64_t>(block) * 256 + tid;
     __shared__ float cam[15];  // R, t, centre
@@ -1377,7 +1375,7 @@ static bool launch_two_kernels(const Args& a, FrameStore& store, hipStream_t str
     store.lo_frames = static_cast<int>(fit < a.frames ? fit : a.frames);
     store.blocks = static_cast<int>(blocks);
     store.intr = a.pose_part + blocks * a.frames * 12;
-    const dim3 grid(static_cast<uint32_t>((blocks + XCDS - 1) / XCDS * XCDS * a.frames));
+    const dim3 grid(XCDS * xcd_share(store.blocks, a.frames));
     hipLaunchKernelGGL((k_adjoint_frames<DYN, SH, T>), grid, dim3(256), 0, stream, a, store);
     hipLaunchKernelGGL((k_adjoint_sum<DYN, SH, T>), dim3(static_cast<uint32_t>((a.n + 127) / 128)), dim3(128), 0, stream,
                        a, store);
