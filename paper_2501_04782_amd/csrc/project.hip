@@ -417,10 +417,16 @@ struct WaveKeys {
 // write some 100 MB): 28 M write requests for the 30 M keys of the 50-frame
 // 960x540 clip of 200k Gaussians, most of 32 bytes, and 446 us, with three
 // workgroups on a CU as with eight.  So the workgroup collects its keys in LDS
-// in order of the tiles, 8 bytes each, and writes a tile's run at once (25 keys
-// there): 335 us; 24 frames of 400k 452 -> 341.  For tile grids of up to
-// STAGE_TILES tiles, whose tables leave room for two workgroups of eight waves
-// on a CU; a workgroup with more than STAGE_KEYS keys writes them one by one.
+// in order of the tiles, 8 bytes each, and writes a tile's run (three keys
+// there) in one go: 335 us; 24 frames of 400k 452 -> 341.  For tile grids of up
+// to STAGE_TILES tiles, whose tables leave room for two workgroups of eight
+// waves on a CU; a workgroup with more than STAGE_KEYS keys writes them one by
+// one.  On few tiles the runs are long enough to fill lines either way, and
+// the collecting costs more than it saves: 666 frames of 1,843 Gaussians on 24
+// tiles 47 us collected against 37, 250 of 4,915 on 64 tiles 46 against 41, 111
+// of 11,059 on 144 tiles 49 against 53 (of smaller Gaussians 37 against 34), 53 of
+// 23,040 on 300 tiles 65 against 88.
+constexpr int STAGE_TILES_FROM = 128;
 constexpr int STAGE_TILES = 2304;
 constexpr int STAGE_KEYS = 5120;
 constexpr int STAGE_THREADS = 512;
@@ -778,7 +784,7 @@ hipError_t launch_scatter(const Args& a, hipStream_t stream) {
     if (a.bhist) {
         const dim3 grid(static_cast<uint32_t>(a.bin_blocks), a.frames);
         const size_t lds = sizeof(uint32_t) * a.tiles;
-        if (a.tiles <= STAGE_TILES && a.bin_rounds == BIN_GROUP / 256)
+        if (a.tiles >= STAGE_TILES_FROM && a.tiles <= STAGE_TILES && a.bin_rounds == BIN_GROUP / 256)
             hipLaunchKernelGGL(k_scatter_lds<true>, grid, dim3(STAGE_THREADS), lds, stream, a);
         else
             hipLaunchKernelGGL(k_scatter_lds<false>, grid, dim3(256), lds, stream, a);

@@ -334,3 +334,10 @@ def test_pyramid_of_small_planes(H, W, planes):
         for lvl in range(1, 4):
             assert torch.equal(got[lvl][p], one[lvl]), (p, lvl)
             np.testing.assert_allclose(got[lvl][p].cpu().numpy(), ref[lvl][0], rtol=0, atol=(lvl + 1) * 10 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("tiles_x,tiles_y,n,frames", [(6, 4, 1843, 70), (127, 1, 1100, 70), (16, 8, 1100, 70)])
+def test_scatter_on_few_tiles(tiles_x, tiles_y, n, frames):
+    """The same on few tiles, where the keys are not collected, the most of them
+    and the fewest where they are."""
+    test_scatter_of_collected_keys(tiles_x, tiles_y, n, frames, (-3.0, 0.5))
