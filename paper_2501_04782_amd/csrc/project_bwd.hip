@@ -420,7 +420,13 @@ __device__ __forceinline__ void sigma_gradient_f64(const Args& a, const double* 
 // 544 -> 526 us on the 50-frame 960x540 clip, 1,869 -> 1,648 us on the 32-frame
 // 1080p clip with cubic means.  (Staging a wave's records through LDS in
 // coalesced reads cut the loads to a quarter but took twice the VALU: 613 us.)
-template <int SPLIT, bool CUBIC, typename T>
+//
+// LARGE: for up to three frames of Gaussians of many tiles (large_gaussians), a
+// wave per frame and, after the first, rounds of eight records, which halve the
+// chain of a lane's dependent rounds but leave two waves per SIMD: two 960x540
+// frames of 20k Gaussians of 29 tiles 97 -> 60 us, three 139 -> 64; of 200k of four
+// tiles 47 and 59 us with rounds of four in one wave, 55 and 80 so.
+template <int SPLIT, bool CUBIC, typename T, bool LARGE>
 __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
     if (overflowed(a.status)) return;
     constexpr int FC = 16;  // frames whose cameras and pose sums are in LDS
@@ -429,7 +435,7 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
     // twelve frames it changes the quaternion gradient's error by 3 % (median of
     // 30 scenes), and with cubic means its registers would leave two waves per
     // SIMD (1080p clip 1,641 -> 1,815 us).
-    constexpr bool SIGMA_F64 = SPLIT == 1;
+    constexpr bool SIGMA_F64 = SPLIT < 4;
     __shared__ double camd[SIGMA_F64 ? SPLIT : 1][SIGMA_F64 ? FC : 1][12];
     __shared__ float cam[SPLIT][FC][12], wpose[SPLIT][FC][12];
     __shared__ double red[SPLIT][64];
@@ -512,11 +518,21 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
                 P.A[1] = rec.y;
                 P.A[2] = rec.z;
                 double s[PART] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-                for (uint32_t k0 = 0;;) {
-                    R.add(base, cnt, k0, s);
-                    k0 += PU;
-                    if (k0 >= cnt) break;
-                    R.load(a, base, cnt, k0);
+                if constexpr (LARGE) {
+                    R.add(base, cnt, 0u, s);
+#pragma unroll 1
+                    for (uint32_t k0 = PU; k0 < cnt; k0 += 8) {
+                        PartialRound<8> M;
+                        M.load(a, base, cnt, k0);
+                        M.add(base, cnt, k0, s);
+                    }
+                } else {
+                    for (uint32_t k0 = 0;;) {
+                        R.add(base, cnt, k0, s);
+                        k0 += PU;
+                        if (k0 >= cnt) break;
+                        R.load(a, base, cnt, k0);
+                    }
                 }
                 float d[PART];
                 for (int k = 0; k < PART; ++k) d[k] = static_cast<float>(s[k]);
@@ -606,7 +622,7 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
 }
 
 // ---------------------------------------------------------------------------
-// The adjoint with dynamics or SH, in two kernels.  One lane per (frame,
+// The adjoint with dynamics or SH, or of large Gaussians, in two kernels.  One lane per (frame,
 // Gaussian) takes the chain rule down to the frame's parameter values and
 // stores them (k_adjoint_frames); one lane per Gaussian then sums them over the
 // frames in FP64 with the frames' weights (k_adjoint_sum).  In one kernel, the
@@ -614,12 +630,13 @@ __global__ __launch_bounds__(64 * SPLIT) void k_adjoint_static(Args a) {
 // chip at one wave per SIMD, waiting on a Gaussian's records frame after frame:
 // on the 50-frame 960x540 clip of 200k Gaussians 2,180 us with B-spline
 // means and cubic covariance, 1,035 us so; 1,430 -> 822 us with SH of degree 3.
-// (Without either, one kernel with its 14 sums in registers is faster: 519 us
-// against 703, and 1,634 against 2,096 us on the 1080p clip.)  The stored values
-// cost 2 x 56 bytes per (frame, Gaussian); they lie in the sort's key
-// buffers, which nothing reads after the sort.  Where those are too small (less
-// than 1.75 intersections of capacity per (frame, Gaussian)) the one-kernel form
-// below runs.
+// (Without either, one kernel with its 14 sums in registers is faster, 519 us
+// against 703, and 1,634 against 2,096 us on the 1080p clip, unless Gaussians are
+// large and few, see large_gaussians.)  The stored values cost twice their 52 to
+// 68 bytes per (frame, Gaussian); they lie in the sort's key buffers, which
+// nothing reads after the sort.  Where those are too small (less than 1.625
+// intersections of capacity per (frame, Gaussian) with SH, 1.75 with dynamics,
+// 2.125 with both) the one-kernel form below runs.
 // ---------------------------------------------------------------------------
 template <bool DYN, bool SH>
 constexpr int frame_values() { return (DYN ? 14 : 13) + (DYN && SH ? 3 : 0); }
@@ -1328,6 +1345,20 @@ __global__ __launch_bounds__(64) void k_intr_frames(Args a, int64_t n_blocks, co
     else a.g_intr[threadIdx.x] = g;
 }
 
+// Do the Gaussians meet many tiles each?  The host knows the workspace's
+// capacity, which callers size to their scene; where it is generous the forms
+// for large Gaussians give the same results up to the order of sums, more slowly.
+// Above the line the static adjoint of few frames takes LARGE, and of four and
+// more the two-kernel form, whose lanes are (frame, Gaussian) pairs, which fill
+// the chip with fewer Gaussians: 50 960x540 frames of 20k Gaussians of 33 tiles
+// 1,094 us in one kernel, 580 in two, of 50k of 15 tiles 860 and 644, 500 640x360
+// frames of 100 of 41 tiles 6,159 and 341, 12 960x540 frames of 80k of 16 tiles 319
+// and 274; 16 1080p frames of 500k of ten tiles 1,068 and 1,202, 50 960x540 frames
+// of 200k of ten tiles 1,534 and 1,563, of four 620 and 808.
+static bool large_gaussians(const Args& a) {
+    return a.k_cap / ((a.n <= 65536 ? 16 : 32) * static_cast<int64_t>(a.frames)) >= a.n;
+}
+
 // Gaussians per workgroup of each variant.
 template <bool DYN, bool SH>
 constexpr int pb_gaussians() { return pb_threads<DYN, SH>() / pb_split<DYN, SH>(); }
@@ -1347,16 +1378,21 @@ static int64_t blocks_for(int64_t n, bool dyn, bool sh) {
     return (n + gpb - 1) / gpb;
 }
 
+template <int SPLIT, bool LARGE, typename T>
+static void launch_static_split(const Args& a, dim3 grid, hipStream_t stream) {
+    const dim3 block(64 * SPLIT);
+    if (a.mean_coeffs) hipLaunchKernelGGL((k_adjoint_static<SPLIT, true, T, LARGE>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((k_adjoint_static<SPLIT, false, T, LARGE>), grid, block, 0, stream, a);
+}
+
 template <typename T>
 static void launch_static(const Args& a, dim3 grid, hipStream_t stream) {
     // four parts of the frames per 64 Gaussians where there are four frames
-    if (a.frames >= 4) {
-        if (a.mean_coeffs) hipLaunchKernelGGL((k_adjoint_static<4, true, T>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((k_adjoint_static<4, false, T>), grid, dim3(256), 0, stream, a);
-    } else {
-        if (a.mean_coeffs) hipLaunchKernelGGL((k_adjoint_static<1, true, T>), grid, dim3(64), 0, stream, a);
-        else hipLaunchKernelGGL((k_adjoint_static<1, false, T>), grid, dim3(64), 0, stream, a);
-    }
+    if (a.frames >= 4) launch_static_split<4, false, T>(a, grid, stream);
+    else if (!large_gaussians(a)) launch_static_split<1, false, T>(a, grid, stream);
+    else if (a.frames == 3) launch_static_split<3, true, T>(a, grid, stream);
+    else if (a.frames == 2) launch_static_split<2, true, T>(a, grid, stream);
+    else launch_static_split<1, true, T>(a, grid, stream);
 }
 
 // The two-kernel form of the adjoint with dynamics or SH, if the store fits in
@@ -1401,7 +1437,10 @@ static void launch_adjoint_as(const Args& a, int64_t& nb, double*& frame_intr, h
     if (dyn && sh) launch_adjoint<true, true, T>(a, nb, frame_intr, stream);
     else if (dyn) launch_adjoint<true, false, T>(a, nb, frame_intr, stream);
     else if (sh) launch_adjoint<false, true, T>(a, nb, frame_intr, stream);
-    else {
+    else if (FrameStore store; a.frames >= 4 && large_gaussians(a) && launch_two_kernels<false, false, T>(a, store, stream)) {
+        nb = store.blocks;
+        frame_intr = store.intr;
+    } else {
         nb = blocks_for(a.n, false, false);
         launch_static<T>(a, dim3(static_cast<uint32_t>(nb)), stream);
     }

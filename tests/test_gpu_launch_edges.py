@@ -341,3 +341,28 @@ def test_scatter_on_few_tiles(tiles_x, tiles_y, n, frames):
     """The same on few tiles, where the keys are not collected, the most of them
     and the fewest where they are."""
     test_scatter_of_collected_keys(tiles_x, tiles_y, n, frames, (-3.0, 0.5))
+
+
+@pytest.mark.parametrize("frames", [1, 2, 3, 4, 9])
+@pytest.mark.parametrize("n,cubic", [(63, False), (65, False), (257, True)])
+def test_adjoint_of_large_gaussians(n, cubic, frames):
+    """A capacity of many tiles per Gaussian takes the static adjoint's forms for
+    large Gaussians (up to three frames, and four and more), one of fewer the
+    others, which the other tests hold against the oracle: the same gradients but
+    for the order of FP32 sums of 64 and of FP64 sums."""
+    w = small_workload(70 + n, 128, 112, n, frames, trajectory=True, cubic=cubic, z=(2.0, 6.0), ls=(-2.1, 0.4))
+    scene, cam, poses, times = device_inputs(w)
+    dl = torch.from_numpy(np.random.default_rng(n).normal(0, 1, (frames, 3, 112, 128)).astype(np.float32)).cuda()
+    out = []
+    for k in (16 * frames * n, 15 * frames * n):
+        ws = raster.Workspace(cam, n, frames, k)
+        out.append(raster.render_batch(scene, cam, poses, times, ws, dL_dimages=dl))
+        torch.cuda.synchronize()
+        assert ws.status()["overflow"] == 0
+    a, b = out
+    assert torch.equal(a["images"], b["images"])
+    tol = 64 * 2.0 ** -24
+    assert torch.linalg.norm(a["dL_dposes"] - b["dL_dposes"]) <= tol * torch.linalg.norm(a["dL_dposes"])
+    for name, g in a["grads"].items():
+        if g is not None:
+            assert torch.linalg.norm(g - b["grads"][name]) <= tol * torch.linalg.norm(g), name
