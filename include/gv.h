@@ -142,8 +142,9 @@ typedef struct {
  * batch: entries staged in LDS per round of a tile's compositing loop
  * (64, 128 or 256); sort_cap: run length of the per-tile sort
  * (512, 1024, 2048 or 4096): lists of up to twice that (at most 4096) are
- * sorted by depth bins in LDS, longer ones through memory, and lists whose
- * depths crowd in a bin by merging LDS-sorted runs of that length;
+ * sorted by depth bins in LDS (up to 64 entries by comparison), longer ones
+ * through memory, and lists whose depths crowd in a few bins by finer bins or
+ * by merging LDS-sorted runs of that length;
  * compact: compositing kernel choice, 0..63.  With bit 2 set the forward lets
  * each wave walk the entries meeting its 8x8 quadrant; with it clear each
  * 16-lane row of a wave walks the entries meeting its 4x4 pixel block; with

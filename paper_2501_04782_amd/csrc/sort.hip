@@ -5,6 +5,7 @@
 // (depth, ties by lower index) whatever order the atomics of the scatter
 // produced and whichever of the ways below sorts it:
 //
+// * by comparison in one wave (buckets of up to 64 keys);
 // * by depth bins in LDS (buckets of up to 2,048 keys at the default setting)
 //   or in the merge scratch (longer ones);
 // * where more than BIN_KEYS keys fall in one bin (a surface, clusters and
@@ -20,9 +21,14 @@
 // kept to eight waves per SIMD.  Merging alone took 445 us on the 50-frame
 // 960x540 clip of 200k Gaussians, 1,485 us on the 32-frame 1080p clip of 500k
 // and 800 us on 24 frames of 400k (buckets beyond 2,048 keys); by bins 295, 960
-// and 490 us.  Eight 540p frames of 200k with 80 % of the depths on a wavy
-// surface 144 against 111 us, all depths equal 107 against 54; half the depths
-// within 0.001 and half spread, the worst found, 139 against 250 us.
+// and 490 us.  500 frames of 100 Gaussians (four keys to a bucket) 360 us, by bins
+// 493, 200 in one wave.  Eight 540p frames of 200k with 80 % of the depths on a wavy
+// surface 148 against 106 us, all depths equal 107 against 56.  Two crowds cost
+// more than merging alone would: half the depths within 0.001 and half spread 138
+// against 214 us, all within 1e-5 (21 values) 137 against 205; the attempt by depth
+// bins takes 60 of them, putting the keys in the scratch 70.  (In registers, fine
+// bins or bins split where they crowd spill at eight waves per SIMD, which costs
+// every bucket 40 % and more; leaving crowds to the merges at once 257.)
 #include "gv_internal.h"
 
 #include <algorithm>
@@ -321,7 +327,7 @@ __device__ __forceinline__ uint32_t scan_bins(uint32_t* bins, int log_nb, uint32
 
 constexpr int64_t MERGE_GROUPS = 1536;  // six per CU, as many as are resident
 
-// A bin with more keys than this costs as much as the merges.
+// Most keys of a bin, each of which is compared with the others.
 constexpr uint32_t BIN_KEYS = 64;
 
 // Words of LDS that a sort of buckets of up to CAP keys takes: the bins, and
@@ -349,13 +355,13 @@ struct FineBins {
         return min(static_cast<int>((static_cast<float>(s) + f * static_cast<float>(cnt)) * per_key), last);
     }
 };
-constexpr int FINE_WORDS = 5 * 256;  // FineBins' tables, in front of the bins
+constexpr int FINE_WORDS = 5 * 256;  // FineBins' tables
 
 // Fills the coarse tables in `lds` from the keys that for_keys passes to its
-// argument and clears 2^log_nb fine bins behind them.  Ends with a barrier.
+// argument and clears the 2^log_nb fine bins.  Ends with a barrier.
 template <typename ForKeys>
-__device__ __forceinline__ FineBins fine_bins(uint32_t* lds, uint32_t* red, DepthBins coarse, uint32_t n, int log_nb,
-                                              const ForKeys& for_keys) {
+__device__ __forceinline__ FineBins fine_bins(uint32_t* lds, uint32_t* bins, uint32_t* red, DepthBins coarse, uint32_t n,
+                                              int log_nb, const ForKeys& for_keys) {
     static_assert(WG == 256, "a thread per coarse bin");
     const int t = static_cast<int>(threadIdx.x);
     unsigned long long* lo = reinterpret_cast<unsigned long long*>(lds);
@@ -365,12 +371,12 @@ __device__ __forceinline__ FineBins fine_bins(uint32_t* lds, uint32_t* red, Dept
     lo[t] = ~0ull;
     hi[t] = 0ull;
     start[t] = 0u;
-    for (int b = t; b < 1 << log_nb; b += WG) lds[FINE_WORDS + b] = 0u;
+    for (int b = t; b < 1 << log_nb; b += WG) bins[b] = 0u;
     __syncthreads();
     for_keys([&](uint64_t x) {
         const int c = coarse(x);
-        atomicMin(&lo[c], static_cast<unsigned long long>(x));
-        atomicMax(&hi[c], static_cast<unsigned long long>(x));
+        if (x < lo[c]) atomicMin(&lo[c], static_cast<unsigned long long>(x));  // (atomics of a crowd wait for each other)
+        if (x > hi[c]) atomicMax(&hi[c], static_cast<unsigned long long>(x));
         atomicAdd(&start[c], 1u);
     });
     __syncthreads();
@@ -446,14 +452,20 @@ __device__ __forceinline__ bool bin_sort_lds(const Args& a, uint32_t s, int n, u
 }
 
 // The same for a longer bucket, or by fine bins: the keys are put in order of
-// their bins in the merge scratch, and each is then compared with its bin's keys
-// there.
+// their bins in the merge scratch, and each is then compared with its bin's keys:
+// there, or, for buckets by fine bins of up to FINE_KEYS keys, in LDS (a dozen
+// keys to a bin: eight 540p frames with half the depths within 0.001 251 us with
+// every comparison a load from the scratch, 224 so).
+constexpr int FINE_KEYS = 1536;
 template <bool FINE>
 __device__ __forceinline__ bool bin_sort_global(const Args& a, uint32_t s, int64_t n, uint32_t* lds, uint32_t* red) {
-    constexpr int LOG_NB = 12, LOG_FINE = 11;
+    constexpr int LOG_NB = 12, LOG_FINE = 11, LOG_LDS = 10;
+    static_assert(2 * FINE_KEYS + (1 << LOG_LDS) <= 4096 && FINE_WORDS <= 2 * FINE_KEYS, "keys, and bins behind them");
+    if (n > static_cast<int64_t>(BIN_KEYS) << (FINE ? LOG_FINE : LOG_NB)) return false;  // some bin has more
     const int t = static_cast<int>(threadIdx.x);
     const KeySlot* src = a.kv + s;
     KeySlot* dst = a.tkv + s;
+    const bool in_lds = FINE && n <= FINE_KEYS;
     auto for_keys = [&](const auto& each) {
         for (int64_t i = t; i < n; i += WG) each(src[i].key);
     };
@@ -463,16 +475,24 @@ __device__ __forceinline__ bool bin_sort_global(const Args& a, uint32_t s, int64
         if (scan_bins(bins, log_nb, red + 2 * (WG / 64)) > BIN_KEYS) return false;
         __syncthreads();
         for (int64_t i = t; i < n; i += WG) {
-            const KeySlot e = src[i];
-            dst[atomicAdd(&bins[bin_of(e.key)], 1u)] = e;
+            KeySlot e = src[i];
+            e.pad = static_cast<uint32_t>(bin_of(e.key));
+            dst[atomicAdd(&bins[e.pad], 1u)] = e;
         }
         __syncthreads();  // bins[b] is now the end of bin b
+        uint64_t* keys = reinterpret_cast<uint64_t*>(lds);
+        if (in_lds) {
+            for (int i = t; i < static_cast<int>(n); i += WG) keys[i] = dst[i].key;
+            __syncthreads();
+        }
         for (int64_t i = t; i < n; i += WG) {
             const KeySlot e = dst[i];
-            const int b = bin_of(e.key);
-            const uint32_t first = b ? bins[b - 1] : 0u, end = bins[b];
+            const uint32_t first = e.pad ? bins[e.pad - 1] : 0u, end = bins[e.pad];
             uint32_t r = first;
-            for (uint32_t k = first; k < end; ++k) r += dst[k].key < e.key ? 1u : 0u;
+            if (in_lds)
+                for (uint32_t k = first; k < end; ++k) r += keys[k] < e.key ? 1u : 0u;
+            else
+                for (uint32_t k = first; k < end; ++k) r += dst[k].key < e.key ? 1u : 0u;
             a.sgid[s + r] = static_cast<uint32_t>(e.key);
             a.sslot[s + r] = e.slot;
         }
@@ -480,10 +500,29 @@ __device__ __forceinline__ bool bin_sort_global(const Args& a, uint32_t s, int64
     };
     if (FINE) {
         const DepthBins B = depth_bins(8, red, for_keys);
-        return place(lds + FINE_WORDS, LOG_FINE, fine_bins(lds, red, B, static_cast<uint32_t>(n), LOG_FINE, for_keys));
+        const int log_nb = in_lds ? LOG_LDS : LOG_FINE;
+        uint32_t* bins = lds + (in_lds ? 2 * FINE_KEYS : FINE_WORDS);
+        return place(bins, log_nb, fine_bins(lds, bins, red, B, static_cast<uint32_t>(n), log_nb, for_keys));
     }
     for (int b = t; b < 1 << LOG_NB; b += WG) lds[b] = 0u;
     return place(lds, LOG_NB, depth_bins(LOG_NB, red, for_keys));
+}
+
+// A bucket of at most a wave's lanes: each lane counts the smaller keys.
+__device__ __forceinline__ void wave_sort(const Args& a, uint32_t s, int n) {
+    const int lane = static_cast<int>(threadIdx.x);
+    KeySlot e = {};
+    if (lane < n) e = a.kv[s + lane];
+    const uint32_t lo = static_cast<uint32_t>(e.key), hi = static_cast<uint32_t>(e.key >> 32);
+    uint32_t r = 0u;
+    for (int k = 0; k < n; ++k) {
+        const uint64_t x = static_cast<uint64_t>(__builtin_amdgcn_readlane(hi, k)) << 32 | __builtin_amdgcn_readlane(lo, k);
+        r += x < e.key ? 1u : 0u;
+    }
+    if (lane < n) {
+        a.sgid[s + r] = lo;
+        a.sslot[s + r] = e.slot;
+    }
 }
 
 // One workgroup per bucket.  A bucket whose keys crowd even in one of the fine
@@ -496,6 +535,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(CAP <= 2048 
     bucket_range(a, seg, s, e);
     if (e <= s) return;
     const uint32_t n = e - s;
+    if (n <= 64u) {
+        if (threadIdx.x < 64) wave_sort(a, s, static_cast<int>(n));
+        return;
+    }
     __shared__ __align__(16) uint32_t lds[SORT_LDS<CAP>];
     __shared__ uint32_t red[4 * (WG / 64)];
     if (n <= CAP ? bin_sort_lds<CAP>(a, s, static_cast<int>(n), lds, red) : bin_sort_global<false>(a, s, n, lds, red))

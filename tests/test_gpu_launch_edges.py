@@ -366,3 +366,39 @@ def test_adjoint_of_large_gaussians(n, cubic, frames):
     for name, g in a["grads"].items():
         if g is not None:
             assert torch.linalg.norm(g - b["grads"][name]) <= tol * torch.linalg.norm(g), name
+
+
+@pytest.mark.parametrize("depths", ["spread", "ties", "plane"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65])
+def test_buckets_of_one_wave(n, depths):
+    """Buckets that one wave sorts by comparison, the fullest and the first
+    beyond: images of one tile against the oracle."""
+    w = small_workload(300 + n, 16, 16, n, 1, z=(2.0, 6.0), ls=(1.5, 0.1))
+    rng = np.random.default_rng(n)
+    s = w["scene"]
+    s.means[0:2] *= 0.1
+    s.opacity_logits[:] = -3.0
+    s.means[2] = {"spread": s.means[2], "ties": 2.0 + 0.25 * rng.integers(0, 4, n), "plane": np.full(n, 4.0)}[depths]
+    out, ws, _ = run_clip(w, backward=False)
+    assert ws.status()["intersections"] == n
+    tally = PixelTally(f"one wave {depths} n={n}")
+    compare_image(out["images"].cpu().numpy()[0], oracle_frame(w, 0), tally.label, colour_range(w), tally)
+    tally.finish(set_aside_max=0.02)
+
+
+@pytest.mark.parametrize("n", [1536, 1537])
+def test_fine_bins_in_lds_and_in_memory(n):
+    """Half the depths within 1e-3 of each other among spread ones, in buckets
+    whose fine bins compare their keys in LDS and in memory: images of one tile
+    against the oracle, as in the test of the depth bins."""
+    w = small_workload(n, 16, 16, n, 1, z=(2.0, 6.0), ls=(1.5, 0.1))
+    rng = np.random.default_rng(n)
+    s = w["scene"]
+    s.means[0:2] *= 0.1
+    s.opacity_logits[:] = -5.0
+    s.opacity_logits[:: n // 20] = -3.0
+    s.means[2] = np.where(rng.random(n) < 0.5, 4.0 + 1e-3 * rng.random(n), s.means[2])
+    out, ws, _ = run_clip(w, backward=False)
+    tally = PixelTally(f"fine bins n={n}")
+    compare_image(out["images"].cpu().numpy()[0], oracle_frame(w, 0), tally.label, colour_range(w), tally)
+    tally.finish(set_aside_max=0.1)
