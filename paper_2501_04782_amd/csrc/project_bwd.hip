@@ -1336,11 +1336,11 @@ __global__ __launch_bounds__(FIN_THREADS) void k_adjoint_finalize(Args a, int64_
     }
 }
 
-__global__ __launch_bounds__(64) void k_intr_frames(Args a, int64_t n_blocks, const double* frame_intr) {
+__global__ __launch_bounds__(FIN_THREADS) void k_intr_frames(Args a, int64_t n_blocks, const double* frame_intr) {
+    __shared__ double red[FIN_THREADS], acc[12];
+    sum_parts<4>(frame_intr, n_blocks * 4, a.frames, red, acc);
     if (threadIdx.x >= 4) return;
-    double v = 0.0;
-    for (int f = 0; f < a.frames; ++f) v += frame_intr[static_cast<int64_t>(f) * n_blocks * 4 + threadIdx.x];
-    const float g = overflowed(a.status) ? 0.0f : static_cast<float>(v);
+    const float g = overflowed(a.status) ? 0.0f : static_cast<float>(acc[threadIdx.x]);
     if (a.accumulate) a.g_intr[threadIdx.x] += g;
     else a.g_intr[threadIdx.x] = g;
 }
@@ -1457,7 +1457,7 @@ hipError_t launch_project_bwd(const Args& a, hipStream_t stream) {
     if (pose_frames + intr > 0)
         hipLaunchKernelGGL(k_adjoint_finalize, dim3(static_cast<uint32_t>(pose_frames + intr)), dim3(FIN_THREADS), 0,
                            stream, a, nb, pose_frames, a.g_intr ? frame_intr : nullptr);
-    if (a.g_intr && frame_intr) hipLaunchKernelGGL(k_intr_frames, dim3(1), dim3(64), 0, stream, a, nb, frame_intr);
+    if (a.g_intr && frame_intr) hipLaunchKernelGGL(k_intr_frames, dim3(1), dim3(FIN_THREADS), 0, stream, a, nb, frame_intr);
     return hipGetLastError();
 }
 

@@ -402,3 +402,26 @@ def test_fine_bins_in_lds_and_in_memory(n):
     tally = PixelTally(f"fine bins n={n}")
     compare_image(out["images"].cpu().numpy()[0], oracle_frame(w, 0), tally.label, colour_range(w), tally)
     tally.finish(set_aside_max=0.1)
+
+
+@pytest.mark.parametrize("frames", [255, 256, 257, 700])
+def test_intrinsics_of_many_frames(frames):
+    """With dynamics the frames' intrinsics sums are added by 256 groups of four
+    threads: as many frames, one fewer and more, against the same clip in two
+    launches that accumulate.  FP64 sums, rounded once in one launch, twice and
+    added in the other: 3 roundings of 2^-24."""
+    rng = np.random.default_rng(frames)
+    scene_np = gv_synth.make_scene(rng, 70, z=(2.0, 6.0), log_scale=(-3.0, 0.3), n_ctrl=5)
+    w = dict(scene=scene_np, camera=gv_synth.make_camera(32, 32, 32.0), poses=gv_synth.make_trajectory(rng, frames),
+             times=gv_synth.make_times(frames), frames=frames, n=70)
+    scene, cam, poses, times = device_inputs(w)
+    dl = torch.from_numpy(rng.normal(0, 1, (frames, 3, 32, 32)).astype(np.float32)).cuda()
+    ws = raster.Workspace(cam, 70, frames, 4 * 70 * frames)
+    whole = raster.render_batch(scene, cam, poses, times, ws, dL_dimages=dl)["grads"]["intrinsics"].clone()
+    h, parts, size = frames // 2, None, 0.0
+    for part in (slice(0, h), slice(h, frames)):
+        one = raster.render_batch(scene, cam, poses[part], times[part], ws, dL_dimages=dl[part])["grads"]["intrinsics"]
+        parts, size = one.clone() if parts is None else parts + one, size + one.abs()
+    torch.cuda.synchronize()
+    assert ws.status()["overflow"] == 0
+    assert torch.all((whole - parts).abs() <= 3 * 2.0 ** -24 * size)
