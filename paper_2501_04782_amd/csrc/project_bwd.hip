@@ -1354,9 +1354,12 @@ __global__ __launch_bounds__(FIN_THREADS) void k_intr_frames(Args a, int64_t n_b
 // 1,094 us in one kernel, 580 in two, of 50k of 15 tiles 860 and 644, 500 640x360
 // frames of 100 of 41 tiles 6,159 and 341, 12 960x540 frames of 80k of 16 tiles 319
 // and 274; 16 1080p frames of 500k of ten tiles 1,068 and 1,202, 50 960x540 frames
-// of 200k of ten tiles 1,534 and 1,563, of four 620 and 808.
+// of 200k of ten tiles 1,534 and 1,563, of four 620 and 808.  Fewer Gaussians gain
+// from fewer tiles on: 50 frames of 2,000 of seven 184 and 62 us, 100 320x240 frames
+// of 300 of seven 170 and 72; four 128x128 frames of 500 of three 14 and 19.
 static bool large_gaussians(const Args& a) {
-    return a.k_cap / ((a.n <= 65536 ? 16 : 32) * static_cast<int64_t>(a.frames)) >= a.n;
+    const int64_t line = a.n <= 16384 ? 8 : a.n <= 65536 ? 16 : 32;  // of capacity, per (frame, Gaussian)
+    return a.k_cap / (line * a.frames) >= a.n;
 }
 
 // Gaussians per workgroup of each variant.
