@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+import gv_synth
 from parity_util import device_inputs, workspace_for
 from test_gpu_parity import small_workload
 
@@ -75,3 +76,51 @@ def test_autotuned_choice_runs_as_measured(tmp_path):
     finally:
         raster.set_tuning(old["batch"], old["sort_cap"], old["compact"], old["bwd_batch"])
     assert same_gradients(quadrant, bits()) == []
+
+
+@pytest.mark.parametrize("kind", ["static", "cubic", "dynamic", "sh"])
+@pytest.mark.parametrize("tight", [False, True])
+def test_two_adjoints_of_one_forward(kind, tight):
+    """A second and a third adjoint of one forward, with another upstream
+    gradient and with other kernels, accumulated or not, equal those of a
+    forward of their own; with spare capacity (the adjoint's values of every
+    frame lie in the sort's buffers) and without."""
+    rng = np.random.default_rng(21)
+    n, F, W, H = 2500, 5, 160, 96
+    kw = {"static": {}, "cubic": dict(cubic=True), "dynamic": dict(n_ctrl=6, poly_cov=True), "sh": dict(sh_degree=2)}[kind]
+    scene_np = gv_synth.make_scene(rng, n, z=(2.0, 8.0), log_scale=(-4.0, 0.4), **kw)
+    w = dict(scene=scene_np, camera=gv_synth.make_camera(W, H, float(W)), poses=gv_synth.make_trajectory(rng, F),
+             times=gv_synth.make_times(F), frames=F, n=n)
+    scene, cam, poses, times = device_inputs(w)
+    cap = raster.estimate_capacity(scene, cam, poses, times, margin=1.5)
+    ws = raster.Workspace(cam, n, F, cap + 4 * F * n)
+    if tight:
+        raster.render_batch(scene, cam, poses, times, ws, backward=False)
+        torch.cuda.synchronize()
+        ws = raster.Workspace(cam, n, F, ws.status()["intersections"])
+    ups = [torch.from_numpy(rng.normal(0, 1, (F, 3, H, W)).astype(np.float32)).cuda() for _ in range(3)]
+    settings = [(128, 1024, 52, 64), (128, 1024, 52, 128), (64, 512, 12, 64)]
+    old = raster.get_tuning()
+    try:
+        want = []
+        for up, t in zip(ups, settings):
+            raster.set_tuning(*t)
+            want.append(raster.render_batch(scene, cam, poses, times, ws, dL_dimages=up))
+        raster.set_tuning(*settings[0])
+        images = raster.render_batch(scene, cam, poses, times, ws, backward=False)["images"]
+        for up, t, x in zip(ups, settings, want):
+            raster.set_tuning(*t)
+            got = raster.render_batch(scene, cam, poses, times, ws, dL_dimages=up, forward=False, images=images)
+            torch.cuda.synchronize()
+            assert same_gradients(x["grads"], got["grads"]) == [] and torch.equal(x["dL_dposes"], got["dL_dposes"])
+        total = {k: None if g is None else g.clone() for k, g in want[2]["grads"].items()}
+        raster.render_batch(scene, cam, poses, times, ws, dL_dimages=ups[2], forward=False, images=images, grads=total,
+                            accumulate=True)
+        torch.cuda.synchronize()
+        assert ws.status()["overflow"] == 0
+        for k, g in want[2]["grads"].items():
+            # twice a sum is exact; the control points' window is added a span at a time
+            assert g is None or torch.allclose(total[k], 2 * g, rtol=4 * 2.0 ** -24 if k == "ctrl" else 0.0,
+                                               atol=4 * 2.0 ** -24 * float(g.abs().max()) if k == "ctrl" else 0.0), k
+    finally:
+        raster.set_tuning(old["batch"], old["sort_cap"], old["compact"], old["bwd_batch"])
