@@ -9,13 +9,14 @@ import torch
 import gv_synth
 from oracle import pyramid as pyr_ref
 from parity_util import PixelTally, colour_range, compare_image, device_inputs, oracle_frame, workspace_for
-from test_gpu_parity import check_clip_against_oracle, run_clip, small_workload
+from test_gpu_parity import check_clip_against_oracle, run_clip, say, small_workload
 from test_gpu_visibility_pyramid import check_visibility
 
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     from paper_2501_04782_amd import _lib as L
+    from paper_2501_04782_amd import camera as gvcam
     from paper_2501_04782_amd import raster
     from paper_2501_04782_amd.optim import Adan
 
@@ -425,3 +426,31 @@ def test_intrinsics_of_many_frames(frames):
     torch.cuda.synchronize()
     assert ws.status()["overflow"] == 0
     assert torch.all((whole - parts).abs() <= 3 * 2.0 ** -24 * size)
+
+
+def test_ode_activation_over_its_range():
+    """The camera MLP's tanh against 64 bits.  With no other weights the state of
+    one RK4 step is the output bias plus the second layer's activations of its
+    biases, so the three translations are tanh of three values to the last bit.
+    Below 0.55: half an ulp of the final sum, and 4 roundings and the fit of a
+    correction of less than a tenth of the result: one ulp.  Above: exp2 and
+    reciprocal off by an ulp each, argument and final rounding: three."""
+    rng = np.random.default_rng(3)
+    x = np.concatenate([np.geomspace(1e-30, 1e-2, 200), np.linspace(0.01, 0.56, 1500), np.linspace(0.5499, 0.5501, 300),
+                        np.linspace(0.55, 12.0, 900), [0.0, 20.0, 88.0, 1e4, 3e38, np.inf]]).astype(np.float32)
+    x *= rng.choice([-1.0, 1.0], x.size).astype(np.float32)
+    x = np.resize(x, (x.size + 2) // 3 * 3).reshape(-1, 3)
+    theta = torch.zeros(len(x), 5191, device="cuda")
+    theta[:, 4672:4675] = torch.from_numpy(x).cuda()  # b2 of units 0 to 2
+    for k in range(3):
+        theta[:, 4736 + (4 + k) * 64 + k] = 1.0  # W3 of the translations
+    z0 = torch.tensor([1.0, 0, 0, 0, 0, 0, 0], device="cuda")
+    ws = gvcam.OdeWorkspace(2, 1)
+    got = torch.stack([gvcam.CameraODE.apply(th, z0, 2, 1, ws)[1, 4:].clone() for th in theta]).cpu().numpy()
+    ref = np.tanh(x.astype(np.float64))
+    ulp = np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64)
+    err = np.abs(got - ref) / np.maximum(ulp, 1e-45)
+    small = np.abs(x) < 0.55
+    say(f"[ode tanh] error in ulp: {err[small].max():.3f} below 0.55, {err[~small].max():.3f} above")
+    assert np.all(np.sign(got) == np.sign(x)) and np.all(np.abs(got) <= 1.0)
+    assert err[small].max() <= 1.0 and err[~small].max() <= 3.0
