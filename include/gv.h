@@ -180,7 +180,18 @@ typedef struct {
 /* Bytes of workspace for up to `frames` frames of `n` Gaussians at the
  * camera's resolution, with room for `k_capacity` (Gaussian, tile)
  * intersections over all frames (a 16x16 tile grid; a typical random scene
- * at 960x540 has about 4 intersections per visible Gaussian per frame). */
+ * at 960x540 has about 4 intersections per visible Gaussian per frame).
+ *
+ * Capacity beyond the scene's intersections also buys speed, and the backward's
+ * results depend on it in their last bits (order and width of sums):
+ * - with dynamics or SH the projection adjoint runs in its faster form, which
+ *   also sums the SH gradients in FP64, from a k_capacity of 1.625 (SH), 1.75
+ *   (dynamics) or 2.125 (both) times frames * n on;
+ * - without either, a k_capacity of 8 (n up to 16,384), 16 (up to 65,536) or 32
+ *   times frames * n selects its forms for large Gaussians, which are slower
+ *   for small ones: give no more than the scene needs with a margin;
+ * - launches of fewer than 128 groups of 1,024 Gaussians bin faster where 16
+ *   k_capacity is at least 4 * ceil(n / 256) * frames * (tiles of the grid). */
 gv_status gv_workspace_bytes(const gv_camera *cam, int64_t n, int32_t frames, int64_t k_capacity,
                              size_t *out_bytes);
 
