@@ -93,7 +93,7 @@ def test_two_adjoints_of_one_forward(kind, tight):
              times=gv_synth.make_times(F), frames=F, n=n)
     scene, cam, poses, times = device_inputs(w)
     cap = raster.estimate_capacity(scene, cam, poses, times, margin=1.5)
-    ws = raster.Workspace(cam, n, F, cap + 4 * F * n)
+    ws = raster.Workspace(cam, n, F, cap + 8 * F * n)
     if tight:
         raster.render_batch(scene, cam, poses, times, ws, backward=False)
         torch.cuda.synchronize()
